@@ -1,0 +1,254 @@
+"""The work a user of this framework has it do, as cases that can be timed and compared.
+
+A case is one call, or the short run of calls that belong together, through paper_1802_09113_amd.binding:
+
+  evaluate   objective and predictions of a weight block over all rows (the forward pass: held-out evaluation, one
+             trial of a line search)
+  gradient   objective and gradient over all rows (the backward pass)
+  direction  sub-sampled Hessian prepared at the weights, then conjugate gradients for the Newton direction
+  step       two iterations of sub-sampled Newton (gradient, Hessian sample, CG, line search, update)
+
+over dense and CSR data, fp32 and fp64, binary and multi-class problems, from two thousand rows of fifty features to
+1.2 GB of data.  Sizes of the listed cases are those of the framework's own workloads (synth.py and the tests: the data
+sets of the paper's Table 1) next to odd ones.
+"""
+import math
+
+import torch
+
+from paper_1802_09113_amd.binding import Context
+
+DTYPES = {"f32": torch.float32, "f64": torch.float64}
+
+# The largest listed data: nothing drawn has more elements than the wide matrix or more stored entries than the text.
+MAX_DENSE = 50000 * 3072
+MAX_NNZ = 20000 * 450
+
+THETA, T = 1e-4, 10            # CG: relative residual and product budget of every run
+STEPS = 2                      # Newton iterations of one "step" pass
+
+
+def listed():
+    return [
+        # the smallest problem anyone runs: a Newton step is a chain of short launches, host and latency are all of it
+        dict(name="tiny_step", kind="step", data="gauss", n=2000, p=50, C=3, dtype="f64", nS=100, lam=1e-3),
+        # image-like rows (60000 x 784, ten classes): the first-order information of one iteration in single precision
+        dict(name="image_gradient_f32", kind="gradient", data="pixels", n=60000, p=784, C=10, dtype="f32", nS=0, lam=1e-4),
+        # the same data in double precision: what one user-visible iteration costs, 5 % Hessian sample
+        dict(name="image_step", kind="step", data="pixels", n=60000, p=784, C=10, dtype="f64", nS=3000, lam=1e-4),
+        # the largest dense matrix (1.23 GB): full gradient
+        dict(name="wide_gradient", kind="gradient", data="centred", n=50000, p=3072, C=10, dtype="f64", nS=0, lam=1e-4),
+        # the same matrix in single precision, whole iterations
+        dict(name="wide_step_f32", kind="step", data="centred", n=50000, p=3072, C=10, dtype="f32", nS=2500, lam=1e-4),
+        # very many rows of few features (measurements and indicator columns), 1 % sample
+        dict(name="tall_step_f32", kind="step", data="tabular", n=581012, p=54, C=7, dtype="f32", nS=5810, lam=1e-5),
+        # no sampling: the exact Newton direction over every row of a sensor table (50000 x 48, eleven classes)
+        dict(name="full_direction", kind="direction", data="gauss", n=50000, p=48, C=11, dtype="f64", nS=50000, lam=1e-4),
+        # odd everything, more than sixteen weight columns: evaluation of a model on held-out rows
+        dict(name="ragged_evaluate_f32", kind="evaluate", data="gauss", n=10007, p=331, C=24, dtype="f32", nS=0, lam=1e-4),
+        # text with a vocabulary of 1.36 million words and twenty classes: whole iterations
+        dict(name="text_step", kind="step", data="text", n=20000, p=1355191, C=20, dtype="f64", nS=1000, lam=1e-4, nnz_row=450),
+        # its gradient in single precision
+        dict(name="text_gradient_f32", kind="gradient", data="text", n=20000, p=1355191, C=20, dtype="f32", nS=0, lam=1e-4,
+             nnz_row=450),
+        # two classes, dense: matrix-vector work (6000 x 5000), direction from a 300-row sample
+        dict(name="binary_direction", kind="direction", data="genes", n=6000, p=5000, C=2, dtype="f64", nS=300, lam=1e-2),
+        # two classes, short sparse rows
+        dict(name="binary_text_step_f32", kind="step", data="text", n=65078, p=20958, C=2, dtype="f32", nS=3254, lam=1e-3,
+             nnz_row=57),
+    ]
+
+
+def _log_int(rng, lo, hi):
+    return int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+
+
+def draw(rng):
+    """One more case; none that asks for more bytes or operations than the listed ones do."""
+    works = [work(c) for c in listed()]
+    most = {k: max(w[k] for w in works) for k in ("bytes", "flops")}
+    while True:
+        case = _draw(rng)
+        w = work(case)
+        if all(w[k] <= most[k] for k in most):
+            return case
+
+
+def _stiff(case):
+    return case["data"] in ("pixels", "genes", "tabular") and case["C"] <= 3
+
+
+def _draw(rng):
+    kind = rng.choice(["evaluate", "gradient", "direction", "step", "step"])
+    dtype = rng.choice(["f32", "f64"])
+    if rng.random() < 0.7:
+        data = rng.choice(["gauss", "pixels", "centred", "tabular", "genes"])
+        # uncentred data are badly conditioned beyond a thousand features: two correct fp32 runs part ways there
+        p = _log_int(rng, 20, 1000 if data in ("pixels", "genes") else 5000)
+        C = rng.choice([2, 3, 5, 7, 10, 11, 11, 17, 24, 33])
+        n = _log_int(rng, 2000, min(600000, MAX_DENSE // p))
+        case = dict(kind=kind, data=data, n=n, p=p, C=C, dtype=dtype)
+    else:
+        C = rng.choice([2, 2, 5, 10, 20, 33])
+        nnz_row = _log_int(rng, 20, 450)
+        n = _log_int(rng, 2000, min(70000, MAX_NNZ // nnz_row))
+        p = _log_int(rng, max(4000, 20 * nnz_row), 1355191 if C <= 20 else 800000)
+        case = dict(kind=kind, data="text", n=n, p=p, C=C, dtype=dtype, nnz_row=nnz_row)
+    case["nS"] = 0
+    if kind in ("direction", "step"):
+        # samples of 1 to 20 %; now and then every row of a matrix small enough for it
+        small = case["data"] != "text" and case["n"] * case["p"] <= MAX_DENSE // 32
+        share = 1.0 if small and rng.random() < 0.2 else math.exp(rng.uniform(math.log(0.01), math.log(0.2)))
+        cap = MAX_DENSE // 8 // case["p"] if case["data"] != "text" else 2000
+        case["nS"] = max(100, min(int(case["n"] * share), cap if share < 1.0 else case["n"]))
+    # two or three classes of uncentred data: only with the stronger regularisation (conditioning, as above)
+    case["lam"] = 1e-2 if _stiff(case) else rng.choice([1e-2, 1e-3])
+    return case
+
+
+# ---- inputs ----------------------------------------------------------------------------------------------------------
+
+def _dense(case, g, dev):
+    """Rows with the values such data have: normal measurements, pixels (mostly zero), mean-centred pixels, a few
+    measurements among indicator columns, sparse expression levels."""
+    n, p, dt, kind = case["n"], case["p"], DTYPES[case["dtype"]], case["data"]
+    if kind == "gauss":
+        return torch.randn(n, p, generator=g, device=dev, dtype=dt)
+    if kind == "tabular":
+        X = (torch.rand(n, p, generator=g, device=dev, dtype=torch.float32) < 0.05).to(dt)
+        m = min(10, p)
+        X[:, :m] = torch.randn(n, m, generator=g, device=dev, dtype=dt)
+        return X
+    X = torch.rand(n, p, generator=g, device=dev, dtype=dt)
+    if kind == "centred":
+        X -= X.mean(dim=1, keepdim=True)
+    else:
+        X *= torch.rand(n, p, generator=g, device=dev, dtype=torch.float32) < (0.2 if kind == "pixels" else 0.13)
+    return X
+
+
+def _text(case, g, dev):
+    """Bag-of-words rows: distinct Zipf(1.1) word ids in ascending order, document lengths that vary around the mean,
+    lognormal weights, rows of unit norm."""
+    n, p, mean = case["n"], case["p"], case["nnz_row"]
+    length = mean * torch.exp(0.4 * torch.randn(n, generator=g, device=dev, dtype=torch.float64) - 0.08)
+    length = length.clamp(1, 3 * mean).to(torch.int64)
+    w = torch.arange(1, p + 1, device=dev, dtype=torch.float64) ** -1.1
+    cdf = torch.cumsum(w, 0)
+    cdf /= cdf[-1].clone()
+    m = 6 * mean                                     # draws per row, of which the first `length` distinct ones stay
+    ids, counts = [], []
+    for lo in range(0, n, 4096):
+        ln = length[lo:lo + 4096, None]
+        u = torch.rand(ln.shape[0], m, generator=g, device=dev, dtype=torch.float64)
+        d = torch.searchsorted(cdf, u).clamp_(max=p - 1).to(torch.int32)
+        srt, order = torch.sort(d, dim=1, stable=True)
+        new = torch.ones_like(srt, dtype=torch.bool)
+        new[:, 1:] = srt[:, 1:] != srt[:, :-1]
+        first = torch.zeros_like(new).scatter_(1, order, new)          # first draws of their word, in draw order
+        keep = first & (torch.cumsum(first, 1) <= ln)
+        kept = torch.gather(keep, 1, order)                            # the same, in word order
+        ids.append(srt[kept])
+        counts.append(kept.sum(1))
+    colidx, counts = torch.cat(ids), torch.cat(counts)
+    rowptr = torch.zeros(n + 1, device=dev, dtype=torch.int64)
+    rowptr[1:] = torch.cumsum(counts, 0)
+    vals = torch.exp(torch.randn(colidx.shape[0], generator=g, device=dev, dtype=torch.float64))
+    norm = torch.sqrt(torch.segment_reduce(vals * vals, "sum", lengths=counts))
+    vals /= torch.repeat_interleave(norm, counts)
+    return rowptr.to(torch.int32), colidx, vals.to(DTYPES[case["dtype"]])
+
+
+def _labels(scores, g):
+    """One draw per row from softmax(scores), scores brought to a spread of two."""
+    scores = scores * (2.0 / scores.std().clamp(min=1e-9))
+    u = torch.rand(scores.shape, generator=g, device=scores.device, dtype=scores.dtype).clamp(1e-30, 1 - 1e-7)
+    return torch.argmax(scores - torch.log(-torch.log(u)), dim=1).to(torch.int32)
+
+
+def prepare(case, seed):
+    dev = torch.device("cuda")
+    g = torch.Generator(device=dev)
+    g.manual_seed(seed)
+    n, p, C, dt = case["n"], case["p"], case["C"], DTYPES[case["dtype"]]
+    true = torch.randn(p, C, generator=g, device=dev, dtype=torch.float32)
+    if case["data"] == "text":
+        csr = _text(case, g, dev)
+        A = torch.sparse_csr_tensor(csr[0], csr[1], csr[2].float(), size=(n, p))
+        labels = _labels(A @ true, g)
+        ctx = Context(labels, C, case["lam"], csr=csr, p=p)
+    else:
+        X = _dense(case, g, dev)
+        scores = torch.cat([X[lo:lo + 65536].float() @ true for lo in range(0, n, 65536)])
+        labels = _labels(scores, g)
+        ctx = Context(labels, C, case["lam"], X=X)
+    # weights as they are within a run: small, not zero
+    W = (0.01 * torch.randn(p, C - 1, generator=g, device=dev, dtype=torch.float64)).to(dt)
+    state = dict(kind=case["kind"], ctx=ctx, W=W)
+    if case["kind"] == "gradient":
+        state["G"] = torch.empty_like(W)
+    elif case["kind"] == "direction":
+        state["S"] = torch.sort(torch.randperm(n, generator=g, device=dev)[:case["nS"]]).values.to(torch.int32)
+        state["G"], _ = ctx.ssn_gradient(W)
+        state["P"] = torch.empty_like(W)
+    elif case["kind"] == "step":
+        state["S"] = torch.stack([torch.sort(torch.randperm(n, generator=g, device=dev)[:case["nS"]]).values
+                                  for _ in range(STEPS)]).to(torch.int32)
+        state["W_run"] = torch.empty_like(W)
+    return state
+
+
+def run(state):
+    ctx, W, kind = state["ctx"], state["W"], state["kind"]
+    if kind == "evaluate":
+        f = ctx.ssn_objective(W)
+        pred, acc = ctx.ssn_predict(W)
+        return [f, pred, acc]
+    if kind == "gradient":
+        G, f = ctx.ssn_gradient(W, state["G"])
+        return [G, f]
+    if kind == "direction":
+        ctx.ssn_hess_prepare(W, state["S"])
+        out = ctx.ssn_cg(state["G"], THETA, T, state["P"])
+        return [out["p"]]
+    state["W_run"].copy_(W)
+    log, _ = ctx.ssn_solve(state["W_run"], state["S"], theta=THETA, T=T, phase_times=False)
+    return [state["W_run"], [r["f"] for r in log]]
+
+
+# ---- what a pass cannot do without -----------------------------------------------------------------------------------
+
+def work(case):
+    """Every input once per pass over it that the method asks for: the data once for an evaluation (objective and
+    predictions share one), once for objective and gradient, the sampled rows once per Newton direction (they are
+    the same for all its products), the weights in and the result out.  A step pass evaluates objective and gradient
+    at its start and after its first iteration, and the objective once more at the end."""
+    n, p, K, nS = case["n"], case["p"], case["C"] - 1, case["nS"]
+    e = 4 if case["dtype"] == "f32" else 8
+    if case["data"] == "text":
+        row_bytes, row_els = case["nnz_row"] * (e + 4) + 4, case["nnz_row"]
+    else:
+        row_bytes, row_els = p * e, p
+    data, sample, block = n * (row_bytes + 4), nS * (row_bytes + 4), p * K * e
+    product = 2.0 * n * row_els * K                       # one product with all rows
+    direction = 2.0 * nS * row_els * K * (1 + 2 * T)      # margins of the sample, T products of two passes
+    if case["kind"] == "evaluate":
+        return dict(bytes=data + block + 4 * n, flops=product)
+    if case["kind"] == "gradient":
+        return dict(bytes=data + 2 * block, flops=2 * product)
+    if case["kind"] == "direction":
+        return dict(bytes=sample + 3 * block, flops=direction)
+    return dict(bytes=(STEPS + 1) * data + STEPS * sample + 2 * STEPS * block,
+                flops=(2 * STEPS + 1) * product + STEPS * direction)
+
+
+def tolerance(case):
+    """About four times what the same rows in another order change in a result, over the listed and 300 drawn cases.
+    Gradients of text are sparse in size (few large entries, a million small ones), hence their "max".  Directions and
+    steps go through ten products of CG, which amplify the rounding of one product a thousandfold and more."""
+    f32 = case["dtype"] == "f32"
+    if case["kind"] == "evaluate":
+        return dict(rel=1e-6, differ=1e-3) if f32 else dict(rel=1e-12, differ=1e-5)
+    if case["kind"] == "gradient":
+        return dict(rel=2e-6, max=1e-3) if f32 else dict(rel=1e-12, max=1e-9)
+    return dict(rel=1e-2, max=0.2) if f32 else dict(rel=1e-4, max=5e-3)
