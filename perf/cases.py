@@ -216,6 +216,119 @@ def run(state):
     return [state["W_run"], [r["f"] for r in log]]
 
 
+# ---- the same results in plain torch, 64 bits ------------------------------------------------------------------------
+
+class _Exact:
+    """The problem of a prepared state in double precision: data from the tensors that the context borrows."""
+
+    def __init__(self, case, state):
+        keep = state["ctx"]._keep
+        self.labels, self.X = keep[0].long(), None if case["data"] == "text" else keep[1].double()
+        self.n, self.p, self.K, self.lam = case["n"], case["p"], case["C"] - 1, case["lam"]
+        if self.X is None:
+            self.rowptr, self.col, self.val = keep[1].long(), keep[2].long(), keep[3].double()
+            self.row = torch.repeat_interleave(torch.arange(self.n, device=self.val.device), self.rowptr.diff())
+
+    def rows(self, S):
+        """The sampled rows as an operand of margins() and back(): dense rows or (rows, columns, values)."""
+        if self.X is not None:
+            return self.X if S is None else self.X[S.long()]
+        if S is None:
+            return self.n, self.row, self.col, self.val
+        place = torch.full((self.n,), -1, device=self.val.device)
+        place[S.long()] = torch.arange(S.numel(), device=self.val.device)
+        mine = place[self.row] >= 0
+        return S.numel(), place[self.row[mine]], self.col[mine], self.val[mine]
+
+    @staticmethod
+    def margins(A, W):
+        if torch.is_tensor(A):
+            return torch.cat([a @ W for a in A.split(65536)])
+        m, row, col, val = A
+        Z = torch.zeros(m, W.shape[1], device=W.device, dtype=torch.float64)
+        for lo in range(0, row.numel(), 1 << 21):
+            e = slice(lo, lo + (1 << 21))
+            Z.index_add_(0, row[e], val[e, None] * W[col[e]])
+        return Z
+
+    def back(self, A, U):
+        G = torch.zeros(self.p, self.K, device=U.device, dtype=torch.float64)
+        if torch.is_tensor(A):
+            for a, u in zip(A.split(65536), U.split(65536)):
+                G += a.t().contiguous() @ u
+            return G
+        _, row, col, val = A
+        for lo in range(0, row.numel(), 1 << 21):
+            e = slice(lo, lo + (1 << 21))
+            G.index_add_(0, col[e], val[e, None] * U[row[e]])
+        return G
+
+    def value(self, W, gradient=False):
+        A = self.rows(None)
+        Z = torch.cat([self.margins(A, W), torch.zeros(self.n, 1, device=W.device, dtype=torch.float64)], dim=1)
+        each = torch.arange(self.n, device=W.device)
+        f = float((torch.logsumexp(Z, 1) - Z[each, self.labels]).sum() / self.n + 0.5 * self.lam * (W * W).sum())
+        if not gradient:
+            return f, Z
+        U = torch.softmax(Z, 1)
+        U[each, self.labels] -= 1
+        return f, self.back(A, U[:, :-1].contiguous()) / self.n + self.lam * W
+
+    def direction(self, W, S, g):
+        """Conjugate gradients on H_S p = -g, at most T products; the iterate of the smallest residual."""
+        A = self.rows(S)
+        Q = torch.softmax(torch.cat([self.margins(A, W), torch.zeros(S.numel(), 1, device=W.device, dtype=torch.float64)], 1), 1)
+        Q = Q[:, :-1].contiguous()
+        p, r = torch.zeros_like(g), -g
+        s, best, least, first = r.clone(), r.clone(), float(r.norm()), float(g.norm())
+        for _ in range(T):
+            QZ = Q * self.margins(A, s)
+            H = self.back(A, QZ - Q * QZ.sum(1, keepdim=True)) / S.numel() + self.lam * s
+            curve = float((s * H).sum())
+            if not curve > 0:
+                break
+            old = float((r * r).sum())
+            p, r = p + old / curve * s, r - old / curve * H
+            norm = float(r.norm())
+            if norm <= least:
+                best, least = p, norm
+            if norm <= THETA * first:
+                break
+            s = r + norm * norm / old * s
+        return best
+
+
+def exact(case, seed):
+    """Objective, gradient, direction and steps in 64 bits.  A direction in single precision has no such value: ten
+    products of CG amplify the rounding of one product far beyond what a comparison of two errors could tell apart."""
+    if case["dtype"] == "f32" and case["kind"] in ("direction", "step"):
+        return None
+    state = prepare(case, seed)
+    e, W = _Exact(case, state), state["W"].double()
+    if case["kind"] == "evaluate":
+        f, Z = e.value(W)
+        Z[:, -1] = 0
+        best = torch.argmax(Z, 1).to(torch.int32)
+        return [f, best, float((best == e.labels).double().mean())]
+    if case["kind"] == "gradient":
+        f, G = e.value(W, gradient=True)
+        return [G, f]
+    if case["kind"] == "direction":
+        return [e.direction(W, state["S"], e.value(W, gradient=True)[1])]
+    values = []
+    for S in state["S"]:
+        f, g = e.value(W, gradient=True)
+        values.append(f)
+        P = e.direction(W, S, g)
+        alpha, slope = 1.0, float((P * g).sum())
+        for _ in range(11):
+            if e.value(W + alpha * P)[0] <= f + 1e-4 * alpha * slope:
+                break
+            alpha *= 0.5
+        W = W + alpha * P
+    return [W, values]
+
+
 # ---- what a pass cannot do without -----------------------------------------------------------------------------------
 
 def work(case):
