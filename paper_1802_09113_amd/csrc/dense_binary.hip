@@ -163,6 +163,95 @@ template <typename T, int VEC, int MODE> __global__ __launch_bounds__(256) void 
     }
 }
 
+// Few rows (the sampled rows of a product, a small matrix): a workgroup of up to eight waves per row.  Two rows per
+// wave, as above, puts 300 sampled rows on 150 waves for 1024 SIMDs, and each wave walks its 2 x 40 KB in five dependent
+// trips; here a row's vectors are spread over as many threads as leave each about four of them (binary_rows_plan), all
+// requested together, and the wave sums run on the vector units (DPP) before one exchange through LDS.  What bounds it
+// is that one trip to memory and the reduction behind it, not bandwidth.
+constexpr int BSPLIT_WAVES = 8;
+template <typename T, int VEC, int MODE> __global__ __launch_bounds__(BSPLIT_WAVES * 64) void binary_row_split_kernel(RowsArgs a)
+{
+    if (a.skip && *a.skip) return;
+    typedef BPack<T, VEC> pack;
+    struct wpack { T v[VEC]; };              // element alignment: the weights may start anywhere
+    constexpr int UNR = 8;
+    constexpr bool TWO = MODE == ROW_MARGIN;
+    __shared__ double red[2][2][BSPLIT_WAVES];       // two buffers in turn: one barrier per row
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, NT = blockDim.x, nw = NT >> 6;
+    const T *X = (const T *)a.X, *w = (const T *)a.M, *w2 = TWO ? (const T *)a.M2 : w;
+    const int64_t p = a.p, ldm = a.ldm;
+    const int64_t pv = p / VEC * VEC;
+    double loss = 0.0;
+    int hits = 0, buf = 0;
+    auto weights = [&](const T *base, int64_t g) {
+        wpack r;
+        if (ldm == 1) r = *(const wpack *)(base + g);
+        else
+#pragma unroll
+            for (int m = 0; m < VEC; ++m) r.v[m] = base[(g + m) * ldm];
+        return r;
+    };
+    for (int64_t s0 = blockIdx.x; s0 < a.nrows; s0 += gridDim.x, buf ^= 1) {
+        const int64_t r0 = a.S ? (int64_t)a.S[s0] : s0;
+        const T *x = X + r0 * a.ldx;
+        T z = 0, y = 0;
+        for (int64_t f = (int64_t)tid * VEC; f < pv; f += (int64_t)UNR * NT * VEC) {
+            pack xa[UNR] = {};
+            wpack wa[UNR] = {}, wb[TWO ? UNR : 1] = {};
+#pragma unroll
+            for (int u = 0; u < UNR; ++u) {
+                const int64_t g = f + (int64_t)u * NT * VEC;
+                if (g >= pv) continue;
+                xa[u] = *(const pack *)(x + g);
+                wa[u] = weights(w, g);
+                if constexpr (TWO) wb[u] = weights(w2, g);
+            }
+#pragma unroll
+            for (int u = 0; u < UNR; ++u)
+#pragma unroll
+                for (int m = 0; m < VEC; ++m) {
+                    z += xa[u].v[m] * wa[u].v[m];
+                    if constexpr (TWO) y += xa[u].v[m] * wb[u].v[m];
+                }
+        }
+        for (int64_t g = pv + tid; g < p; g += NT) {           // features beyond the last whole vector
+            z += x[g] * w[g * ldm];
+            if constexpr (TWO) y += x[g] * w2[g * ldm];
+        }
+        const double zs = wave_inclusive_scan((double)z);      // lane 63: the wave's sum
+        double ys = 0.0;
+        if constexpr (TWO) ys = wave_inclusive_scan((double)y);
+        if (lane == 63) {
+            red[buf][0][wv] = zs;
+            if constexpr (TWO) red[buf][1][wv] = ys;
+        }
+        __syncthreads();
+        if (wv == 0) {
+            double t = 0.0, t2 = 0.0;
+#pragma unroll
+            for (int k = 0; k < BSPLIT_WAVES; ++k) {
+                if (k >= nw) break;
+                t += red[buf][0][k];
+                if constexpr (TWO) t2 += red[buf][1][k];
+            }
+            if constexpr (TWO) {
+                if (lane == 0) {
+                    T *Z = (T *)a.UP;
+                    Z[s0 * a.KP] = (T)t;
+                    Z[s0 * a.KP + 1] = (T)t2;
+                }
+            } else {
+                binary_row<T, MODE>(a, s0, r0, (T)t, lane, loss, hits);
+            }
+        }
+    }
+    if constexpr (MODE == ROW_OBJ || MODE == ROW_GRAD || MODE == ROW_APPLY) {
+        if (tid == 0) a.loss_part[blockIdx.x] = loss;
+    } else if constexpr (MODE == ROW_PRED) {
+        if (tid == 0) a.hit_part[blockIdx.x] = hits;
+    }
+}
+
 // grid: (feature tiles of 256 * VEC, row chunks)
 template <typename T, int VEC> __global__ __launch_bounds__(256) void binary_xtu_kernel(XtuArgs a)
 {
@@ -210,16 +299,21 @@ template <typename T, int VEC> __global__ __launch_bounds__(256) void binary_xtu
         if (f + m < a.p) part[f + m] = acc[m];
 }
 
-template <typename T, int VEC> hipError_t rows_mode(const RowsArgs &a, int blocks, hipStream_t st)
+template <typename T, int VEC, int MODE> void rows_go(const RowsArgs &a, int blocks, int split, hipStream_t st)
 {
-    dim3 grid(blocks), block(256);
+    if (split) hipLaunchKernelGGL((binary_row_split_kernel<T, VEC, MODE>), dim3(blocks), dim3(split), 0, st, a);
+    else hipLaunchKernelGGL((binary_rows_kernel<T, VEC, MODE>), dim3(blocks), dim3(256), 0, st, a);
+}
+
+template <typename T, int VEC> hipError_t rows_mode(const RowsArgs &a, int blocks, int split, hipStream_t st)
+{
     switch (a.mode) {
-    case ROW_OBJ: hipLaunchKernelGGL((binary_rows_kernel<T, VEC, ROW_OBJ>), grid, block, 0, st, a); break;
-    case ROW_GRAD: hipLaunchKernelGGL((binary_rows_kernel<T, VEC, ROW_GRAD>), grid, block, 0, st, a); break;
-    case ROW_PREP: hipLaunchKernelGGL((binary_rows_kernel<T, VEC, ROW_PREP>), grid, block, 0, st, a); break;
-    case ROW_APPLY: hipLaunchKernelGGL((binary_rows_kernel<T, VEC, ROW_APPLY>), grid, block, 0, st, a); break;
-    case ROW_PRED: hipLaunchKernelGGL((binary_rows_kernel<T, VEC, ROW_PRED>), grid, block, 0, st, a); break;
-    case ROW_MARGIN: hipLaunchKernelGGL((binary_rows_kernel<T, VEC, ROW_MARGIN>), grid, block, 0, st, a); break;
+    case ROW_OBJ: rows_go<T, VEC, ROW_OBJ>(a, blocks, split, st); break;
+    case ROW_GRAD: rows_go<T, VEC, ROW_GRAD>(a, blocks, split, st); break;
+    case ROW_PREP: rows_go<T, VEC, ROW_PREP>(a, blocks, split, st); break;
+    case ROW_APPLY: rows_go<T, VEC, ROW_APPLY>(a, blocks, split, st); break;
+    case ROW_PRED: rows_go<T, VEC, ROW_PRED>(a, blocks, split, st); break;
+    case ROW_MARGIN: rows_go<T, VEC, ROW_MARGIN>(a, blocks, split, st); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -232,21 +326,32 @@ template <typename T> bool rows_aligned(const void *X, int64_t ldx)
 
 }  // namespace
 
-// workgroups (4 waves each, one loss / hit partial per wave) for a pass over nrows rows, two rows per wave and trip
-int binary_rows_blocks(int64_t nrows, int num_cus)
+// workgroups and loss / hit partials of a pass over nrows rows of p features: a workgroup of *split threads per row (one
+// partial each) for up to four rows per compute unit, else (*split = 0) four waves of two rows at a time (four partials
+// each).  Product call on nS sampled rows, two rows per wave / workgroup per row, us (10 is the host's own time):
+//   p = 5000  fp64: nS 100 15.5/10.4  300 20.9/12.6  1000 27.3/21.9  2000 36.6/36.7   fp32: 300 15.5/12.5  1000 18.5/18.2  2000 23.2/29.5
+//   p = 20000 fp64: 100 49.5/16.9  1000 73.4/55.2  3000 177.6/175.9                   fp32: 100 32.4/16.1  1000 49.1/45.7  2000 62.0/77.4
+//   p = 512 and less: equal up to 2000 rows.
+void binary_rows_plan(int64_t nrows, int64_t p, int64_t es, int num_cus, int *blocks, int *parts, int *split)
 {
-    int64_t b = (nrows + 7) / 8;
+    const bool few = nrows <= (int64_t)num_cus * 4;
+    int64_t nt = (p * es / 64 + 63) / 64 * 64;               // four 16-byte vectors per thread
+    if (nt > BSPLIT_WAVES * 64) nt = BSPLIT_WAVES * 64;
+    if (nt < 64) nt = 64;
+    *split = few ? (int)nt : 0;
+    int64_t b = *split ? nrows : (nrows + 7) / 8;
     const int64_t cap = (int64_t)num_cus * 8;
     if (b > cap) b = cap;
-    return (int)(b < 1 ? 1 : b);
+    *blocks = (int)(b < 1 ? 1 : b);
+    *parts = *split ? *blocks : *blocks * ROWS_WAVES_PER_BLOCK;
 }
 
-hipError_t launch_binary_rows(int dtype, const RowsArgs &a, int blocks, hipStream_t st)
+hipError_t launch_binary_rows(int dtype, const RowsArgs &a, int blocks, int split, hipStream_t st)
 {
     if (a.K != 1) return hipErrorInvalidValue;
     if (dtype == SSN_F32)
-        return rows_aligned<float>(a.X, a.ldx) ? rows_mode<float, 4>(a, blocks, st) : rows_mode<float, 1>(a, blocks, st);
-    return rows_aligned<double>(a.X, a.ldx) ? rows_mode<double, 2>(a, blocks, st) : rows_mode<double, 1>(a, blocks, st);
+        return rows_aligned<float>(a.X, a.ldx) ? rows_mode<float, 4>(a, blocks, split, st) : rows_mode<float, 1>(a, blocks, split, st);
+    return rows_aligned<double>(a.X, a.ldx) ? rows_mode<double, 2>(a, blocks, split, st) : rows_mode<double, 1>(a, blocks, split, st);
 }
 
 hipError_t launch_binary_xtu(int dtype, const XtuArgs &a, hipStream_t st)

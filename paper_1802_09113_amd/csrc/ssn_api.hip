@@ -270,10 +270,12 @@ int launch_rows(ssn_ctx *c, const RowsArgs &a, int *nparts)
         }
     }
     if (c->binary) {
-        const int blocks = binary_rows_blocks(a.nrows, c->num_cus);
-        if (blocks * ROWS_WAVES_PER_BLOCK > c->wave_parts) return fail(c, SSN_E_INVALID_ARG, "internal: wave partial overflow");
-        SSN_HIP(c, launch_binary_rows(c->d.dtype, a, blocks, c->st));
-        if (nparts) *nparts = blocks * ROWS_WAVES_PER_BLOCK;
+        int blocks = 0, parts = 0;
+        int split = 0;
+        binary_rows_plan(a.nrows, c->d.p, (int64_t)c->es, c->num_cus, &blocks, &parts, &split);
+        if (parts > c->wave_parts) return fail(c, SSN_E_INVALID_ARG, "internal: wave partial overflow");
+        SSN_HIP(c, launch_binary_rows(c->d.dtype, a, blocks, split, c->st));
+        if (nparts) *nparts = parts;
         return SSN_OK;
     }
     if (use_fused(c, a)) {

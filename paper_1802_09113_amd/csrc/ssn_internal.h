@@ -138,8 +138,9 @@ int dense_narrow_max_grid(int64_t p, int num_cus);       // 0: no narrow launch 
 hipError_t launch_dense_narrow(int dtype, const RowsArgs &a, int grid, hipStream_t st);
 hipError_t launch_csr_rows(int dtype, const RowsArgs &a, int blocks, hipStream_t st);
 // binary problem (K = 1) on a dense matrix: matrix-vector kernels on the vector units (dense_binary.hip)
-int binary_rows_blocks(int64_t nrows, int num_cus);
-hipError_t launch_binary_rows(int dtype, const RowsArgs &a, int blocks, hipStream_t st);
+// *split: threads of a workgroup per row, 0 for the wave-per-two-rows form; *parts: loss / hit partials the launch leaves
+void binary_rows_plan(int64_t nrows, int64_t p, int64_t es, int num_cus, int *blocks, int *parts, int *split);
+hipError_t launch_binary_rows(int dtype, const RowsArgs &a, int blocks, int split, hipStream_t st);
 hipError_t launch_binary_xtu(int dtype, const XtuArgs &a, hipStream_t st);
 hipError_t launch_finalize(int dtype, const FinArgs &a, int blocks, hipStream_t st);
 

@@ -81,6 +81,19 @@ def test_dense_binary_calls(p, ldx, xoff, dtype):
 
 
 @pytest.mark.parametrize("dtype", DTYPES, ids=["f64", "f32"])
+@pytest.mark.parametrize("n,p,ldw", [(1024, 515, 3), (1025, 515, 1), (700, 8197, 3), (301, 16390, 1)],
+                         ids=["last_split", "first_paired", "two_trips_f64", "two_trips_tail"])
+def test_dense_binary_workgroup_per_row(n, p, ldw, dtype):
+    # a workgroup per row up to 1024 rows, weights packed and strided; 8197 and 16390 features leave a second trip of
+    # vectors per thread and a tail behind the whole vectors
+    d = synth.make(5, n=n, p=p)
+    pair = Pair(d, dtype, lam=LAM, ldw=ldw)
+    print(f"[case] dense binary n={n} p={p} ldw={ldw} dtype={dtype}", flush=True)
+    _check_calls(pair, n, 120, dtype, path=3)
+    pair.close()
+
+
+@pytest.mark.parametrize("dtype", DTYPES, ids=["f64", "f32"])
 def test_sparse_binary_calls(dtype):
     n = 3001
     d = workload(6, n)
