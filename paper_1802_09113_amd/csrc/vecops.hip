@@ -9,13 +9,18 @@
 
 namespace ssn {
 
-// sum over the block's VEC_BLOCK threads, the same bits in every thread: a butterfly inside each wave,
-// then the four wave sums in order
+// Sum over the wave, complete in lane 63: the last value of the scan on the vector units (DPP).  Most kernels of this
+// file are chains of a memory trip, a reduction and another trip, and a butterfly through LDS (six steps of two 32-bit
+// exchanges each) made every reduction on that chain a third of a microsecond longer.  All lanes must be active.
+__device__ __forceinline__ double wave_sum_last(double v) { return wave_inclusive_scan(v); }
+
+// sum over the block's VEC_BLOCK threads, the same bits in every thread: inside each wave, then the four wave sums
+// in order
 __device__ __forceinline__ double block_sum(double v)
 {
     __shared__ double sm[VEC_BLOCK / 64];
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-    if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = v;
+    v = wave_sum_last(v);
+    if ((threadIdx.x & 63) == 63) sm[threadIdx.x >> 6] = v;
     __syncthreads();
     double r = sm[0];
 #pragma unroll
@@ -28,11 +33,9 @@ __device__ __forceinline__ double block_sum(double v)
 __device__ __forceinline__ void block_sum2(double a, double b, double &ra, double &rb)
 {
     __shared__ double sm2[2 * (VEC_BLOCK / 64)];
-    for (int off = 32; off > 0; off >>= 1) {
-        a += __shfl_xor(a, off);
-        b += __shfl_xor(b, off);
-    }
-    if ((threadIdx.x & 63) == 0) {
+    a = wave_sum_last(a);
+    b = wave_sum_last(b);
+    if ((threadIdx.x & 63) == 63) {
         sm2[threadIdx.x >> 6] = a;
         sm2[VEC_BLOCK / 64 + (threadIdx.x >> 6)] = b;
     }
@@ -108,6 +111,31 @@ __device__ __forceinline__ double chunk_sum(const T *part, int nchunks, int64_t 
     return s;
 }
 
+// The thread rows' shares of the block's EL sums (thread row cl = thread / EL holds element thread % EL), added up in a
+// fixed order for the threads of row 0.  With EL = 4 a thread row is a quarter of a DPP row: the four of a DPP row are
+// added on the vector units first, so that sixteen values per element are left to one thread instead of a chain of 64
+// LDS reads and dependent additions (and of 164 registers).  Every thread of the block calls it; `sm` (VEC_BLOCK
+// values) is free again after the caller's next barrier.
+template <int EL> __device__ __forceinline__ double fold_rows(double t, double *sm)
+{
+    constexpr int LEFT = EL == 4 ? VEC_BLOCK / 16 : VEC_BLOCK / EL;
+    const int tid = threadIdx.x;
+    if constexpr (EL == 4) {
+        t += dpp_or_zero<0x114, 0xf>(t);     // row_shr 4, 8: lanes 12..15 of the row have the sums of its four
+        t += dpp_or_zero<0x118, 0xf>(t);
+        if ((tid & 12) == 12) sm[(tid >> 4) * EL + (tid & 3)] = t;
+    } else {
+        sm[tid] = t;
+    }
+    __syncthreads();
+    double s = 0.0;
+    if (tid < EL) {
+#pragma unroll
+        for (int k = 0; k < LEFT; ++k) s += sm[k * EL + tid];
+    }
+    return s;
+}
+
 // ---- finalize: out = scale * sum_chunks part + lambda * M -----------------------------------
 // A block owns EL consecutive elements at a time; its 256/EL thread rows split the chunk sum and are
 // folded through LDS in a fixed order.
@@ -127,12 +155,8 @@ template <typename T, int EL> __global__ __launch_bounds__(VEC_BLOCK) void final
         const int64_t e = grp * EL + el;
         double s = 0.0;
         if (e < total) s = chunk_sum<T, CLN>(part, a.nchunks, total, e, cl);
-        sm[threadIdx.x] = s;
-        __syncthreads();
+        const double t = fold_rows<EL>(s, sm);
         if (cl == 0 && e < total) {
-            double t = 0.0;
-#pragma unroll
-            for (int k = 0; k < CLN; ++k) t += sm[k * EL + el];
             const double m = (double)M[off_of(e, a.K, a.ldm)];
             const T o = (T)(a.scale * t + a.lambda * m);
             out[off_of(e, a.K, a.ldo)] = o;
@@ -204,13 +228,11 @@ __device__ __forceinline__ CgSlot cg_advance(const CgSlot &prev, double rr_new, 
 __device__ __forceinline__ void block_sum3(double a, double b, double c, double &ra, double &rb, double &rc)
 {
     __shared__ double sm3[3 * (VEC_BLOCK / 64)];
-    for (int off = 32; off > 0; off >>= 1) {
-        a += __shfl_xor(a, off);
-        b += __shfl_xor(b, off);
-        c += __shfl_xor(c, off);
-    }
+    a = wave_sum_last(a);
+    b = wave_sum_last(b);
+    c = wave_sum_last(c);
     constexpr int NWV = VEC_BLOCK / 64;
-    if ((threadIdx.x & 63) == 0) {
+    if ((threadIdx.x & 63) == 63) {
         sm3[threadIdx.x >> 6] = a;
         sm3[NWV + (threadIdx.x >> 6)] = b;
         sm3[2 * NWV + (threadIdx.x >> 6)] = c;
@@ -246,6 +268,11 @@ __device__ __forceinline__ void block_sum3(double a, double b, double c, double 
 //
 // The theta test for r_k is only known here, after product k has been launched: when the loop stops, that
 // one product has run for nothing (the launches after it see the flag and return at once).
+//
+// What bounds it is its chain: partials and state in, three sums, the scalars, the elements, two sums, partials out.
+// Hence the sums on the vector units, sixteen instead of 64 values for the last thread to add at EL = 4, and the elements
+// of p, r, s, H s fetched with the partials instead of behind the sums (100 elements from 7 chunks: 5.8 -> 4.4 us;
+// 480 from the chunks of 50 000 rows: 7.5 -> 6.7 us, fp64; CG is ten of these launches).
 template <typename T, int EL> __global__ __launch_bounds__(VEC_BLOCK) void finalize_cg_kernel(FinArgs a, FinCgArgs g)
 {
     // Loads first: the state, this thread's share of the partial sums and the first batch of the block's chunk
@@ -255,6 +282,18 @@ template <typename T, int EL> __global__ __launch_bounds__(VEC_BLOCK) void final
     const int64_t total = a.p * a.K;
     const T *part = (const T *)a.part;
     const CgSlot prev = g.first ? *g.cur : *g.prev;    // k == 0 with n_gg > 0: not the state yet, every use is overridden
+    // the vectors' elements of the block's first group (all it has unless the problem is very wide) go out with them
+    T *pv = (T *)g.pv, *r = (T *)g.r, *sv = (T *)g.s, *hsv = (T *)g.hs, *pb = (T *)g.pbest;
+    T pe0 = 0, re0 = 0, hs0 = 0, sv0 = 0;
+    if (cl == 0 && (int64_t)blockIdx.x * EL + el < total) {
+        const int64_t o = off_of((int64_t)blockIdx.x * EL + el, a.K, a.ldm);
+        pe0 = pv[o];
+        re0 = r[o];
+        if (!g.first) {
+            hs0 = hsv[o];
+            sv0 = sv[o];
+        }
+    }
     const double *rin = g.first ? g.gg_part : g.rr_in;
     const int nin = g.first ? g.n_gg : g.n_in;
     double vz = 0.0, vr = 0.0, vh = 0.0, tfirst = 0.0;   // tfirst: chunks cl, cl + CLN, .. (first eight) of the first group
@@ -337,7 +376,6 @@ template <typename T, int EL> __global__ __launch_bounds__(VEC_BLOCK) void final
     if (!c.best_pending && (c.done || brk)) return;
     __shared__ double sm[VEC_BLOCK];
     const int64_t ngroups = (total + EL - 1) / EL;
-    T *pv = (T *)g.pv, *r = (T *)g.r, *sv = (T *)g.s, *hsv = (T *)g.hs, *pb = (T *)g.pbest;
     const bool update = !c.done && !brk;
     double lrr = 0.0, lrh = 0.0;
     for (int64_t grp = blockIdx.x; grp < ngroups; grp += gridDim.x) {
@@ -347,20 +385,17 @@ template <typename T, int EL> __global__ __launch_bounds__(VEC_BLOCK) void final
             if (grp == blockIdx.x) t = chunk_sum<T, CLN>(part, a.nchunks, total, e, cl, 8, tfirst);
             else t = chunk_sum<T, CLN>(part, a.nchunks, total, e, cl);
         }
-        sm[threadIdx.x] = t;
-        __syncthreads();
+        const double tt = fold_rows<EL>(t, sm);
         if (cl == 0 && e < total) {
             const int64_t o = off_of(e, a.K, a.ldm);
-            const T pe = pv[o];
+            const bool head = grp == blockIdx.x;                      // already in registers
+            const T pe = head ? pe0 : pv[o];
             if (c.best_pending) pb[o] = pe;                           // line 10 for the iterate the last product left
             if (update) {
-                double tt = 0.0;
-#pragma unroll
-                for (int k = 0; k < CLN; ++k) tt += sm[k * EL + el];
-                const double re = (double)r[o];
+                const double re = (double)(head ? re0 : r[o]);
                 const T hr = (T)(a.scale * tt + a.lambda * re);       // the element of H r, rounded as if stored
-                const T hs = g.first ? hr : (T)((double)hr + beta * (double)hsv[o]);
-                const T sn = g.first ? (T)re : (T)(re + beta * (double)sv[o]);      // line 12
+                const T hs = g.first ? hr : (T)((double)hr + beta * (double)(head ? hs0 : hsv[o]));
+                const T sn = g.first ? (T)re : (T)(re + beta * (double)(head ? sv0 : sv[o]));      // line 12
                 hsv[o] = hs;
                 sv[o] = sn;
                 pv[o] = (T)((double)pe + alpha * (double)sn);         // line 8
@@ -731,11 +766,9 @@ __global__ __launch_bounds__(OBJ_BLOCK) void objective_value_kernel(const double
     }
     // the block's two sums: over the lanes of a wave, then over the waves in wave order
     __shared__ double sm[2 * (OBJ_BLOCK / 64)];
-    for (int off = 32; off > 0; off >>= 1) {
-        loss += __shfl_xor(loss, off);
-        sq += __shfl_xor(sq, off);
-    }
-    if ((threadIdx.x & 63) == 0) {
+    loss = wave_sum_last(loss);
+    sq = wave_sum_last(sq);
+    if ((threadIdx.x & 63) == 63) {
         sm[threadIdx.x >> 6] = loss;
         sm[OBJ_BLOCK / 64 + (threadIdx.x >> 6)] = sq;
     }
@@ -1332,10 +1365,13 @@ __global__ __launch_bounds__(VEC_BLOCK) void cg_alpha_kernel(CgSlot *cur, const 
                                                               const double *ss_part, int n_ss, double scale, double lambda,
                                                               double *trace_k)
 {
+    // both reductions at once, and before the state is looked at: one trip's wait instead of three
+    const double tz = thread_parts(zu_part, n_zu), ts = thread_parts(ss_part, n_ss);
     const CgSlot c = *cur;
     if (c.done) return;
-    const double zu = sum_parts(zu_part, n_zu);
-    const double ss = sum_parts(ss_part, n_ss) + c.sigma * c.sigma * c.goff;
+    double zu, ss;
+    block_sum2(tz, ts, zu, ss);
+    ss += c.sigma * c.sigma * c.goff;
     const double sHs = scale * zu + lambda * ss;
     if (threadIdx.x != 0) return;
     if (!(sHs > 0.0)) {                      // not positive definite in floating point: stop, keep p_best
