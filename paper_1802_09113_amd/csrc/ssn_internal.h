@@ -144,9 +144,11 @@ hipError_t launch_binary_rows(int dtype, const RowsArgs &a, int blocks, int spli
 hipError_t launch_binary_xtu(int dtype, const XtuArgs &a, hipStream_t st);
 hipError_t launch_finalize(int dtype, const FinArgs &a, int blocks, hipStream_t st);
 
-// out = lambda * M (p x K), with optional <.,.> partials disabled; used by the CSR path before scattering
+// out = lambda * M (p x K); used by the CSR path before the gather adds to it.  sq_part (nullable, RED_MAX_PARTS
+// entries): partials of ||M||^2, *n_sq of them
 hipError_t launch_scale_copy(int dtype, int64_t p, int K, double lambda, const void *M, int64_t ldm,
-                             void *out, int64_t ldo, const int32_t *skip, hipStream_t st);
+                             void *out, int64_t ldo, const int32_t *skip, hipStream_t st, double *sq_part = nullptr,
+                             int *n_sq = nullptr);
 
 // partials of <A, B> over the p x K block: part[b] for b < blocks
 hipError_t launch_dot_part(int dtype, int64_t p, int K, const void *A, int64_t lda, const void *B, int64_t ldb,

@@ -79,6 +79,59 @@ __device__ __forceinline__ int64_t off_of(int64_t e, int K, int64_t ld)
     return j * ld + (e - j * K);
 }
 
+// Passes that read a large contiguous block, as 16-byte vectors: a workgroup takes one contiguous share of `per` vectors
+// (a multiple of VEC_BLOCK), every thread four of them in flight.  Element by element, with strides of 2 MB between a
+// thread's 8-byte loads, <A, A> of 206 MB (1.36 million x 19, fp64) took 58 us (3.6 TB/s); this way 36 us (5.8 TB/s).
+// Passes with two operands and a result do not take this form: Y = alpha X + Z of the same size became slower (115 ->
+// 133 us, the shares of three streams), and updates of a 9 MB block stayed where they were (10 us).  `per` == 0
+// (flat_share): the block is too small to give every workgroup a vector per thread, not contiguous, or not 16-byte
+// aligned, and the element loop stays.
+template <typename T> struct alignas(16) Pack16 {
+    static constexpr int N = 16 / sizeof(T);
+    T v[N];
+};
+constexpr int FLAT_U = 4;
+
+static int64_t flat_share(int64_t total, int es, int blocks, bool contiguous, const void *A, const void *B)
+{
+    const int64_t nv = total / (16 / es);
+    if (!contiguous || (((uintptr_t)A | (uintptr_t)B) & 15) != 0 || nv < (int64_t)blocks * VEC_BLOCK) return 0;
+    return ((nv + blocks - 1) / blocks + VEC_BLOCK - 1) / VEC_BLOCK * VEC_BLOCK;
+}
+
+// f(a, b) of every element of the workgroup's share (B == nullptr: f(a, a)); its results go to `out` (nullable, may be
+// A or B).  The elements behind the last whole vector are the first workgroup's.
+template <typename T, typename F>
+__device__ __forceinline__ void flat_pass(int64_t total, int64_t per, const T *A, const T *B, T *out, F f)
+{
+    typedef Pack16<T> pack;
+    constexpr int N = pack::N;
+    const int64_t nv = total / N, lo = (int64_t)blockIdx.x * per, hi = lo + per < nv ? lo + per : nv;
+    const pack *Av = (const pack *)A, *Bv = (const pack *)B;
+    for (int64_t i0 = lo + threadIdx.x; i0 < hi; i0 += FLAT_U * VEC_BLOCK) {
+        pack x[FLAT_U], y[FLAT_U];
+#pragma unroll
+        for (int u = 0; u < FLAT_U; ++u) x[u] = Av[i0 + u * VEC_BLOCK < hi ? i0 + u * VEC_BLOCK : i0];
+        if (B) {
+#pragma unroll
+            for (int u = 0; u < FLAT_U; ++u) y[u] = Bv[i0 + u * VEC_BLOCK < hi ? i0 + u * VEC_BLOCK : i0];
+        }
+#pragma unroll
+        for (int u = 0; u < FLAT_U; ++u) {
+            if (i0 + u * VEC_BLOCK >= hi) continue;
+            pack o;
+#pragma unroll
+            for (int j = 0; j < N; ++j) o.v[j] = f(x[u].v[j], B ? y[u].v[j] : x[u].v[j]);
+            if (out) ((pack *)out)[i0 + u * VEC_BLOCK] = o;
+        }
+    }
+    const int64_t e = nv * N + threadIdx.x;
+    if (blockIdx.x == 0 && e < total) {
+        const T o = f(A[e], B ? B[e] : A[e]);
+        if (out) out[e] = o;
+    }
+}
+
 int vec_blocks(int64_t total)
 {
     // small blocks: one element per thread (the kernels on them are chains of a few dependent round trips,
@@ -558,38 +611,68 @@ hipError_t launch_cg_tail(int dtype, const CgVecs &v, const CgSlot *prev, CgSlot
     return hipGetLastError();
 }
 
+// out = lambda * M; sq_part (nullable): one partial of ||M||^2 per block
 template <typename T>
 __global__ __launch_bounds__(VEC_BLOCK) void scale_copy_kernel(int64_t p, int K, double lambda, const T *M, int64_t ldm,
-                                                                T *out, int64_t ldo, const int32_t *skip)
+                                                                T *out, int64_t ldo, double *sq_part, int64_t per,
+                                                                const int32_t *skip)
 {
     if (skip && *skip) return;
     const int64_t total = p * K;
-    for (int64_t e = (int64_t)blockIdx.x * VEC_BLOCK + threadIdx.x; e < total; e += (int64_t)gridDim.x * VEC_BLOCK)
-        out[off_of(e, K, ldo)] = (T)(lambda * (double)M[off_of(e, K, ldm)]);
+    double sq = 0.0;
+    if (per > 0) {
+        flat_pass<T>(total, per, M, nullptr, out, [&](T m, T) {
+            sq += (double)m * (double)m;
+            return (T)(lambda * (double)m);
+        });
+    } else {
+        for (int64_t e = (int64_t)blockIdx.x * VEC_BLOCK + threadIdx.x; e < total; e += (int64_t)gridDim.x * VEC_BLOCK) {
+            const double m = (double)M[off_of(e, K, ldm)];
+            out[off_of(e, K, ldo)] = (T)(lambda * m);
+            sq += m * m;
+        }
+    }
+    if (sq_part) {
+        const double r = block_sum(sq);
+        if (threadIdx.x == 0) sq_part[blockIdx.x] = r;
+    }
 }
 
 hipError_t launch_scale_copy(int dtype, int64_t p, int K, double lambda, const void *M, int64_t ldm, void *out,
-                             int64_t ldo, const int32_t *skip, hipStream_t st)
+                             int64_t ldo, const int32_t *skip, hipStream_t st, double *sq_part, int *n_sq)
 {
-    const int blocks = vec_blocks(p * K) * 4 > 4096 ? 4096 : vec_blocks(p * K) * 4;
+    const int64_t total = p * K;
+    const int es = dtype == SSN_F32 ? 4 : 8;
+    int blocks = vec_blocks(total);
+    const int64_t per = flat_share(total, es, blocks, ldm == K && ldo == K, M, out);
+    // element by element without partials to leave: more workgroups make up for the loads a thread keeps in flight
+    if (per == 0 && !sq_part) blocks = blocks * 4 > 4096 ? 4096 : blocks * 4;
+    if (n_sq) *n_sq = blocks;
     if (dtype == SSN_F32)
         hipLaunchKernelGGL(scale_copy_kernel<float>, dim3(blocks), dim3(VEC_BLOCK), 0, st, p, K, lambda, (const float *)M,
-                           ldm, (float *)out, ldo, skip);
+                           ldm, (float *)out, ldo, sq_part, per, skip);
     else
         hipLaunchKernelGGL(scale_copy_kernel<double>, dim3(blocks), dim3(VEC_BLOCK), 0, st, p, K, lambda,
-                           (const double *)M, ldm, (double *)out, ldo, skip);
+                           (const double *)M, ldm, (double *)out, ldo, sq_part, per, skip);
     return hipGetLastError();
 }
 
 template <typename T>
 __global__ __launch_bounds__(VEC_BLOCK) void dot_part_kernel(int64_t p, int K, const T *A, int64_t lda, const T *B,
-                                                              int64_t ldb, double *part, const int32_t *skip)
+                                                              int64_t ldb, double *part, int64_t per, const int32_t *skip)
 {
     if (skip && *skip) return;
     const int64_t total = p * K;
     double local = 0.0;
-    for (int64_t e = (int64_t)blockIdx.x * VEC_BLOCK + threadIdx.x; e < total; e += (int64_t)gridDim.x * VEC_BLOCK)
-        local += (double)A[off_of(e, K, lda)] * (double)B[off_of(e, K, ldb)];
+    if (per > 0) {
+        flat_pass<T>(total, per, A, A == B ? nullptr : B, (T *)nullptr, [&](T x, T y) {
+            local += (double)x * (double)y;
+            return x;
+        });
+    } else {
+        for (int64_t e = (int64_t)blockIdx.x * VEC_BLOCK + threadIdx.x; e < total; e += (int64_t)gridDim.x * VEC_BLOCK)
+            local += (double)A[off_of(e, K, lda)] * (double)B[off_of(e, K, ldb)];
+    }
     const double r = block_sum(local);
     if (threadIdx.x == 0) part[blockIdx.x] = r;
 }
@@ -597,12 +680,13 @@ __global__ __launch_bounds__(VEC_BLOCK) void dot_part_kernel(int64_t p, int K, c
 hipError_t launch_dot_part(int dtype, int64_t p, int K, const void *A, int64_t lda, const void *B, int64_t ldb,
                            double *part, int blocks, const int32_t *skip, hipStream_t st)
 {
+    const int64_t per = flat_share(p * K, dtype == SSN_F32 ? 4 : 8, blocks, lda == K && ldb == K, A, B);
     if (dtype == SSN_F32)
         hipLaunchKernelGGL(dot_part_kernel<float>, dim3(blocks), dim3(VEC_BLOCK), 0, st, p, K, (const float *)A, lda,
-                           (const float *)B, ldb, part, skip);
+                           (const float *)B, ldb, part, per, skip);
     else
         hipLaunchKernelGGL(dot_part_kernel<double>, dim3(blocks), dim3(VEC_BLOCK), 0, st, p, K, (const double *)A, lda,
-                           (const double *)B, ldb, part, skip);
+                           (const double *)B, ldb, part, per, skip);
     return hipGetLastError();
 }
 
