@@ -16,6 +16,9 @@
 
 using namespace ssn;
 
+// where in the pinned page (512 doubles) ssn_cg's results land, and how many doubles fit
+constexpr int CG_POST_AT = 264, CG_POST_MAX = 512 - CG_POST_AT;
+
 struct ssn_ctx {
     ssn_desc d{};
     int K = 0, KP = 0;
@@ -74,6 +77,7 @@ struct ssn_ctx {
     unsigned long long f_seq = 0; // ticket of the last enqueue
     double *pub_host = nullptr;   // host-visible block ssn_solve's per-iteration scalars and CG state are written to
     double *pub_dev = nullptr;    // its device address
+    double *cg_post_host = nullptr, *cg_post_dev = nullptr;   // ssn_cg's final state and trace, CG_POST_MAX doubles
     // prepared Hessian sample
     const int32_t *S = nullptr;
     int64_t nS = 0;
@@ -521,22 +525,40 @@ int enqueue_objective_value(ssn_ctx *c, const void *W, int nparts, int slot, dou
 
 double now_ms();
 
+// Spin on the ticket a kernel posts behind its value (c->f_seq: the last one given out).  Everything enqueued before
+// that kernel has completed by then (one stream), and the host is back a microsecond or two after the store instead
+// of a stream synchronisation's wake-up later.  A ticket that does not come (a failed launch, a fault)
+// ends in the synchronisation, which reports it.
+int await_ticket(ssn_ctx *c)
+{
+    const unsigned long long want = c->f_seq;
+    const double t_give_up = now_ms() + 2000.0;
+    for (unsigned spin = 0;; ++spin) {
+        if (__atomic_load_n(c->f_ticket, __ATOMIC_ACQUIRE) == want) return SSN_OK;
+        if ((spin & 0x3ff) == 0x3ff && now_ms() > t_give_up) break;
+    }
+    SSN_HIP(c, hipStreamSynchronize(c->st));
+    return SSN_OK;
+}
+
+// *bad = how many of v[0..count) lie outside [0, hi)
+int count_outside(ssn_ctx *c, const int32_t *v, int64_t count, int64_t hi, int32_t *bad)
+{
+    if (count <= CHECK_POST_MAX) {
+        SSN_HIP(c, launch_check_range_post(v, (int)count, 0, hi, c->f_host_dev, c->f_ticket_dev, ++c->f_seq, c->st));
+        SSN_TRY(await_ticket(c));
+        *bad = (int32_t)*(volatile double *)c->f_host;
+        return SSN_OK;
+    }
+    SSN_HIP(c, launch_check_range(v, count, 0, hi, c->int_dev, c->st));
+    return read_int(c, c->int_dev, bad);
+}
+
 // wait for f(W) enqueued by enqueue_objective_value into scal_dev[0]
 int read_objective(ssn_ctx *c, bool mirrored, double *f)
 {
     if (mirrored) {
-        // Spin on the ticket the value kernel posts behind the value.  Everything enqueued before that kernel
-        // has completed by then (one stream), and the host is back a microsecond or two after the store instead
-        // of a stream synchronisation's wake-up later.  A ticket that does not come (a failed launch, a fault)
-        // ends in the synchronisation, which reports it.
-        const unsigned long long want = c->f_seq;
-        const double t_give_up = now_ms() + 2000.0;
-        bool seen = false;
-        for (unsigned spin = 0;; ++spin) {
-            if (__atomic_load_n(c->f_ticket, __ATOMIC_ACQUIRE) == want) { seen = true; break; }
-            if ((spin & 0x3ff) == 0x3ff && now_ms() > t_give_up) break;
-        }
-        if (!seen) SSN_HIP(c, hipStreamSynchronize(c->st));
+        SSN_TRY(await_ticket(c));
         *f = *(volatile double *)c->f_host;
     } else {
         SSN_TRY(read_scalar(c, c->scal_dev, f));
@@ -862,6 +884,8 @@ int ssn_create(ssn_ctx **out, const ssn_desc *d)
         c->f_ticket_dev = (unsigned long long *)(c->f_host_dev + 1);
         c->pub_host = c->host_pin + 128;                             // bytes 1024..2047
         c->pub_dev = pin_dev + 128;
+        c->cg_post_host = c->host_pin + CG_POST_AT;                  // bytes 2112..4095
+        c->cg_post_dev = pin_dev + CG_POST_AT;
     }
     if (d->layout == SSN_DENSE_ROWMAJOR) {
         const int64_t nft = (d->p + 63) / 64;
@@ -1008,8 +1032,7 @@ static int hess_prepare_impl(ssn_ctx *c, const void *W, const int32_t *S, int64_
     c->prepared = false;
     if (validate) {
         int32_t bad = 0;
-        SSN_HIP(c, launch_check_range(S, nS, 0, c->d.n, c->int_dev, c->st));
-        SSN_TRY(read_int(c, c->int_dev, &bad));
+        SSN_TRY(count_outside(c, S, nS, c->d.n, &bad));
         if (bad) return fail(c, SSN_E_BAD_INDEX, "ssn_hess_prepare: sample index outside [0,n)");
     }
     const int64_t rows = round_up(nS, 16);
@@ -1042,8 +1065,7 @@ int ssn_gradient_sampled(ssn_ctx *c, const void *W, const int32_t *S, int64_t nS
     if (!c || !W || !G || !S || nS < 1 || W == G)
         return fail(c, SSN_E_INVALID_ARG, "ssn_gradient_sampled: null or aliased argument, or nS < 1");
     int32_t bad = 0;
-    SSN_HIP(c, launch_check_range(S, nS, 0, c->d.n, c->int_dev, c->st));
-    SSN_TRY(read_int(c, c->int_dev, &bad));
+    SSN_TRY(count_outside(c, S, nS, c->d.n, &bad));
     if (bad) return fail(c, SSN_E_BAD_INDEX, "ssn_gradient_sampled: sample index outside [0,n)");
     return gradient_impl(c, W, G, f_S, false, S, nS);
 }
@@ -1190,10 +1212,18 @@ int ssn_cg(ssn_ctx *c, const void *G, double theta, int32_t T, void *P_out, ssn_
     SSN_TRY(cg_enqueue(c, G, theta, T, P_out));
     CgSlot fin;
     std::vector<double> tr((size_t)3 * (T > 0 ? T : 1));
-    SSN_HIP(c, hipMemcpyAsync(&fin, c->slots + T, sizeof(CgSlot), hipMemcpyDeviceToHost, c->st));
-    if (trace && T > 0)
-        SSN_HIP(c, hipMemcpyAsync(tr.data(), c->trace_dev, sizeof(double) * 3 * (size_t)T, hipMemcpyDeviceToHost, c->st));
-    SSN_HIP(c, hipStreamSynchronize(c->st));
+    const int ntrace = trace ? 3 * T : 0;
+    if (CG_POST_STATE + ntrace <= CG_POST_MAX) {
+        SSN_HIP(c, launch_cg_post(c->slots + T, c->trace_dev, ntrace, c->cg_post_dev, c->f_ticket_dev, ++c->f_seq, c->st));
+        SSN_TRY(await_ticket(c));
+        memcpy(&fin, c->cg_post_host, sizeof(CgSlot));
+        if (ntrace > 0) memcpy(tr.data(), c->cg_post_host + CG_POST_STATE, sizeof(double) * (size_t)ntrace);
+    } else {
+        SSN_HIP(c, hipMemcpyAsync(&fin, c->slots + T, sizeof(CgSlot), hipMemcpyDeviceToHost, c->st));
+        if (trace && T > 0)
+            SSN_HIP(c, hipMemcpyAsync(tr.data(), c->trace_dev, sizeof(double) * 3 * (size_t)T, hipMemcpyDeviceToHost, c->st));
+        SSN_HIP(c, hipStreamSynchronize(c->st));
+    }
     if (trace)
         for (int k = 0; k < 3 * fin.iters && k < 3 * T; ++k) trace[k] = tr[k];
     if (info) cg_fill_info(fin, info);
@@ -1361,10 +1391,9 @@ int ssn_predict(ssn_ctx *c, const void *W, int32_t *pred, double *acc)
     int nparts = 0;
     SSN_TRY(launch_rows(c, a, &nparts));
     if (acc) {
-        int32_t hits = 0;
-        SSN_HIP(c, launch_sum_int(c->hit_part, nparts, c->int_dev + 1, c->st));
-        SSN_TRY(read_int(c, c->int_dev + 1, &hits));
-        *acc = (double)hits / (double)c->d.n;
+        SSN_HIP(c, launch_sum_int(c->hit_part, nparts, c->int_dev + 1, c->f_host_dev, c->f_ticket_dev, ++c->f_seq, c->st));
+        SSN_TRY(await_ticket(c));
+        *acc = *(volatile double *)c->f_host / (double)c->d.n;
     }
     return SSN_OK;
 }
@@ -1398,12 +1427,10 @@ int ssn_solve(ssn_ctx *c, void *W, const ssn_params *pr, ssn_iter_record *log, i
     // the whole sample schedule is checked once, not sample by sample
     if (pr->iters > 0) {
         int32_t bad = 0;
-        SSN_HIP(c, launch_check_range(pr->S_all, (int64_t)pr->iters * pr->nS, 0, c->d.n, c->int_dev, c->st));
-        SSN_TRY(read_int(c, c->int_dev, &bad));
+        SSN_TRY(count_outside(c, pr->S_all, (int64_t)pr->iters * pr->nS, c->d.n, &bad));
         if (bad) return fail(c, SSN_E_BAD_INDEX, "ssn_solve: sample index outside [0,n)");
         if (pr->Sg_all) {
-            SSN_HIP(c, launch_check_range(pr->Sg_all, (int64_t)pr->iters * pr->nSg, 0, c->d.n, c->int_dev, c->st));
-            SSN_TRY(read_int(c, c->int_dev, &bad));
+            SSN_TRY(count_outside(c, pr->Sg_all, (int64_t)pr->iters * pr->nSg, c->d.n, &bad));
             if (bad) return fail(c, SSN_E_BAD_INDEX, "ssn_solve: gradient sample index outside [0,n)");
         }
     }

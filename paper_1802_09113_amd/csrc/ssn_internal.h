@@ -192,10 +192,17 @@ hipError_t launch_solve_publish(const double *slope_part, int n, const double *f
                                 double *host_out, bool support_only, hipStream_t st);
 // streaming read of `bytes` (multiple of 16, 16-byte aligned); one checksum partial per block
 hipError_t launch_stream_read(const void *src, int64_t bytes, double *part, int blocks, hipStream_t st);
-hipError_t launch_sum_int(const int32_t *a, int na, int32_t *out, hipStream_t st);
+// *out = sum of a[0..na); also posted to the host (see post_to_host)
+hipError_t launch_sum_int(const int32_t *a, int na, int32_t *out, double *out_host, unsigned long long *ticket_host,
+                          unsigned long long ticket, hipStream_t st);
 
 // validation passes: *bad receives the number of offending entries
 hipError_t launch_check_range(const int32_t *v, int64_t count, int64_t lo, int64_t hi, int32_t *bad, hipStream_t st);
+// the count posted to the host by one launch of one workgroup (count <= CHECK_POST_MAX: beyond, one workgroup's chain of
+// trips takes longer than what it saves)
+constexpr int CHECK_POST_MAX = 65536;
+hipError_t launch_check_range_post(const int32_t *v, int count, int64_t lo, int64_t hi, double *out_host,
+                                   unsigned long long *ticket_host, unsigned long long ticket, hipStream_t st);
 hipError_t launch_check_rowptr(const int32_t *rowptr, int64_t n, int64_t nnz, int32_t *bad, hipStream_t st);
 
 // ---- column-sorted view of a set of CSR rows (csc.hip) --------------------------------------------
@@ -284,6 +291,11 @@ struct CgSlot {          // state before product k
     double goff;
     double rho, sigma, pi, pibest;   // r_j = rho g_j, s_j = sigma g_j, p_j = pi g_j, p_best_j = pibest g_j
 };
+
+// *fin (CG_POST_STATE doubles) and trace[0..ntrace) into host-visible memory, then the ticket
+constexpr int CG_POST_STATE = (int)(sizeof(CgSlot) / sizeof(double));
+hipError_t launch_cg_post(const CgSlot *fin, const double *trace, int ntrace, double *out_host, unsigned long long *ticket_host,
+                          unsigned long long ticket, hipStream_t st);
 
 struct CgVecs {
     int64_t p;

@@ -1015,7 +1015,8 @@ hipError_t launch_combine(const double *a, int na, double scale, const double *b
     return hipGetLastError();
 }
 
-__global__ __launch_bounds__(VEC_BLOCK) void sum_int_kernel(const int32_t *a, int na, int32_t *out)
+__global__ __launch_bounds__(VEC_BLOCK) void sum_int_kernel(const int32_t *a, int na, int32_t *out, double *out_host,
+                                                             unsigned long long *ticket_host, unsigned long long ticket)
 {
     __shared__ long long sm[VEC_BLOCK];
     long long v = 0;
@@ -1026,12 +1027,37 @@ __global__ __launch_bounds__(VEC_BLOCK) void sum_int_kernel(const int32_t *a, in
         if ((int)threadIdx.x < s) sm[threadIdx.x] += sm[threadIdx.x + s];
         __syncthreads();
     }
-    if (threadIdx.x == 0) *out = (int32_t)sm[0];
+    if (threadIdx.x == 0) {
+        *out = (int32_t)sm[0];
+        post_to_host((double)(int32_t)sm[0], out_host, ticket_host, ticket);
+    }
 }
 
-hipError_t launch_sum_int(const int32_t *a, int na, int32_t *out, hipStream_t st)
+hipError_t launch_sum_int(const int32_t *a, int na, int32_t *out, double *out_host, unsigned long long *ticket_host,
+                          unsigned long long ticket, hipStream_t st)
 {
-    hipLaunchKernelGGL(sum_int_kernel, dim3(1), dim3(VEC_BLOCK), 0, st, a, na, out);
+    hipLaunchKernelGGL(sum_int_kernel, dim3(1), dim3(VEC_BLOCK), 0, st, a, na, out, out_host, ticket_host, ticket);
+    return hipGetLastError();
+}
+
+// The final CG state and the trace of its products (3 doubles each) for a host that is waiting for them: a copy engine's
+// two transfers and the wake-up of a stream synchronisation cost more than this launch.
+__global__ __launch_bounds__(VEC_BLOCK) void cg_post_kernel(const CgSlot *fin, const double *trace, int ntrace, double *out_host,
+                                                             unsigned long long *ticket_host, unsigned long long ticket)
+{
+    constexpr int NW = (int)(sizeof(CgSlot) / sizeof(double));
+    static_assert(sizeof(CgSlot) % sizeof(double) == 0 && NW == CG_POST_STATE, "the state is posted in whole doubles");
+    for (int i = threadIdx.x; i < NW + ntrace; i += VEC_BLOCK)
+        ((volatile double *)out_host)[i] = i < NW ? ((const double *)fin)[i] : trace[i - NW];
+    __threadfence_system();
+    __syncthreads();
+    if (threadIdx.x == 0) __hip_atomic_store(ticket_host, ticket, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+hipError_t launch_cg_post(const CgSlot *fin, const double *trace, int ntrace, double *out_host, unsigned long long *ticket_host,
+                          unsigned long long ticket, hipStream_t st)
+{
+    hipLaunchKernelGGL(cg_post_kernel, dim3(1), dim3(VEC_BLOCK), 0, st, fin, trace, ntrace, out_host, ticket_host, ticket);
     return hipGetLastError();
 }
 
@@ -1085,6 +1111,40 @@ hipError_t launch_check_range(const int32_t *v, int64_t count, int64_t lo, int64
 {
     hipLaunchKernelGGL(zero_int_kernel, dim3(1), dim3(1), 0, st, bad);
     hipLaunchKernelGGL(check_range_kernel, dim3(vec_blocks(count)), dim3(VEC_BLOCK), 0, st, v, count, lo, hi, bad);
+    return hipGetLastError();
+}
+
+// The same check of up to CHECK_POST_MAX values by one workgroup, which posts the count to the host: one launch in place
+// of clearing, counting, copying and synchronising (sample indices are checked on every call that takes a sample).
+__global__ __launch_bounds__(OBJ_BLOCK) void check_range_post_kernel(const int32_t *v, int count, int64_t lo, int64_t hi,
+                                                                      double *out_host, unsigned long long *ticket_host,
+                                                                      unsigned long long ticket)
+{
+    constexpr int U = 8;
+    int local = 0;
+    for (int i0 = threadIdx.x; i0 < count; i0 += U * OBJ_BLOCK) {
+        int32_t x[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) x[u] = v[i0 + u * OBJ_BLOCK < count ? i0 + u * OBJ_BLOCK : i0];
+#pragma unroll
+        for (int u = 0; u < U; ++u) local += i0 + u * OBJ_BLOCK < count && (x[u] < lo || x[u] >= hi);
+    }
+    __shared__ double sm[OBJ_BLOCK / 64];
+    const double w = wave_sum_last((double)local);           // whole numbers: exact
+    if ((threadIdx.x & 63) == 63) sm[threadIdx.x >> 6] = w;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double bad = 0.0;
+#pragma unroll
+        for (int k = 0; k < OBJ_BLOCK / 64; ++k) bad += sm[k];
+        post_to_host(bad, out_host, ticket_host, ticket);
+    }
+}
+
+hipError_t launch_check_range_post(const int32_t *v, int count, int64_t lo, int64_t hi, double *out_host,
+                                   unsigned long long *ticket_host, unsigned long long ticket, hipStream_t st)
+{
+    hipLaunchKernelGGL(check_range_post_kernel, dim3(1), dim3(OBJ_BLOCK), 0, st, v, count, lo, hi, out_host, ticket_host, ticket);
     return hipGetLastError();
 }
 
