@@ -146,7 +146,14 @@ __global__ __launch_bounds__(64 * ROWS_WAVES_PER_BLOCK) void csr_rows_kernel(Row
         } else {
             z = csr_row_margin<T>(a, b, e, lane, K, NS);
         }
+        if constexpr (MODE == ROW_GRAD) {
+            if (a.Zkeep && cv) ((T *)a.Zkeep)[sv * (2 * K) + lane] = z;
+        }
         if constexpr (MODE == ROW_MARGIN) {              // margins of both operands, [X M | X M2], 2K values per row
+            if (!a.M2) {                                 // the first half is there: M is the second operand
+                if (cv) ((T *)a.UP)[sv * a.KP + K + lane] = z;
+                continue;
+            }
             RowsArgs b2 = a;
             b2.M = a.M2;
             const T z2 = csr_row_margin<T>(b2, b, e, lane, K, NS);

@@ -78,6 +78,12 @@ struct ssn_ctx {
     double *pub_host = nullptr;   // host-visible block ssn_solve's per-iteration scalars and CG state are written to
     double *pub_dev = nullptr;    // its device address
     double *cg_post_host = nullptr, *cg_post_dev = nullptr;   // ssn_cg's final state and trace, CG_POST_MAX doubles
+    // Inside ssn_solve on CSR data with more than one weight column (z_keep): gradient passes leave the margins X W in
+    // the first halves of Zbuf, and z_for is the block they belong to (nullptr: none).  A line search that backs off
+    // then needs X P only -- one pass over the data with one operand instead of two (20000 rows x 450 entries,
+    // 1.36 million x 19 weights, fp64: 535 us).  The n x K values cost the gradient pass nothing that shows.
+    bool z_keep = false;
+    const void *z_for = nullptr;
     // prepared Hessian sample
     const int32_t *S = nullptr;
     int64_t nS = 0;
@@ -603,7 +609,13 @@ int gradient_impl(ssn_ctx *c, const void *W, void *G, double *f, bool defer_f = 
     a.UP = c->Ubuf;
     int nparts = 0;
     a.part = c->part;
+    const bool keep = c->z_keep && !S;
+    if (keep) {
+        a.Zkeep = c->Zbuf;
+        c->z_for = nullptr;
+    }
     SSN_TRY(launch_rows(c, a, &nparts));
+    if (keep) c->z_for = W;
     if (c->fused) {
         SSN_TRY(finalize_dense(c, nparts / 4, scale, W, G, false, nullptr, nullptr));
     } else {
@@ -1272,6 +1284,7 @@ int trial_enqueue(ssn_ctx *c, const void *W, const void *P, double alpha, void *
         dst = c->trial;
     }
     c->sq_for = nullptr;
+    if (c->z_for == dst) c->z_for = nullptr;
     if (formed) {
     } else if (c->d.p * (int64_t)c->K > OBJ_VALUE_ELEMS) {
         // a large block: ||trial||^2 for the regulariser comes out of the pass that writes the trial point
@@ -1294,16 +1307,22 @@ int trial_enqueue(ssn_ctx *c, const void *W, const void *P, double alpha, void *
 // tiles per operand) keep the plain trials.
 bool margin_cache_ok(const ssn_ctx *c) { return !is_dense(c) || c->binary || 2 * c->K <= 32; }
 
+int margins_alloc(ssn_ctx *c)
+{
+    if (!c->Zbuf) SSN_HIP(c, hipMalloc(&c->Zbuf, (size_t)c->d.n * (size_t)(2 * c->K) * c->es));
+    if (!c->ls_dots) SSN_HIP(c, hipMalloc((void **)&c->ls_dots, sizeof(double) * 3 * RED_MAX_PARTS));
+    return SSN_OK;
+}
+
 int margins_enqueue(ssn_ctx *c, const void *W, const void *P)
 {
-    if (!c->Zbuf) {
-        SSN_HIP(c, hipMalloc(&c->Zbuf, (size_t)c->d.n * (size_t)(2 * c->K) * c->es));
-        SSN_HIP(c, hipMalloc((void **)&c->ls_dots, sizeof(double) * 3 * RED_MAX_PARTS));
-    }
+    SSN_TRY(margins_alloc(c));
     RowsArgs a = rows_base(c);
     a.nrows = c->d.n;
-    a.M = W;
-    a.M2 = P;
+    // the gradient pass at W left X W: only X P is missing (the same values, so the trials are the same to the last bit)
+    const bool have = c->z_for == W && c->z_for != nullptr;
+    a.M = have ? P : W;
+    a.M2 = have ? nullptr : P;
     a.mode = ROW_MARGIN;
     a.UP = c->Zbuf;
     a.KP = 2 * c->K;
@@ -1371,6 +1390,7 @@ int linesearch_impl(ssn_ctx *c, const void *W, const void *P, double fW, double 
             dst = c->trial;
         }
         c->sq_for = nullptr;
+        if (c->z_for == dst) c->z_for = nullptr;
         SSN_HIP(c, launch_axpy(c->d.dtype, c->d.p, c->K, alpha, P, c->d.ldw, W, c->d.ldw, dst, c->d.ldw, c->st));
     }
     *alpha_out = alpha;
@@ -1478,6 +1498,11 @@ int ssn_solve(ssn_ctx *c, void *W, const ssn_params *pr, ssn_iter_record *log, i
     // (see the end of the loop), and the caller's block receives the final iterate at the end if it is not there.
     void *cur = W, *oth = c->trial;
     int k = 0;
+    c->z_for = nullptr;
+    if (!is_dense(c) && c->K > 1 && !pr->Sg_all && !(pr->flags & SSN_SOLVE_NO_MARGIN_CACHE)) {
+        c->z_keep = margins_alloc(c) == SSN_OK;
+        if (!c->z_keep) (void)hipGetLastError();     // no room: the line search forms both products if it gets there
+    }
 #define SOLVE_TRY(expr)                     \
     do {                                    \
         status = (expr);                    \
@@ -1580,6 +1605,8 @@ int ssn_solve(ssn_ctx *c, void *W, const ssn_params *pr, ssn_iter_record *log, i
         pend_rec = rec;
     }
 done:
+    c->z_keep = false;
+    c->z_for = nullptr;
 #undef SOLVE_TRY
 #undef SOLVE_HIP
     if (cur != W) {                          // the final iterate into the caller's block

@@ -38,7 +38,9 @@ struct RowsArgs {
     // right operand, p x K, leading dimension ldm
     const void *M;
     int64_t ldm;
-    const void *M2;      // ROW_MARGIN: second right operand (same leading dimension)
+    const void *M2;      // ROW_MARGIN: second right operand (same leading dimension); CSR only, nullptr: the margins of M
+                         // are the second half of the row's pair and its first half stays as it is
+    void *Zkeep;         // CSR, ROW_GRAD, nullable: the margins of M into the first half of the rows' pairs (stride 2 K)
     // per-row buffers with row stride KP (padded K): Pin read by ROW_APPLY, UP written by GRAD/PREP/APPLY
     const void *Pin;
     void *UP;
