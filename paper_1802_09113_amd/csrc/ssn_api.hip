@@ -81,7 +81,7 @@ struct ssn_ctx {
     // Inside ssn_solve on CSR data with more than one weight column (z_keep): gradient passes leave the margins X W in
     // the first halves of Zbuf, and z_for is the block they belong to (nullptr: none).  A line search that backs off
     // then needs X P only -- one pass over the data with one operand instead of two (20000 rows x 450 entries,
-    // 1.36 million x 19 weights, fp64: 535 us).  The n x K values cost the gradient pass nothing that shows.
+    // 1.36 million x 19 weights, fp64: 534 -> 276 us).  The n x K values cost the gradient pass nothing that shows.
     bool z_keep = false;
     const void *z_for = nullptr;
     // prepared Hessian sample
@@ -297,8 +297,8 @@ int launch_rows(ssn_ctx *c, const RowsArgs &a, int *nparts)
     }
     // dense: one wave per 16-row block; CSR: one wave per row
     int blocks = rows_grid_blocks(is_dense(c) ? a.nrows : a.nrows * 16, c->num_cus), split_waves = 0;
-    // few row blocks of a wide matrix: a workgroup per row block (needs 16-byte aligned rows)
-    if (is_dense(c) && (uintptr_t)c->d.X % 16 == 0 && (c->d.ldx * (int64_t)c->es) % 16 == 0)
+    // few row blocks of a wide matrix: a workgroup per row block
+    if (is_dense(c))
         dense_rows_plan(c->d.dtype, a.nrows, c->d.p, a.mode == ROW_MARGIN ? 2 * c->K : c->K, c->num_cus, &blocks, &split_waves);
     if (!is_dense(c)) {
         // rows differ in length, so more waves than fit on the chip at once let the hardware fill in behind the short
