@@ -524,6 +524,34 @@ def test_results_are_deterministic(cfg, n):
     pair.close()
 
 
+@pytest.mark.parametrize("dtype", DTYPES, ids=["f64", "f32"])
+def test_text_results_are_the_same_in_every_context(dtype):
+    # One set of stored entries over the whole vocabulary: every context that is made on it, and every call, gives the
+    # same bits (its column-sorted view neither drops nor moves an entry), and a gradient is that of the oracle.  So two
+    # runs whose results on text differ by an entry's worth were given different entries.
+    n = 3000
+    d = workload(4, n)
+    S_all = synth.sample_schedule(n, 150, 2)
+    runs = []
+    for k in range(3):
+        pair = Pair(d, dtype)
+        print(f"[case] text context {k} n={n} nnz={d['vals'].size} dtype={dtype}", flush=True)
+        W0h, W = pair.block(synth.probe(pair.p, pair.K, sub=1, scale=0.01))
+        for _ in range(2):
+            G, f = pair.gpu.ssn_gradient(W)
+            run = W.clone()
+            log, _ = pair.gpu.ssn_solve(run, torch.from_numpy(S_all).cuda(), theta=1e-4, T=10)
+            torch.cuda.synchronize()
+            runs.append((f, [(r["f"], r["alpha"], r["gnorm"]) for r in log], G.clone(), run))
+        if k == 0:
+            G_ref, f_ref = pair.oracle.gradient(W0h)
+            assert rel_scalar(f, f_ref) <= TOL[dtype] and rel_err(pair.host(G), G_ref) <= TOL[dtype]
+        pair.close()
+    for r in runs[1:]:
+        assert r[:2] == runs[0][:2]
+        assert torch.equal(r[2], runs[0][2]) and torch.equal(r[3], runs[0][3])
+
+
 def _ill_conditioned_shape(n, p, C, lam, seed, spread):
     """Dense stand-in whose columns differ in scale by e^(2 spread): with a small lambda CG needs its whole budget."""
     g = np.random.default_rng(seed)
