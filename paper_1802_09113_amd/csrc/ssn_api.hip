@@ -78,10 +78,13 @@ struct ssn_ctx {
     double *pub_host = nullptr;   // host-visible block ssn_solve's per-iteration scalars and CG state are written to
     double *pub_dev = nullptr;    // its device address
     double *cg_post_host = nullptr, *cg_post_dev = nullptr;   // ssn_cg's final state and trace, CG_POST_MAX doubles
-    // Inside ssn_solve on CSR data with more than one weight column (z_keep): gradient passes leave the margins X W in
-    // the first halves of Zbuf, and z_for is the block they belong to (nullptr: none).  A line search that backs off
-    // then needs X P only -- one pass over the data with one operand instead of two (20000 rows x 450 entries,
-    // 1.36 million x 19 weights, fp64: 534 -> 276 us).  The n x K values cost the gradient pass nothing that shows.
+    // Inside ssn_solve on CSR data with more than one weight column (z_keep), once a search has backed off and Zbuf is
+    // there: gradient passes leave the margins X W in the first halves of Zbuf, and z_for is the block they belong to
+    // (nullptr: none).  A line search that backs off from that block then needs X P only -- one pass over the data with one
+    // operand instead of two (20000 rows x 450 entries, 1.36 million x 19 weights, fp64: 534 -> 276 us).  That is so where
+    // the first trial was no gradient pass: in the last iteration and behind a rejected first trial.  A look-ahead pass
+    // leaves the trial point's margins in their place, and if its trial is rejected both products are formed.  The n x K
+    // values cost the gradient pass nothing that shows.
     bool z_keep = false;
     const void *z_for = nullptr;
     // prepared Hessian sample
@@ -609,7 +612,7 @@ int gradient_impl(ssn_ctx *c, const void *W, void *G, double *f, bool defer_f = 
     a.UP = c->Ubuf;
     int nparts = 0;
     a.part = c->part;
-    const bool keep = c->z_keep && !S;
+    const bool keep = c->z_keep && c->Zbuf && !S;      // no buffer yet: no search has backed off
     if (keep) {
         a.Zkeep = c->Zbuf;
         c->z_for = nullptr;
@@ -1499,10 +1502,7 @@ int ssn_solve(ssn_ctx *c, void *W, const ssn_params *pr, ssn_iter_record *log, i
     void *cur = W, *oth = c->trial;
     int k = 0;
     c->z_for = nullptr;
-    if (!is_dense(c) && c->K > 1 && !pr->Sg_all && !(pr->flags & SSN_SOLVE_NO_MARGIN_CACHE)) {
-        c->z_keep = margins_alloc(c) == SSN_OK;
-        if (!c->z_keep) (void)hipGetLastError();     // no room: the line search forms both products if it gets there
-    }
+    c->z_keep = !is_dense(c) && c->K > 1 && !pr->Sg_all && !(pr->flags & SSN_SOLVE_NO_MARGIN_CACHE);
 #define SOLVE_TRY(expr)                     \
     do {                                    \
         status = (expr);                    \

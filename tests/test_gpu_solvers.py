@@ -641,3 +641,27 @@ def test_line_search_on_cached_margins_takes_the_same_decisions(cfg, n, p, nS, w
     assert out["alpha"] == ref["alpha"] and out["n_eval"] == ref["n_eval"] and out["ok"] == ref["ok"]
     assert rel_scalar(out["f_new"], ref["f_new"]) <= TOL[dtype]
     pair.close()
+
+
+def test_solve_without_back_tracking_takes_no_margin_cache():
+    # the cache is n x 2 K values (192 MB here); a solve whose first trials are all accepted never looks at it
+    n, p, K = 300000, 64, 40
+    g = np.random.default_rng(6)
+    vals = g.standard_normal(n)
+    d = dict(layout="csr", n=n, p=p, C=K + 1, K=K, lam=1.0, rowptr=np.arange(n + 1, dtype=np.int64),
+             colidx=g.integers(0, p, size=n).astype(np.int32), vals=vals, labels=g.integers(0, K + 1, size=n).astype(np.int32))
+    pair = Pair(d, F64)
+    S_all = synth.sample_schedule(n, 2000, 3)
+    Sd = torch.from_numpy(S_all).cuda()
+    _, W = pair.block(np.zeros((p, K)))
+    G, _ = pair.gpu.ssn_gradient(W)                          # the whole matrix's view and the other workspaces
+    pair.gpu.ssn_hess_prepare(W, Sd[0].contiguous())
+    pair.gpu.ssn_cg(G, 1e-4, 10)
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    print("[case] solve without back-tracking", flush=True)
+    log, _ = pair.gpu.ssn_solve(W, Sd, theta=1e-4, T=10)
+    torch.cuda.synchronize()
+    assert [r["ls_evals"] for r in log] == [1, 1, 1]
+    assert free - torch.cuda.mem_get_info()[0] < n * 2 * K * 8 // 2
+    pair.close()
