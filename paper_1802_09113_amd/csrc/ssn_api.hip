@@ -1329,7 +1329,9 @@ int margins_enqueue(ssn_ctx *c, const void *W, const void *P)
     a.mode = ROW_MARGIN;
     a.UP = c->Zbuf;
     a.KP = 2 * c->K;
+    c->z_for = nullptr;
     SSN_TRY(launch_rows(c, a, nullptr));
+    c->z_for = c->z_keep ? W : nullptr;          // whose margins the first halves are, also where another block's were before
     const int vb = vec_blocks(c->d.p * (int64_t)c->K);
     SSN_HIP(c, launch_dot3_part(c->d.dtype, c->d.p, c->K, W, c->d.ldw, P, c->d.ldw, c->ls_dots, vb, c->st));
     return SSN_OK;

@@ -665,3 +665,25 @@ def test_solve_without_back_tracking_takes_no_margin_cache():
     assert [r["ls_evals"] for r in log] == [1, 1, 1]
     assert free - torch.cuda.mem_get_info()[0] < n * 2 * K * 8 // 2
     pair.close()
+
+
+@pytest.mark.parametrize("lookahead", [True, False], ids=["look_ahead", "no_look_ahead"])
+@pytest.mark.parametrize("dtype", DTYPES, ids=["f64", "f32"])
+def test_margins_kept_from_gradient_passes_change_nothing(dtype, lookahead):
+    # The second run finds the margin cache of the first, so its gradient passes leave X W there and a search that backs
+    # off adds X P only; the first forms both products at its first back-off.  Same bits.
+    n, nS, iters = 403, 40, 6
+    pair = Pair(workload(4, n), dtype)
+    Sd = torch.from_numpy(synth.sample_schedule(n, nS, iters)).cuda()
+    runs = []
+    for k in range(3):
+        print(f"[case] kept margins run={k} dtype={dtype} lookahead={lookahead}", flush=True)
+        _, W = pair.block(np.zeros((pair.p, pair.K)))
+        log, _ = pair.gpu.ssn_solve(W, Sd, theta=1e-4, T=10, lookahead=lookahead)
+        torch.cuda.synchronize()
+        runs.append(([(r["f"], r["alpha"], r["ls_evals"], r["cg_iters"]) for r in log], W.clone()))
+    evals = [r[2] for r in runs[0][0]]
+    assert sum(e > 1 for e in evals) >= 2                    # iterations that backed off
+    for r in runs[1:]:
+        assert r[0] == runs[0][0] and torch.equal(r[1], runs[0][1])
+    pair.close()
