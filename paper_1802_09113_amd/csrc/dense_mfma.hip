@@ -16,6 +16,7 @@
 
 #include <cstdlib>
 #include <limits>
+#include <type_traits>
 
 namespace ssn {
 
@@ -470,18 +471,48 @@ __global__ __launch_bounds__(SPLIT ? 1024 : 64 * ROWS_WAVES_PER_BLOCK) void dens
         }
         f0 = p / (STEP * UNR) * (STEP * UNR);
         if (SPLIT && wib != 0) f0 = p;                 // the tail belongs to wave 0
-        for (; f0 < p; f0 += STEP) {                   // guarded tail
-            const int64_t f = f0 + VEC * g;
+        // The tail, less than a trip.  With four elements per vector it can be 63 features long: loads clamped into the row,
+        // so that a step's are in flight together (one behind a guard each was a wait each: 120000 x 191 fp32, 18 weight
+        // columns, objective kernel 60 -> 40 us, and aligned rows of 784 features 47 -> 41 us on 40000).  The shorter tails of
+        // the other widths keep the guarded loads: with the clamped ones their main loops came out up to 1.4 times slower
+        // (fp32 element loads) or 1.07 times (fp64).
+        if constexpr (VEC == 4) {
+#pragma unroll 1
+            for (; f0 < p; f0 += STEP) {
+                T xt[RB][VEC], wt[VEC][NB];
 #pragma unroll
-            for (int m = 0; m < VEC; ++m) {
-                const bool ok = (f + m) < p;
+                for (int m = 0; m < VEC; ++m) {
+                    const int64_t f = f0 + VEC * g + m, fc = f < p ? f : p - 1;
 #pragma unroll
-                for (int nb = 0; nb < NB; ++nb) {
-                    const T w = (ok && cval[nb]) ? mcol[nb][(f + m) * ldm] : T(0);
+                    for (int k = 0; k < RB; ++k) xt[k][m] = xrow[k][fc];
 #pragma unroll
-                    for (int k = 0; k < RB; ++k) {
-                        const T x = ok ? xrow[k][f + m] : T(0);
-                        acc[k][nb] = mfma16(x, w, acc[k][nb]);
+                    for (int nb = 0; nb < NB; ++nb) wt[m][nb] = mcol[nb][fc * ldm];
+                }
+#pragma unroll
+                for (int m = 0; m < VEC; ++m) {
+                    const bool ok = f0 + VEC * g + m < p;
+#pragma unroll
+                    for (int nb = 0; nb < NB; ++nb) {
+                        const T w = (ok && cval[nb]) ? wt[m][nb] : T(0);
+#pragma unroll
+                        for (int k = 0; k < RB; ++k) acc[k][nb] = mfma16(ok ? xt[k][m] : T(0), w, acc[k][nb]);
+                    }
+                }
+            }
+        } else {
+            for (; f0 < p; f0 += STEP) {                   // guarded tail
+                const int64_t f = f0 + VEC * g;
+#pragma unroll
+                for (int m = 0; m < VEC; ++m) {
+                    const bool ok = (f + m) < p;
+#pragma unroll
+                    for (int nb = 0; nb < NB; ++nb) {
+                        const T w = (ok && cval[nb]) ? mcol[nb][(f + m) * ldm] : T(0);
+#pragma unroll
+                        for (int k = 0; k < RB; ++k) {
+                            const T x = ok ? xrow[k][f + m] : T(0);
+                            acc[k][nb] = mfma16(x, w, acc[k][nb]);
+                        }
                     }
                 }
             }
@@ -546,7 +577,8 @@ __global__ __launch_bounds__(256) void dense_xtu_kernel(XtuArgs a)
     struct __attribute__((packed, aligned(sizeof(T)))) pack { T v[VEC]; };      // any element-aligned row, as above
     constexpr int FT = 64;
     constexpr int NL = FT / (16 * VEC);
-    const int lane = threadIdx.x & 63, wib = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63;
+    const int wib = FROMZ ? (int)(threadIdx.x >> 6) : __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int q = lane & 15, g = lane >> 4;
     const int64_t p = a.p;
     const int K = a.K;
@@ -585,43 +617,79 @@ __global__ __launch_bounds__(256) void dense_xtu_kernel(XtuArgs a)
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) acc[t][nb] = v4{0, 0, 0, 0};
 
+    // A tile that ends behind the last feature loads element by element, clamped to the row: what it reads twice goes to
+    // rows of the result that are not stored.
+    const int last = (int)(p - 1 - f0 < FT - 1 ? p - 1 - f0 : FT - 1);
+    auto load_x = [&](const T *xt, int fl, auto whole) -> pack {
+        if constexpr (decltype(whole)::value) return *(const pack *)(xt + fl);
+        pack r;
+#pragma unroll
+        for (int m = 0; m < VEC; ++m) r.v[m] = xt[fl + m < last ? fl + m : last];
+        return r;
+    };
     // main loop: 16 rows (four MFMA contraction steps) per trip, every load of the trip issued before its
-    // first MFMA; the guarded loop below takes the rest
+    // first MFMA; the loop below takes the rest
     constexpr int RU = 4;
     int64_t r0 = r_begin;
-    if (full) {
-        for (; r0 + 4 * RU <= r_end; r0 += 4 * RU) {
-            pack xv[RU][NL];
-            T ub[RU][NB];
-            T zsl[FROMZ ? RU : 1][MAXS], pinv[FROMZ ? RU : 1];
+    if constexpr (FROMZ) {
+        // whole tiles only: its registers are full, and a copy of the loop for the last one took a wave of four
+        if (full) {
+            for (; r0 + 4 * RU <= r_end; r0 += 4 * RU) {
+                pack xv[RU][NL];
+                T ub[RU][NB], zsl[RU][MAXS], pinv[RU];
 #pragma unroll
-            for (int u = 0; u < RU; ++u) {
-                const int64_t sc = r0 + 4 * u + g;
-                const int64_t xr = a.S ? (int64_t)a.S[sc] : sc;
-                const T *xrow = X + xr * a.ldx + f0 + VEC * q;
+                for (int u = 0; u < RU; ++u) {
+                    const int64_t sc = r0 + 4 * u + g;
+                    const int64_t xr = a.S ? (int64_t)a.S[sc] : sc;
+                    const T *xrow = X + xr * a.ldx + f0 + VEC * q;
 #pragma unroll
-                for (int ld = 0; ld < NL; ++ld) xv[u][ld] = *(const pack *)(xrow + ld * 16 * VEC);
-                if constexpr (FROMZ) {
+                    for (int ld = 0; ld < NL; ++ld) xv[u][ld] = *(const pack *)(xrow + ld * 16 * VEC);
                     load_z(sc, zsl[u], pinv[u]);      // every load of the trip is issued before the first row sum
-                } else {
+                }
+#pragma unroll
+                for (int u = 0; u < RU; ++u) ub[u][0] = form_u(zsl[u], pinv[u], true);
+#pragma unroll
+                for (int u = 0; u < RU; ++u)
+#pragma unroll
+                    for (int ld = 0; ld < NL; ++ld)
+#pragma unroll
+                        for (int m = 0; m < VEC; ++m)
+#pragma unroll
+                            for (int nb = 0; nb < NB; ++nb)
+                                acc[ld * VEC + m][nb] = mfma16(xv[u][ld].v[m], ub[u][nb], acc[ld * VEC + m][nb]);
+            }
+        }
+    } else {
+        // The last, incomplete tile of features takes these trips too: four rows at a time, each load behind a guard, its
+        // wave was what the launch waited for (40000 rows, three weight columns: 1999 features fp32 108 -> 59 us, 2047
+        // features fp64 241 -> 121 us, 2000 features, aligned, fp32 106 -> 57 us).
+        auto trips = [&](auto whole) {
+            for (; r0 + 4 * RU <= r_end; r0 += 4 * RU) {
+                pack xv[RU][NL];
+                T ub[RU][NB];
+#pragma unroll
+                for (int u = 0; u < RU; ++u) {
+                    const int64_t sc = r0 + 4 * u + g;
+                    const int64_t xr = a.S ? (int64_t)a.S[sc] : sc;
+                    const T *xrow = X + xr * a.ldx + f0;
+#pragma unroll
+                    for (int ld = 0; ld < NL; ++ld) xv[u][ld] = load_x(xrow, ld * 16 * VEC + VEC * q, whole);
 #pragma unroll
                     for (int nb = 0; nb < NB; ++nb) ub[u][nb] = U[sc * a.KP + nb * 16 + q];
                 }
+#pragma unroll
+                for (int u = 0; u < RU; ++u)
+#pragma unroll
+                    for (int ld = 0; ld < NL; ++ld)
+#pragma unroll
+                        for (int m = 0; m < VEC; ++m)
+#pragma unroll
+                            for (int nb = 0; nb < NB; ++nb)
+                                acc[ld * VEC + m][nb] = mfma16(xv[u][ld].v[m], ub[u][nb], acc[ld * VEC + m][nb]);
             }
-            if constexpr (FROMZ) {
-#pragma unroll
-                for (int u = 0; u < RU; ++u) ub[u][0] = form_u(zsl[u], pinv[u], true);
-            }
-#pragma unroll
-            for (int u = 0; u < RU; ++u)
-#pragma unroll
-                for (int ld = 0; ld < NL; ++ld)
-#pragma unroll
-                    for (int m = 0; m < VEC; ++m)
-#pragma unroll
-                        for (int nb = 0; nb < NB; ++nb)
-                            acc[ld * VEC + m][nb] = mfma16(xv[u][ld].v[m], ub[u][nb], acc[ld * VEC + m][nb]);
-        }
+        };
+        if (full) trips(std::true_type{});
+        else trips(std::false_type{});
     }
     for (; r0 < r_end; r0 += 4) {
         const int64_t si = r0 + g;
@@ -647,6 +715,8 @@ __global__ __launch_bounds__(256) void dense_xtu_kernel(XtuArgs a)
             pack xv;
             if (full) {
                 xv = *(const pack *)(xrow + fl);
+            } else if constexpr (!FROMZ) {
+                xv = load_x(xrow, fl, std::false_type{});
             } else {
 #pragma unroll
                 for (int m = 0; m < VEC; ++m) xv.v[m] = (f0 + fl + m) < p ? xrow[fl + m] : T(0);
@@ -835,11 +905,25 @@ static hipError_t rows_dispatch_mode(const RowsArgs &a, int blocks, int split_wa
     constexpr int VEC = 16 / sizeof(T);
     const int nb = ((MODE == ROW_MARGIN ? 2 * a.K : a.K) + 15) / 16;
     if (nb != 1 && nb != 2) return hipErrorInvalidValue;
-    // Rows that are not 16-byte aligned take the same loads once two trips of them fit (features behind the last whole trip
-    // are read element by element, so no load leaves its row): 10007 x 331 fp32, 24 classes, objective kernel
-    // 17.0 -> 12.2 us; 20001 x 2051 with ten classes, also on a workgroup per row block now, objective call 102 -> 49 us fp32,
-    // 131 -> 92 us fp64.  Narrower ones keep the element (or 8-byte) loads, whose trips they fill.
-    const bool v = vec_ok<T>(a.X, a.ldx) || a.p >= 32 * VEC;
+    // Rows that are not 16-byte aligned take the same loads (features behind the last whole trip are read element by element,
+    // so no load leaves its row): always on a workgroup per row block, and with a wave per row block where they are the
+    // faster form.  Objective kernel, element loads / 16-byte loads, us:
+    //   fp32, from two trips (128 features) on: 10000 x 331, 24 classes 16.9/10.2; 120000 x 163, 19 classes 37.5/35.3;
+    //     40000 x 1999, four classes 148/80.  97 features on 120000 rows are 25.2/29.0, hence the line.
+    //   fp64, one class tile, four classes: the bytes in flight pay once every SIMD has a wave (16384 rows).  1301 features:
+    //     9000 rows 47.1/47.6, 16000 49/51, 17000 50/36, 40000 135/109; 129 features: 9000 rows 6.8/7.1, 40000 13.6/12.5.
+    //   fp64, two class tiles: fewer trips, each with twice the W operands, but two waves per SIMD (2048 row blocks at a
+    //     time) where element loads leave three (3072).  In as many rounds as those, from two trips (64 features) on:
+    //     9000 x 65 9.0/8.6, 9000 x 1999 139/90, 60000 x 331 0.84 of the time; with a round more, rarely before there are
+    //     four and 512 features: 40000 x 129 1.12, 48000 x 1301 1.05, 80000 x 785 1.05, 100000 x 785 0.95, 120000 x 1999 0.86.
+    const bool aligned = vec_ok<T>(a.X, a.ldx);
+    bool v = aligned;
+    if (!aligned) {
+        const int64_t nblk = (a.nrows + 15) / 16, round16 = (nblk + 2047) / 2048, round_el = (nblk + 3071) / 3072;
+        if (sizeof(T) == 4) v = a.p >= 128;
+        else if (nb == 1) v = a.p >= 128 && nblk > 1024;
+        else v = a.p >= 64 && (round16 == round_el || (round16 >= 4 && a.p >= 512));
+    }
     if (split_waves > 0) {
         dim3 grid(blocks), block(64 * split_waves);
         const size_t lds = (size_t)split_waves * nb * 256 * sizeof(T);
@@ -848,7 +932,9 @@ static hipError_t rows_dispatch_mode(const RowsArgs &a, int blocks, int split_wa
         return hipGetLastError();
     }
     dim3 grid(blocks), block(64 * ROWS_WAVES_PER_BLOCK);
-    const bool pair = v && nb == 1 && a.p >= 512;
+    // two row blocks per trip on aligned rows only: on others it was never the faster form (fp64, three weight columns,
+    // 9000 x 1301: 67 us against 47, 40000 x 1301: 148 against 109; fp32 38 against 24, 60 against 47)
+    const bool pair = aligned && nb == 1 && a.p >= 512;
     if constexpr (sizeof(T) == 4) {
         if (!v && nb == 1 && half_vec_ok(4, a.X, a.ldx)) {
             hipLaunchKernelGGL((dense_rows_kernel<T, 1, 2, MODE, false, false>), grid, block, 0, st, a);
@@ -889,8 +975,8 @@ template <typename T> static hipError_t xtu_dispatch(const XtuArgs &a, hipStream
     constexpr int VEC = 16 / sizeof(T);
     const int nb = (a.K + 15) / 16;
     // a tile of 64 features is read in whole vectors whatever the rows' alignment; a matrix without a whole tile keeps
-    // the element (or 8-byte) loads on unaligned rows.  Measured with
-    // the rows kernel's: gradient call of 60001 x 785 fp32, 33 classes, 191 -> 148 us, direction from its 5 % sample 715 -> 342 us.
+    // the element (or 8-byte) loads on unaligned rows.  Element / 16-byte loads, us, three weight columns, 40000 rows: 1301
+    // features fp32 46/43, fp64 94/92, 2047 features fp32 61/61; 18 weight columns: 331 features fp32 28.6/22.3, fp64 35/35.
     const bool aligned = vec_ok<T>(a.X, a.ldx), v = aligned || a.p >= 64;
     dim3 grid((unsigned)((a.p + 255) / 256), (unsigned)a.nchunks), block(256);
     if (a.Zpart) {
