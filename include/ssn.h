@@ -22,7 +22,12 @@
  *     void*; NULL = the default stream).  Calls that return a scalar through
  *     a [host] pointer return once everything they enqueued has completed
  *     (they wait for the last kernel's result to arrive in host memory, or
- *     for the stream); all other calls are asynchronous.
+ *     for the stream); all other calls are asynchronous.  The waiting thread
+ *     spins for up to 20 ms, a core's worth, and leaves a longer wait to the
+ *     runtime's stream synchronisation.  That goes for the objective and
+ *     gradient value, the accuracy, ssn_cg, each trial of a line search, and
+ *     the index check of every call that validates a sample (ssn_hess_prepare,
+ *     ssn_hessvec, ssn_gradient_sampled, ssn_solve).
  *   - Element type T is float (SSN_F32) or double (SSN_F64) for X/vals, W, V,
  *     G, HV, P.  Sums over rows are carried in fp64 in both cases.
  *   - W, V, G, HV, P (direction) are p-by-K, row-major, class index fastest,

@@ -536,12 +536,14 @@ double now_ms();
 
 // Spin on the ticket a kernel posts behind its value (c->f_seq: the last one given out).  Everything enqueued before
 // that kernel has completed by then (one stream), and the host is back a microsecond or two after the store instead
-// of a stream synchronisation's wake-up later.  A ticket that does not come (a failed launch, a fault)
-// ends in the synchronisation, which reports it.
+// of a stream synchronisation's wake-up later.  A wait that is long beside that wake-up is left to the synchronisation,
+// which waits as the process has told the runtime to (by default it spins, too); so is a ticket that does not come
+// (a failed launch, a fault, a stream under capture: none comes there, and the synchronisation refuses at once).
 int await_ticket(ssn_ctx *c)
 {
+    constexpr double SPIN_MS = 20.0;
     const unsigned long long want = c->f_seq;
-    const double t_give_up = now_ms() + 2000.0;
+    const double t_give_up = now_ms() + SPIN_MS;
     for (unsigned spin = 0;; ++spin) {
         if (__atomic_load_n(c->f_ticket, __ATOMIC_ACQUIRE) == want) return SSN_OK;
         if ((spin & 0x3ff) == 0x3ff && now_ms() > t_give_up) break;

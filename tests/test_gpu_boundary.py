@@ -1,6 +1,10 @@
 """GPU tests of the boundary's remaining calls: the device-scalar forms of objective and gradient, the accuracy
 of held-out rows described by an ssn_desc, and the conversion between the paper's stacked d-vector and the
 p x K blocks of this library (checked through the explicit Hessian of eq. (7a)/(7b) in the paper's ordering)."""
+import os
+import subprocess
+import sys
+
 import numpy as np
 import pytest
 import torch
@@ -102,3 +106,48 @@ def test_stacked_vector_ordering_against_the_explicit_hessian(ldw):
     torch.cuda.synchronize()
     assert torch.equal(back, vd)
     pair.close()
+
+
+# In a process of its own: a refused call ends its capture, and the runtime remembers that.
+_UNDER_CAPTURE = """
+import os, sys, time, torch
+from paper_1802_09113_amd.binding import Context, SsnError, SSN_E_HIP
+X = torch.randn(500, 40, device="cuda", dtype=torch.float64)
+ctx = Context(torch.randint(0, 3, (500,), device="cuda", dtype=torch.int32), 3, 1e-2, X=X)
+W = torch.zeros(40, 2, device="cuda", dtype=torch.float64)
+S = torch.arange(0, 500, 5, device="cuda", dtype=torch.int32)
+G, _ = ctx.ssn_gradient(W)
+ctx.ssn_hess_prepare(W, S)
+ctx.ssn_cg(G, 1e-4, 5)
+torch.cuda.synchronize()
+call = {"prepare": lambda: ctx.ssn_hess_prepare(W, S), "cg": lambda: ctx.ssn_cg(G, 1e-4, 5, P=W),
+        "predict": lambda: ctx.ssn_predict(W, want_pred=False), "objective": lambda: ctx.ssn_objective(W)}[sys.argv[1]]
+st, g = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+ctx.ssn_set_stream(st.cuda_stream)
+status = 0
+with torch.cuda.stream(st):
+    g.capture_begin()
+    t = time.monotonic()
+    try:
+        call()
+    except SsnError as e:
+        status = e.status
+    t = time.monotonic() - t
+    try:
+        g.capture_end()
+    except RuntimeError:
+        pass
+print("refused", status == SSN_E_HIP, t, flush=True)
+os._exit(0)
+"""
+
+
+@pytest.mark.parametrize("call", ["prepare", "cg", "predict", "objective"])
+def test_calls_that_wait_are_refused_under_capture_at_once(call):
+    # nothing runs while a stream is being captured, so the result these calls wait for cannot come
+    print(f"[case] {call} under capture", flush=True)
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    out = subprocess.run([sys.executable, "-c", _UNDER_CAPTURE, call], cwd=root, capture_output=True, text=True, timeout=100)
+    words = out.stdout.split()
+    assert words[:2] == ["refused", "True"], (out.stdout, out.stderr[-2000:])
+    assert float(words[2]) < 0.5
