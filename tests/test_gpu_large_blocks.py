@@ -1,6 +1,7 @@
-"""Passes over p x K weight blocks at the sizes where they change form: contiguous blocks of more than 65 536 elements
-go as 16-byte vectors in one share per workgroup, smaller, padded or unaligned ones element by element.  CSR data of few
-rows, so that the block passes are what the calls consist of.  Against the oracle, and axpy against its own arithmetic."""
+"""Passes over p x K weight blocks at the sizes where they change form: contiguous, 16-byte aligned blocks that give every
+thread of the launch a vector (fp64: all of more than 65 536 elements; fp32: multiples of 1024 from there on, and all of
+1 048 576 and more) go as 16-byte vectors in one share per workgroup, the others element by element.  CSR data of few rows, so
+that the block passes are what the calls consist of.  Against the oracle, and axpy against its own arithmetic."""
 import numpy as np
 import pytest
 import torch
@@ -21,16 +22,39 @@ def _data(n, p, C):
                 rowptr=rowptr, colidx=colidx, vals=g.standard_normal(colidx.size))
 
 
-# 65536 elements (the last element-wise size), one more, a tail of every length behind the vectors, a workgroup's share
-# that ends inside a round of four vectors, a million elements in shares of several rounds
+# 65536 elements (one per thread, element by element), one more, shares that end inside a round of four vectors per thread,
+# one and two million elements, packed and padded
 @pytest.mark.parametrize("dtype", [F64, F32], ids=["f64", "f32"])
 @pytest.mark.parametrize("p,C,pad", [(65536, 2, 0), (65537, 2, 0), (21847, 4, 0), (10923, 8, 0), (131075, 2, 0), (65539, 20, 0),
                                      (65539, 20, 1), (400001, 6, 0)])
 def test_block_passes(p, C, pad, dtype):
+    _check(p, C, pad, 0, dtype)
+
+
+# Shares of several rounds (from 2 097 154 elements in fp64, 4 194 308 in fp32) with every length of tail behind the last
+# whole vector; the smallest vector pass of fp32 (66560 elements, without a tail) and the element-wise size behind it;
+# packed blocks that start one element behind a 16-byte boundary
+@pytest.mark.parametrize("dtype", [F64, F32], ids=["f64", "f32"])
+@pytest.mark.parametrize("p,C,shift", [(5000000, 2, 0), (5000001, 2, 0), (5000002, 2, 0), (5000003, 2, 0), (1700003, 4, 0),
+                                       (66560, 2, 0), (66561, 2, 0), (66560, 2, 1), (1400001, 4, 1)])
+def test_block_passes_over_several_rounds(p, C, shift, dtype):
+    _check(p, C, 0, shift, dtype)
+
+
+def _check(p, C, pad, shift, dtype):
     n, d = 60, _data(60, p, C)
     pair = Pair(d, dtype, ldw=C - 1 + pad)
+    if shift:
+        plain = pair.block
+
+        def shifted(host):
+            r, t = plain(host)
+            flat = torch.empty(shift + t.numel(), dtype=t.dtype, device=t.device)
+            flat[shift:].copy_(t.flatten())
+            return r, flat[shift:].view(t.shape)
+        pair.block = shifted
     tol = TOL[dtype]
-    print(f"[case] block p={p} C={C} pad={pad} dtype={dtype}", flush=True)
+    print(f"[case] block p={p} C={C} pad={pad} shift={shift} dtype={dtype}", flush=True)
     Wh, Wd = pair.block(synth.probe(p, C - 1, sub=1, scale=0.3))
     G_ref, f_ref = pair.oracle.gradient(Wh)
     G, f = pair.gpu.ssn_gradient(Wd)
