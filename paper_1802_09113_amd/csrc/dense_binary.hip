@@ -163,7 +163,7 @@ template <typename T, int VEC, int MODE> __global__ __launch_bounds__(256) void 
     }
 }
 
-// Few rows (the sampled rows of a product, a small matrix): a workgroup of up to eight waves per row.  Two rows per
+// Few rows (the sampled rows of a product, a small matrix): a workgroup of up to eight waves for one row.  Two rows per
 // wave, as above, puts 300 sampled rows on 150 waves for 1024 SIMDs, and each wave walks its 2 x 40 KB in five dependent
 // trips; here a row's vectors are spread over as many threads as leave each about four of them (binary_rows_plan), all
 // requested together, and the wave sums run on the vector units (DPP) before one exchange through LDS.  What bounds it
@@ -176,13 +176,11 @@ template <typename T, int VEC, int MODE> __global__ __launch_bounds__(BSPLIT_WAV
     struct wpack { T v[VEC]; };              // element alignment: the weights may start anywhere
     constexpr int UNR = 8;
     constexpr bool TWO = MODE == ROW_MARGIN;
-    __shared__ double red[2][2][BSPLIT_WAVES];       // two buffers in turn: one barrier per row
+    __shared__ double red[2][BSPLIT_WAVES];
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, NT = blockDim.x, nw = NT >> 6;
-    const T *X = (const T *)a.X, *w = (const T *)a.M, *w2 = TWO ? (const T *)a.M2 : w;
+    const T *w = (const T *)a.M, *w2 = TWO ? (const T *)a.M2 : w;
     const int64_t p = a.p, ldm = a.ldm;
     const int64_t pv = p / VEC * VEC;
-    double loss = 0.0;
-    int hits = 0, buf = 0;
     auto weights = [&](const T *base, int64_t g) {
         wpack r;
         if (ldm == 1) r = *(const wpack *)(base + g);
@@ -191,64 +189,64 @@ template <typename T, int VEC, int MODE> __global__ __launch_bounds__(BSPLIT_WAV
             for (int m = 0; m < VEC; ++m) r.v[m] = base[(g + m) * ldm];
         return r;
     };
-    for (int64_t s0 = blockIdx.x; s0 < a.nrows; s0 += gridDim.x, buf ^= 1) {
-        const int64_t r0 = a.S ? (int64_t)a.S[s0] : s0;
-        const T *x = X + r0 * a.ldx;
-        T z = 0, y = 0;
-        for (int64_t f = (int64_t)tid * VEC; f < pv; f += (int64_t)UNR * NT * VEC) {
-            pack xa[UNR] = {};
-            wpack wa[UNR] = {}, wb[TWO ? UNR : 1] = {};
+    const int64_t s0 = blockIdx.x;           // the launcher's grid has a workgroup for every row
+    const int64_t r0 = a.S ? (int64_t)a.S[s0] : s0;
+    const T *x = (const T *)a.X + r0 * a.ldx;
+    T z = 0, y = 0;
+    for (int64_t f = (int64_t)tid * VEC; f < pv; f += (int64_t)UNR * NT * VEC) {
+        pack xa[UNR] = {};
+        wpack wa[UNR] = {}, wb[TWO ? UNR : 1] = {};
 #pragma unroll
-            for (int u = 0; u < UNR; ++u) {
-                const int64_t g = f + (int64_t)u * NT * VEC;
-                if (g >= pv) continue;
-                xa[u] = *(const pack *)(x + g);
-                wa[u] = weights(w, g);
-                if constexpr (TWO) wb[u] = weights(w2, g);
+        for (int u = 0; u < UNR; ++u) {
+            const int64_t g = f + (int64_t)u * NT * VEC;
+            if (g >= pv) continue;
+            xa[u] = *(const pack *)(x + g);
+            wa[u] = weights(w, g);
+            if constexpr (TWO) wb[u] = weights(w2, g);
+        }
+#pragma unroll
+        for (int u = 0; u < UNR; ++u)
+#pragma unroll
+            for (int m = 0; m < VEC; ++m) {
+                z += xa[u].v[m] * wa[u].v[m];
+                if constexpr (TWO) y += xa[u].v[m] * wb[u].v[m];
             }
-#pragma unroll
-            for (int u = 0; u < UNR; ++u)
-#pragma unroll
-                for (int m = 0; m < VEC; ++m) {
-                    z += xa[u].v[m] * wa[u].v[m];
-                    if constexpr (TWO) y += xa[u].v[m] * wb[u].v[m];
-                }
-        }
-        for (int64_t g = pv + tid; g < p; g += NT) {           // features beyond the last whole vector
-            z += x[g] * w[g * ldm];
-            if constexpr (TWO) y += x[g] * w2[g * ldm];
-        }
-        const double zs = wave_inclusive_scan((double)z);      // lane 63: the wave's sum
-        double ys = 0.0;
-        if constexpr (TWO) ys = wave_inclusive_scan((double)y);
-        if (lane == 63) {
-            red[buf][0][wv] = zs;
-            if constexpr (TWO) red[buf][1][wv] = ys;
-        }
-        __syncthreads();
-        if (wv == 0) {
-            double t = 0.0, t2 = 0.0;
-#pragma unroll
-            for (int k = 0; k < BSPLIT_WAVES; ++k) {
-                if (k >= nw) break;
-                t += red[buf][0][k];
-                if constexpr (TWO) t2 += red[buf][1][k];
-            }
-            if constexpr (TWO) {
-                if (lane == 0) {
-                    T *Z = (T *)a.UP;
-                    Z[s0 * a.KP] = (T)t;
-                    Z[s0 * a.KP + 1] = (T)t2;
-                }
-            } else {
-                binary_row<T, MODE>(a, s0, r0, (T)t, lane, loss, hits);
-            }
-        }
     }
+    for (int64_t g = pv + tid; g < p; g += NT) {           // features beyond the last whole vector
+        z += x[g] * w[g * ldm];
+        if constexpr (TWO) y += x[g] * w2[g * ldm];
+    }
+    const double zs = wave_inclusive_scan((double)z);      // lane 63: the wave's sum
+    double ys = 0.0;
+    if constexpr (TWO) ys = wave_inclusive_scan((double)y);
+    if (lane == 63) {
+        red[0][wv] = zs;
+        if constexpr (TWO) red[1][wv] = ys;
+    }
+    __syncthreads();
+    if (wv != 0) return;
+    double t = 0.0, t2 = 0.0;
+#pragma unroll
+    for (int k = 0; k < BSPLIT_WAVES; ++k) {
+        if (k >= nw) break;
+        t += red[0][k];
+        if constexpr (TWO) t2 += red[1][k];
+    }
+    if constexpr (TWO) {
+        if (lane == 0) {
+            T *Z = (T *)a.UP;
+            Z[s0 * a.KP] = (T)t;
+            Z[s0 * a.KP + 1] = (T)t2;
+        }
+        return;
+    }
+    double loss = 0.0;
+    int hits = 0;
+    binary_row<T, MODE>(a, s0, r0, (T)t, lane, loss, hits);
     if constexpr (MODE == ROW_OBJ || MODE == ROW_GRAD || MODE == ROW_APPLY) {
-        if (tid == 0) a.loss_part[blockIdx.x] = loss;
+        if (lane == 0) a.loss_part[blockIdx.x] = loss;
     } else if constexpr (MODE == ROW_PRED) {
-        if (tid == 0) a.hit_part[blockIdx.x] = hits;
+        if (lane == 0) a.hit_part[blockIdx.x] = hits;
     }
 }
 
@@ -339,16 +337,16 @@ void binary_rows_plan(int64_t nrows, int64_t p, int64_t es, int num_cus, int *bl
     if (nt > BSPLIT_WAVES * 64) nt = BSPLIT_WAVES * 64;
     if (nt < 64) nt = 64;
     *split = few ? (int)nt : 0;
-    int64_t b = *split ? nrows : (nrows + 7) / 8;
+    int64_t b = (nrows + 7) / 8;
     const int64_t cap = (int64_t)num_cus * 8;
     if (b > cap) b = cap;
-    *blocks = (int)(b < 1 ? 1 : b);
+    *blocks = few ? (int)nrows : (int)b;
     *parts = *split ? *blocks : *blocks * ROWS_WAVES_PER_BLOCK;
 }
 
 hipError_t launch_binary_rows(int dtype, const RowsArgs &a, int blocks, int split, hipStream_t st)
 {
-    if (a.K != 1) return hipErrorInvalidValue;
+    if (a.K != 1 || blocks < 1 || (split && blocks != a.nrows)) return hipErrorInvalidValue;
     if (dtype == SSN_F32)
         return rows_aligned<float>(a.X, a.ldx) ? rows_mode<float, 4>(a, blocks, split, st) : rows_mode<float, 1>(a, blocks, split, st);
     return rows_aligned<double>(a.X, a.ldx) ? rows_mode<double, 2>(a, blocks, split, st) : rows_mode<double, 1>(a, blocks, split, st);
