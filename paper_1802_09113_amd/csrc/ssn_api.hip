@@ -1418,7 +1418,7 @@ int ssn_predict(ssn_ctx *c, const void *W, int32_t *pred, double *acc)
     int nparts = 0;
     SSN_TRY(launch_rows(c, a, &nparts));
     if (acc) {
-        SSN_HIP(c, launch_sum_int(c->hit_part, nparts, c->int_dev + 1, c->f_host_dev, c->f_ticket_dev, ++c->f_seq, c->st));
+        SSN_HIP(c, launch_sum_int(c->hit_part, nparts, c->f_host_dev, c->f_ticket_dev, ++c->f_seq, c->st));
         SSN_TRY(await_ticket(c));
         *acc = *(volatile double *)c->f_host / (double)c->d.n;
     }

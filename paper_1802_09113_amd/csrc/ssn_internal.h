@@ -194,14 +194,14 @@ hipError_t launch_solve_publish(const double *slope_part, int n, const double *f
                                 double *host_out, bool support_only, hipStream_t st);
 // streaming read of `bytes` (multiple of 16, 16-byte aligned); one checksum partial per block
 hipError_t launch_stream_read(const void *src, int64_t bytes, double *part, int blocks, hipStream_t st);
-// *out = sum of a[0..na); also posted to the host (see post_to_host)
-hipError_t launch_sum_int(const int32_t *a, int na, int32_t *out, double *out_host, unsigned long long *ticket_host,
+// the sum of a[0..na) posted to the host (see post_to_host)
+hipError_t launch_sum_int(const int32_t *a, int na, double *out_host, unsigned long long *ticket_host,
                           unsigned long long ticket, hipStream_t st);
 
 // validation passes: *bad receives the number of offending entries
 hipError_t launch_check_range(const int32_t *v, int64_t count, int64_t lo, int64_t hi, int32_t *bad, hipStream_t st);
 // the count posted to the host by one launch of one workgroup (count <= CHECK_POST_MAX: beyond, one workgroup's chain of
-// trips takes longer than what it saves)
+// trips takes longer than what it saves).
 constexpr int CHECK_POST_MAX = 65536;
 hipError_t launch_check_range_post(const int32_t *v, int count, int64_t lo, int64_t hi, double *out_host,
                                    unsigned long long *ticket_host, unsigned long long ticket, hipStream_t st);

@@ -1015,7 +1015,7 @@ hipError_t launch_combine(const double *a, int na, double scale, const double *b
     return hipGetLastError();
 }
 
-__global__ __launch_bounds__(VEC_BLOCK) void sum_int_kernel(const int32_t *a, int na, int32_t *out, double *out_host,
+__global__ __launch_bounds__(VEC_BLOCK) void sum_int_kernel(const int32_t *a, int na, double *out_host,
                                                              unsigned long long *ticket_host, unsigned long long ticket)
 {
     __shared__ long long sm[VEC_BLOCK];
@@ -1027,16 +1027,13 @@ __global__ __launch_bounds__(VEC_BLOCK) void sum_int_kernel(const int32_t *a, in
         if ((int)threadIdx.x < s) sm[threadIdx.x] += sm[threadIdx.x + s];
         __syncthreads();
     }
-    if (threadIdx.x == 0) {
-        *out = (int32_t)sm[0];
-        post_to_host((double)(int32_t)sm[0], out_host, ticket_host, ticket);
-    }
+    if (threadIdx.x == 0) post_to_host((double)(int32_t)sm[0], out_host, ticket_host, ticket);
 }
 
-hipError_t launch_sum_int(const int32_t *a, int na, int32_t *out, double *out_host, unsigned long long *ticket_host,
+hipError_t launch_sum_int(const int32_t *a, int na, double *out_host, unsigned long long *ticket_host,
                           unsigned long long ticket, hipStream_t st)
 {
-    hipLaunchKernelGGL(sum_int_kernel, dim3(1), dim3(VEC_BLOCK), 0, st, a, na, out, out_host, ticket_host, ticket);
+    hipLaunchKernelGGL(sum_int_kernel, dim3(1), dim3(VEC_BLOCK), 0, st, a, na, out_host, ticket_host, ticket);
     return hipGetLastError();
 }
 
