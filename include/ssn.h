@@ -110,8 +110,9 @@ typedef struct {
 #define SSN_SOLVE_NO_PHASE_TIMES 2
 /* Back-tracking trials of the line search (every trial after the first) are evaluated on cached margins:
  * X (W + alpha P) = X W + alpha X P, so one pass over the data leaves X W and X P (n rows of 2K numbers) and each
- * further trial is a pass over those instead of over X.  The same F up to rounding; Alg. 3's trial sequence and
- * exit rules are unchanged.  This flag makes every trial a pass over the data, as Alg. 3 is written. */
+ * further trial is a pass over those instead of over X.  They are allocated when a search of the context first backs
+ * off (or by the first ssn_linesearch) and kept.  The same F up to rounding; Alg. 3's trial sequence and exit rules are
+ * unchanged.  This flag makes every trial a pass over the data, as Alg. 3 is written. */
 #define SSN_SOLVE_NO_MARGIN_CACHE 4
 
 /* Parameters of ssn_solve (Alg. 1, 2, 3).  The paper gives no numeric values for beta, rho,
