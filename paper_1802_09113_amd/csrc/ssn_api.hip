@@ -98,6 +98,8 @@ struct ssn_ctx {
     double *cg_parts = nullptr;                // dense paths: 2 x 2 x RED_MAX_PARTS partials of r.r and r.(H s), double-buffered
     void *cg_pb = nullptr;                     // CSR: best iterate on the sample's columns (cg_pb_cap elements)
     int64_t cg_pb_cap = 0;
+    void *hess = nullptr;                      // dense, small p K: blocks of the formed sub-sampled Hessian, per row chunk
+    int64_t hess_cap = 0;
     void *grad_next = nullptr;                 // gradient at the first line-search trial (look-ahead of ssn_solve)
     CgSlot *slots = nullptr;
     int slots_cap = 0;
@@ -166,6 +168,21 @@ int ensure_rows(ssn_ctx *c, void **buf, int64_t *have, int64_t rows)
     }
     SSN_HIP(c, hipMalloc(buf, (size_t)rows * (size_t)c->KP * c->es));
     *have = rows;
+    return SSN_OK;
+}
+
+// make sure a workspace has at least `need` elements
+int ensure_elems(ssn_ctx *c, void **buf, int64_t *have, int64_t need)
+{
+    if (*have >= need) return SSN_OK;
+    if (*buf) {
+        SSN_HIP(c, hipStreamSynchronize(c->st));
+        SSN_HIP(c, hipFree(*buf));
+        *buf = nullptr;
+        *have = 0;
+    }
+    SSN_HIP(c, hipMalloc(buf, (size_t)need * c->es));
+    *have = need;
     return SSN_OK;
 }
 
@@ -819,7 +836,7 @@ int ssn_destroy(ssn_ctx *c)
     if (c->st_aux) (void)hipStreamSynchronize(c->st_aux);      // a view of the next sample may still be in the making
     void *dev[] = {c->Zbuf, c->ls_dots, c->Ubuf, c->Pbuf, c->part, c->loss_part, c->hit_part, c->red_a, c->red_b, c->red_c, c->red_sq, c->scal_dev, c->int_dev,
                    c->cg_p, c->cg_r, c->cg_s, c->cg_hs, c->cg_parts, c->cg_pb, c->trial, c->grad, c->grad_next, c->dir, c->slots, c->trace_dev,
-                   c->tail_row, c->csr1_rwin, c->csr1_zrow, c->csr1_zhead};
+                   c->tail_row, c->csr1_rwin, c->csr1_zrow, c->csr1_zhead, c->hess};
     for (void *p : dev)
         if (p) (void)hipFree(p);
     if (c->host_pin) (void)hipHostFree(c->host_pin);
@@ -1106,6 +1123,22 @@ int ssn_hessvec(ssn_ctx *c, const void *W, const int32_t *S, int64_t nS, const v
     return ssn_hess_apply(c, V, HV);
 }
 
+// state slots and trace for T products
+static int ensure_slots(ssn_ctx *c, int32_t T)
+{
+    if (c->slots_cap >= T + 1) return SSN_OK;
+    SSN_HIP(c, hipStreamSynchronize(c->st));
+    if (c->slots) (void)hipFree(c->slots);
+    if (c->trace_dev) (void)hipFree(c->trace_dev);
+    c->slots = nullptr;
+    c->trace_dev = nullptr;
+    SSN_HIP(c, hipMalloc((void **)&c->slots, sizeof(CgSlot) * (size_t)(T + 1)));
+    SSN_HIP(c, hipMalloc((void **)&c->trace_dev, sizeof(double) * 3 * (size_t)(T + 1)));
+    SSN_HIP(c, hipMemsetAsync(c->slots, 0, sizeof(CgSlot) * (size_t)(T + 1), c->st));
+    c->slots_cap = T + 1;
+    return SSN_OK;
+}
+
 // every launch of Alg. 2; the final state waits in slots[T]
 // n_slope (nullable): on the CSR path the partials of <P_out, G> over the sample's columns are left in red_a,
 // *n_slope of them (the rest of the product is CgSlot::pibest * CgSlot::goff); 0 where they are not made
@@ -1118,6 +1151,34 @@ static int cg_enqueue(ssn_ctx *c, const void *G, double theta, int32_t T, void *
 {
     if (n_slope) *n_slope = 0;
     if (solve_fused) *solve_fused = false;
+    SSN_TRY(ensure_slots(c, T));
+    HessSmall hs{};
+    if (is_dense(c) && hess_small_plan(c->d.dtype, c->d.p, c->K, c->nS, T, c->num_cus, &hs)) {
+        SSN_TRY(ensure_elems(c, &c->hess, &c->hess_cap, hs.chunks * hs.elems));
+        RowsArgs r = rows_base(c);
+        r.S = c->S;
+        r.nrows = c->nS;
+        HessCg h{};
+        h.scale = scale_sample(c);
+        h.lambda = c->d.lambda;
+        h.theta = theta;
+        h.T = T;
+        h.ld = c->d.ldw;
+        h.G = G;
+        h.P = P_out;
+        h.fin = c->slots + T;
+        h.trace = solve_W ? nullptr : c->trace_dev;
+        if (solve_W && solve_trial && solve_pub) {
+            h.W = solve_W;
+            h.trial = solve_trial;
+            h.f_dev = c->scal_dev;
+            h.slope_dev = c->scal_dev + 1;
+            h.host_out = solve_pub;
+            if (solve_fused) *solve_fused = true;
+        }
+        SSN_HIP(c, launch_hess_small(c->d.dtype, hs, r, c->Pbuf, c->hess, h, c->st));
+        return SSN_OK;
+    }
     if (!c->cg_p) {
         SSN_TRY(vec_bytes_alloc(c, &c->cg_p));
         SSN_TRY(vec_bytes_alloc(c, &c->cg_r));
@@ -1126,17 +1187,6 @@ static int cg_enqueue(ssn_ctx *c, const void *G, double theta, int32_t T, void *
     if (is_dense(c) && !c->cg_hs) {
         SSN_TRY(vec_bytes_alloc(c, &c->cg_hs));
         SSN_HIP(c, hipMalloc((void **)&c->cg_parts, sizeof(double) * 4 * RED_MAX_PARTS));
-    }
-    if (c->slots_cap < T + 1) {
-        SSN_HIP(c, hipStreamSynchronize(c->st));
-        if (c->slots) (void)hipFree(c->slots);
-        if (c->trace_dev) (void)hipFree(c->trace_dev);
-        c->slots = nullptr;
-        c->trace_dev = nullptr;
-        SSN_HIP(c, hipMalloc((void **)&c->slots, sizeof(CgSlot) * (size_t)(T + 1)));
-        SSN_HIP(c, hipMalloc((void **)&c->trace_dev, sizeof(double) * 3 * (size_t)(T + 1)));
-        SSN_HIP(c, hipMemsetAsync(c->slots, 0, sizeof(CgSlot) * (size_t)(T + 1), c->st));
-        c->slots_cap = T + 1;
     }
     CgVecs v{};
     v.p = c->d.p;

@@ -368,4 +368,36 @@ hipError_t launch_cg_tail_solve(int dtype, const CgVecs &v, const CgSlot *prev, 
 hipError_t launch_cg_tail(int dtype, const CgVecs &v, const CgSlot *prev, CgSlot *fin, const double *rr_in, int n_in,
                           double theta, double *trace, int k, int blocks, hipStream_t st);
 
+
+// ---- small dense problems: H_S formed once, Alg. 2 in one workgroup (hess_small.hip) ---------------------
+struct HessSmall {
+    int pairs;               // class pairs a <= b: one p x p block each
+    int nc, pl;              // strips of eight features per block row; row length of a stored block
+    int upt;                 // strips per thread of the CG kernel
+    int nsup, chunks;        // pairs of feature blocks, row chunks of the forming kernel
+    int lds;
+    int64_t rows_per_chunk, elems;           // elems: of one chunk's blocks; the workspace holds chunks * elems
+};
+// whether this form serves T products on nS sampled rows, and how
+bool hess_small_plan(int dtype, int64_t p, int K, int64_t nS, int T, int num_cus, HessSmall *h);
+struct HessCg {
+    const void *H;           // set by the launcher, with the sizes below
+    int64_t elems;
+    int32_t nsum, p, K, pairs, nc, pl;
+    double scale, lambda, theta;
+    int32_t T;
+    int64_t ld;              // leading dimension of the p x K blocks below
+    const void *G;
+    void *P;                 // the direction
+    CgSlot *fin;
+    double *trace;
+    // inside ssn_solve (trial nullable): as in launch_cg_tail_solve
+    const void *W;
+    void *trial;
+    const double *f_dev;
+    double *slope_dev, *host_out;
+};
+// r: the sample's rows (S, nrows) and the row stride KP of their probabilities P
+hipError_t launch_hess_small(int dtype, const HessSmall &h, const RowsArgs &r, const void *P, void *part, HessCg a, hipStream_t st);
+
 }  // namespace ssn

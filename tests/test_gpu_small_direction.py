@@ -1,0 +1,83 @@
+"""GPU parity of Newton directions on a formed sub-sampled Hessian (dense problems of a few hundred weights): every strip
+count per thread, features below, at and above the strips of eight and the 16- and 64-feature tiles, one and several row
+chunks, padded weights and rows, and the shapes on either side of what the form serves."""
+import numpy as np
+import pytest
+import torch
+
+from tests.gpu_util import Pair, rel_err
+
+pytestmark = pytest.mark.gpu
+
+F64, F32 = torch.float64, torch.float32
+
+# n, p, C, nS, ldw, ldx.  Class pairs C (C - 1) / 2; the form's limit is some 32 000 (fp64) / 70 000 (fp32) elements
+CASES = [
+    (300, 1, 2, 40, None, None),          # one weight
+    (400, 8, 33, 64, None, None),         # 528 class pairs, one strip a row
+    (400, 9, 12, 1, 13, None),            # one row, two strips a row, padded weights
+    (700, 16, 6, 67, None, 19),           # one feature tile, padded rows
+    (900, 33, 5, 300, None, None),        # three feature tiles, chunks that the CG kernel adds itself
+    (4000, 54, 7, 1500, None, None),      # fp32: nine strips a thread; fp64: too many blocks, the matrix-free form
+    (2000, 50, 3, 2000, 3, 50),           # every row
+    (5000, 64, 4, 4999, None, None),      # whole tiles; twelve and more chunks
+    (1500, 65, 3, 700, 5, 67),            # two feature blocks, one of them one feature wide
+    (900, 130, 2, 500, None, None),       # binary, three feature blocks
+    (700, 176, 2, 333, None, None),       # binary, fp64: the widest served
+    (800, 264, 2, 120, None, 265),        # binary, fp32: the widest served; fp64: not
+    (600, 273, 2, 90, None, None),        # binary, not served
+]
+
+
+@pytest.mark.parametrize("dtype", [F64, F32], ids=["f64", "f32"])
+@pytest.mark.parametrize("n,p,C,nS,ldw,ldx", CASES)
+def test_direction_on_the_formed_hessian(n, p, C, nS, ldw, ldx, dtype):
+    g = np.random.default_rng(1000 * p + C)
+    X = g.standard_normal((n, p)) / np.sqrt(p)
+    labels = g.integers(0, C, n).astype(np.int32)
+    pair = Pair(dict(layout="dense", X=X, labels=labels, n=n, p=p, C=C, K=C - 1, lam=0.05), dtype, ldw=ldw, ldx=ldx)
+    Wh, Wd = pair.block(0.5 * g.standard_normal((p, C - 1)))
+    S = g.integers(0, n, nS)                       # a multiset
+    Gh, Gd = pair.block(pair.oracle.gradient(Wh)[0])
+    pair.gpu.ssn_hess_prepare(Wd, pair.idx(S))
+    # Features of norm one: the data term has eigenvalues of at most max(1, p / nS), lambda is 0.05, so five iterations
+    # amplify the rounding of a product (a few 1e-16 / 1e-7 over sums of up to 264 features) by the condition number, at
+    # most a few hundred, per iteration at worst; observed 1e-13 / 1e-5.
+    tol = 1e-10 if dtype == F64 else 2e-3
+    for theta, T in [(1e-30, 5), (0.2, 9)]:
+        print(f"[case] direction n={n} p={p} C={C} nS={nS} dtype={dtype} theta={theta}", flush=True)
+        ref = pair.oracle.cg(Wh, S, Gh, theta, T)
+        if theta < 1e-20 and np.min(ref["rnorm"]) < 1e-6 * np.linalg.norm(Gh):
+            ref = pair.oracle.cg(Wh, S, Gh, 1e-3, T)        # a handful of weights: converged within the budget
+            theta = 1e-3
+        out = pair.gpu.ssn_cg(Gd, theta, T)
+        torch.cuda.synchronize()
+        assert (out["iters"], out["flags"]) == (ref["iters"], ref["flags"])
+        np.testing.assert_allclose(out["alpha"], ref["alpha"], rtol=tol)
+        np.testing.assert_allclose(out["rnorm"], ref["rnorm"], rtol=100 * tol, atol=tol * np.linalg.norm(Gh))
+        np.testing.assert_allclose(out["sHs"], ref["sHs"], rtol=100 * tol)
+        assert rel_err(pair.host(out["p"]), ref["p"]) <= tol
+        again = pair.gpu.ssn_cg(Gd, theta, T)
+        torch.cuda.synchronize()
+        assert torch.equal(again["p"][:, : C - 1], out["p"][:, : C - 1])
+    pair.close()
+
+
+@pytest.mark.parametrize("dtype", [F64, F32], ids=["f64", "f32"])
+def test_formed_hessian_and_an_indefinite_product(dtype):
+    """lambda = 0 and rows of zeros: H_S is zero, s^T H s is not positive, the direction is the steepest descent."""
+    n, p, C = 200, 20, 4
+    X = np.zeros((n, p))
+    X[0] = 1.0
+    labels = (np.arange(n) % C).astype(np.int32)
+    pair = Pair(dict(layout="dense", X=X, labels=labels, n=n, p=p, C=C, K=C - 1, lam=0.0), dtype)
+    Wh, Wd = pair.block(np.ones((p, C - 1)))
+    S = np.arange(10, 60)
+    Gh, Gd = pair.block(pair.oracle.gradient(Wh)[0])
+    pair.gpu.ssn_hess_prepare(Wd, pair.idx(S))
+    ref = pair.oracle.cg(Wh, S, Gh, 1e-4, 6)
+    out = pair.gpu.ssn_cg(Gd, 1e-4, 6)
+    torch.cuda.synchronize()
+    assert (out["iters"], out["flags"]) == (ref["iters"], ref["flags"]) == (1, 2)
+    np.testing.assert_array_equal(pair.host(out["p"]), -Gh)
+    pair.close()
