@@ -104,17 +104,23 @@ __global__ __launch_bounds__(VEC_BLOCK) void csc_head_flag_kernel(const int32_t 
 }
 
 // rank[t] (exclusive scan of head, so rank + head - 1 is the position of entry t's column among the distinct
-// columns) -> cols[position] = column; ccol[e] = position for the entry's place e in row order (idx[t]);
+// columns) -> cols[position] = column, cstart[position] = its first entry (cstart ends with nnz); ccol[e] = position for the entry's place e in row order (idx[t]);
 // *ncols_out = number of distinct columns
 __global__ __launch_bounds__(VEC_BLOCK) void csc_support_kernel(const int32_t *key, const int32_t *head, const int32_t *rank,
-                                                                const int32_t *idx, int64_t nnz, int32_t *cols, int32_t *ccol,
-                                                                int32_t *ncols_out)
+                                                                const int32_t *idx, int64_t nnz, int32_t *cols, int32_t *cstart,
+                                                                int32_t *ccol, int32_t *ncols_out)
 {
     for (int64_t t = (int64_t)blockIdx.x * VEC_BLOCK + threadIdx.x; t < nnz; t += (int64_t)gridDim.x * VEC_BLOCK) {
         const int32_t pos = rank[t] + head[t] - 1;
-        if (head[t]) cols[pos] = key[t];
+        if (head[t]) {
+            cols[pos] = key[t];
+            cstart[pos] = (int32_t)t;
+        }
         ccol[idx[t]] = pos;
-        if (t == nnz - 1) *ncols_out = pos + 1;
+        if (t == nnz - 1) {
+            *ncols_out = pos + 1;
+            cstart[pos + 1] = (int32_t)nnz;
+        }
     }
 }
 
@@ -162,7 +168,8 @@ void csc_free(CscView *v)
 {
     void *all[] = {v->key, v->row, v->val, v->piece_start, v->piece_col, v->piece_part, v->off, v->key_in, v->idx_in, v->idx_out,
                    v->row_in, v->val_in, v->flag, v->pid, v->cub_tmp, v->count_dev, v->cols, v->ccol, v->piece_cpos,
-                   v->cnt, v->head, v->next, v->tsum, v->toff, v->ftoff, v->len, v->bitmap, v->eidx, v->csr_pos, v->win_pid};
+                   v->cnt, v->head, v->next, v->tsum, v->toff, v->ftoff, v->len, v->bitmap, v->eidx, v->csr_pos, v->win_pid,
+                   v->cstart, v->freq, v->freq_tmp, v->gram, v->xfreq};
     for (void *q : all)
         if (q) (void)hipFree(q);
     *v = CscView{};
@@ -192,6 +199,7 @@ hipError_t csc_build(CscView *v, int dtype, const int32_t *rowptr, const int32_t
     v->npieces = 0;
     v->win_npieces = -1;                 // the window index of an earlier build is void
     v->ncols = 0;
+    v->gram_rows = 0;
     v->has_support = false;
     if (!v->count_dev) CSC_HIP(hipMalloc((void **)&v->count_dev, 4 * sizeof(int32_t)));
 
@@ -279,6 +287,7 @@ hipError_t csc_build(CscView *v, int dtype, const int32_t *rowptr, const int32_t
     if (support) {
         // key_in / idx_in are free once the sort is done: they take the column-head flags and their scan
         CSC_HIP(grow((void **)&v->cols, &v->cap_cols, nnz, sizeof(int32_t)));
+        CSC_HIP(grow((void **)&v->cstart, &v->cap_cstart, nnz + 1, sizeof(int32_t)));
         CSC_HIP(grow((void **)&v->ccol, &v->cap_ccol, nnz, sizeof(int32_t)));
         hipLaunchKernelGGL(csc_head_flag_kernel, dim3(grid_for(nnz)), dim3(VEC_BLOCK), 0, st, v->key, nnz, v->key_in);
         bytes = 0;
@@ -287,7 +296,7 @@ hipError_t csc_build(CscView *v, int dtype, const int32_t *rowptr, const int32_t
         bytes = v->cub_bytes;
         CSC_HIP(hipcub::DeviceScan::ExclusiveSum(v->cub_tmp, bytes, v->key_in, v->idx_in, (int)nnz, st));
         hipLaunchKernelGGL(csc_support_kernel, dim3(grid_for(nnz)), dim3(VEC_BLOCK), 0, st, v->key, v->key_in, v->idx_in,
-                           v->idx_out, nnz, v->cols, v->ccol, v->count_dev + 1);
+                           v->idx_out, nnz, v->cols, v->cstart, v->ccol, v->count_dev + 1);
     }
     int32_t counts[2] = {0, 0};
     CSC_HIP(hipMemcpyAsync(counts, v->count_dev, (support ? 2 : 1) * sizeof(int32_t), hipMemcpyDeviceToHost, st));
@@ -453,6 +462,54 @@ static void own_scan1(const int32_t *in, int64_t n, int32_t *out, int32_t *total
     a.na = 1;
     a.n = n;
     own_scan(a, scratch, area, st);
+}
+
+// The distinct columns of at least fmin entries, in order: counted per tile of SCAN_TILE columns, the counts summed up by
+// one block, listed
+__global__ __launch_bounds__(VEC_BLOCK) void freq_count_kernel(const int32_t *cstart, int64_t nc, int32_t fmin, int32_t *tsum)
+{
+    const int64_t b0 = (int64_t)blockIdx.x * SCAN_TILE + (int64_t)threadIdx.x * SCAN_ITEMS;
+    int s = 0;
+#pragma unroll
+    for (int k = 0; k < SCAN_ITEMS; ++k)
+        if (b0 + k < nc) s += (cstart[b0 + k + 1] - cstart[b0 + k] >= fmin) ? 1 : 0;
+    int tot;
+    (void)block_exclusive_scan(s, &tot);
+    if (threadIdx.x == 0) tsum[blockIdx.x] = tot;
+}
+__global__ __launch_bounds__(VEC_BLOCK) void freq_write_kernel(const int32_t *cstart, int64_t nc, int32_t fmin, const int32_t *toff,
+                                                               int64_t cap, int32_t *freq)
+{
+    const int64_t b0 = (int64_t)blockIdx.x * SCAN_TILE + (int64_t)threadIdx.x * SCAN_ITEMS;
+    bool f[SCAN_ITEMS];
+    int s = 0;
+#pragma unroll
+    for (int k = 0; k < SCAN_ITEMS; ++k) {
+        f[k] = b0 + k < nc && cstart[b0 + k + 1] - cstart[b0 + k] >= fmin;
+        s += f[k];
+    }
+    int tot;
+    int64_t at = toff[blockIdx.x] + block_exclusive_scan(s, &tot);
+#pragma unroll
+    for (int k = 0; k < SCAN_ITEMS; ++k)
+        if (f[k] && at < cap) freq[at++] = (int32_t)(b0 + k);
+}
+hipError_t csc_frequent_columns(CscView *v, int fmin, hipStream_t st)
+{
+    const int64_t tiles = (v->ncols + SCAN_TILE - 1) / SCAN_TILE, cap = v->nnz / fmin + 1;
+    CSC_HIP(grow((void **)&v->freq, &v->cap_freq, cap + 1, sizeof(int32_t)));
+    CSC_HIP(grow((void **)&v->freq_tmp, &v->cap_freq_tmp, 2 * (tiles + 2), sizeof(int32_t)));
+    v->nfreq_dev = v->count_dev + 3;
+    ScanArgs a{};
+    a.na = 1;
+    a.tsum[0] = v->freq_tmp;
+    a.toff[0] = v->freq_tmp + tiles + 2;
+    a.total[0] = v->nfreq_dev;
+    hipLaunchKernelGGL(freq_count_kernel, dim3((unsigned)tiles), dim3(VEC_BLOCK), 0, st, v->cstart, (int64_t)v->ncols, fmin, a.tsum[0]);
+    hipLaunchKernelGGL(scan_tiles_kernel, dim3(1), dim3(VEC_BLOCK), 0, st, a, tiles);
+    hipLaunchKernelGGL(freq_write_kernel, dim3((unsigned)tiles), dim3(VEC_BLOCK), 0, st, v->cstart, (int64_t)v->ncols, fmin, a.toff[0],
+                       cap, v->freq);
+    return hipGetLastError();
 }
 
 // zeroes the multiplicities and the bitmap of sampled rows, empties the rows' lists of sample positions
@@ -652,12 +709,13 @@ __global__ __launch_bounds__(VEC_BLOCK) void samp_piece_count_kernel(const int32
     }
 }
 // ... and numbered here: piece_start / piece_col of every piece (and the sentinels behind the last), and with
-// `support` the distinct columns cols[], the pieces' places among them piece_cpos[], and every entry's place among
+// `support` the distinct columns cols[], their first entries cstart[], the pieces' places among them piece_cpos[], and every entry's place among
 // them written at the entry's place in row order: ccol[eidx[t]]
 __global__ __launch_bounds__(VEC_BLOCK) void samp_piece_write_kernel(const int32_t *key, const int32_t *nnz_dev, const int32_t *np_dev,
-                                                                      const int32_t *toff_p, const int32_t *toff_h, bool support,
-                                                                      const int32_t *eidx, int32_t *piece_start, int32_t *piece_col,
-                                                                      int32_t *piece_cpos, int32_t *cols, int32_t *ccol)
+                                                                      const int32_t *nc_dev, const int32_t *toff_p,
+                                                                      const int32_t *toff_h, bool support, const int32_t *eidx,
+                                                                      int32_t *piece_start, int32_t *piece_col, int32_t *piece_cpos,
+                                                                      int32_t *cols, int32_t *cstart, int32_t *ccol)
 {
     const int64_t nnz = *nnz_dev;
     const int64_t b0 = (int64_t)blockIdx.x * SCAN_TILE + (int64_t)threadIdx.x * SCAN_ITEMS;
@@ -681,7 +739,10 @@ __global__ __launch_bounds__(VEC_BLOCK) void samp_piece_write_kernel(const int32
                 if (support) piece_cpos[pid] = pos;
             }
             if (support) {
-                if (hf[k]) cols[pos] = kk[k];
+                if (hf[k]) {
+                    cols[pos] = kk[k];
+                    cstart[pos] = (int32_t)t;
+                }
                 ccol[eidx[t]] = pos;
             }
         }
@@ -690,7 +751,10 @@ __global__ __launch_bounds__(VEC_BLOCK) void samp_piece_write_kernel(const int32
     }
     if (blockIdx.x == 0 && threadIdx.x < 4) {          // the sentinels behind the last piece
         const int32_t np = *np_dev;
-        if (threadIdx.x == 0) piece_start[np] = (int32_t)nnz;
+        if (threadIdx.x == 0) {
+            piece_start[np] = (int32_t)nnz;
+            if (support) cstart[*nc_dev] = (int32_t)nnz;
+        }
         piece_col[np + threadIdx.x] = -1;
         if (support) piece_cpos[np + threadIdx.x] = -1;
     }
@@ -728,6 +792,7 @@ hipError_t csc_build_filtered(CscView *v, const CscView &full, int dtype, const 
     v->npieces = 0;
     v->win_npieces = -1;                 // the window index of an earlier build is void
     v->ncols = 0;
+    v->gram_rows = 0;
     v->has_support = false;
     v->nrows = nS;
     const int64_t bound = nS * (int64_t)max_len;
@@ -767,6 +832,7 @@ hipError_t csc_build_filtered(CscView *v, const CscView &full, int dtype, const 
         CSC_HIP(grow((void **)&v->len, &v->cap_len, nS + 1, sizeof(int32_t)));
         CSC_HIP(grow((void **)&v->eidx, &v->cap_eidx, bound, sizeof(int32_t)));
         CSC_HIP(grow((void **)&v->cols, &v->cap_cols, bound, sizeof(int32_t)));
+        CSC_HIP(grow((void **)&v->cstart, &v->cap_cstart, bound + 1, sizeof(int32_t)));
         CSC_HIP(grow((void **)&v->ccol, &v->cap_ccol, bound, sizeof(int32_t)));
         CSC_HIP(grow(&v->val_in, &v->cap_valin, bound, es));
         CSC_HIP(grow((void **)&v->piece_cpos, &v->cap_pcpos, bound + 4, sizeof(int32_t)));
@@ -812,7 +878,8 @@ hipError_t csc_build_filtered(CscView *v, const CscView &full, int dtype, const 
                            a.tsum[1]);
         hipLaunchKernelGGL(scan_tiles_kernel, dim3(1), dim3(VEC_BLOCK), 0, st, a, stiles);
         hipLaunchKernelGGL(samp_piece_write_kernel, dim3((unsigned)stiles), dim3(VEC_BLOCK), 0, st, v->key, nnz_dev, np_dev,
-                           a.toff[0], a.toff[1], support, v->eidx, v->piece_start, v->piece_col, v->piece_cpos, v->cols, v->ccol);
+                           nc_dev, a.toff[0], a.toff[1], support, v->eidx, v->piece_start, v->piece_col, v->piece_cpos, v->cols,
+                           v->cstart, v->ccol);
     }
     CSC_HIP(hipGetLastError());
     int32_t counts[3] = {0, 0, 0};

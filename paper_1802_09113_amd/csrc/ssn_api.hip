@@ -98,6 +98,8 @@ struct ssn_ctx {
     double *cg_parts = nullptr;                // dense paths: 2 x 2 x RED_MAX_PARTS partials of r.r and r.(H s), double-buffered
     void *cg_pb = nullptr;                     // CSR: best iterate on the sample's columns (cg_pb_cap elements)
     int64_t cg_pb_cap = 0;
+    double *dual = nullptr;                    // CSR: workspace of directions in the sample's row space
+    int64_t dual_cap = 0;
     void *hess = nullptr;                      // dense, small p K: blocks of the formed sub-sampled Hessian, per row chunk
     int64_t hess_cap = 0;
     void *grad_next = nullptr;                 // gradient at the first line-search trial (look-ahead of ssn_solve)
@@ -836,7 +838,7 @@ int ssn_destroy(ssn_ctx *c)
     if (c->st_aux) (void)hipStreamSynchronize(c->st_aux);      // a view of the next sample may still be in the making
     void *dev[] = {c->Zbuf, c->ls_dots, c->Ubuf, c->Pbuf, c->part, c->loss_part, c->hit_part, c->red_a, c->red_b, c->red_c, c->red_sq, c->scal_dev, c->int_dev,
                    c->cg_p, c->cg_r, c->cg_s, c->cg_hs, c->cg_parts, c->cg_pb, c->trial, c->grad, c->grad_next, c->dir, c->slots, c->trace_dev,
-                   c->tail_row, c->csr1_rwin, c->csr1_zrow, c->csr1_zhead, c->hess};
+                   c->tail_row, c->csr1_rwin, c->csr1_zrow, c->csr1_zhead, c->hess, c->dual};
     for (void *p : dev)
         if (p) (void)hipFree(p);
     if (c->host_pin) (void)hipHostFree(c->host_pin);
@@ -1046,7 +1048,8 @@ int ssn_rowmajor_to_vec(ssn_ctx *c, const void *block, void *vec)
 
 // validate: check the sample indices first (one pass and one synchronisation)
 // CSR, inside ssn_solve: the column-sorted view (and support) of the sample S, built on the auxiliary stream
-static int prebuild_sample_view(ssn_ctx *c, const int32_t *S, int64_t nS)
+static bool dual_ok(const ssn_ctx *c, const CscView &v, double theta, int32_t T);
+static int prebuild_sample_view(ssn_ctx *c, const int32_t *S, int64_t nS, double theta, int32_t T)
 {
     c->next_ready = false;
     if (!c->st_aux) {
@@ -1054,6 +1057,7 @@ static int prebuild_sample_view(ssn_ctx *c, const int32_t *S, int64_t nS)
         SSN_HIP(c, hipEventCreateWithFlags(&c->ev_aux, hipEventDisableTiming));
     }
     SSN_TRY(build_sample_view(c, &c->csc_next, S, nS, c->st_aux, true));
+    if (dual_ok(c, c->csc_next, theta, T)) SSN_HIP(c, csc_gram(&c->csc_next, c->d.dtype, c->st_aux));
     SSN_HIP(c, hipEventRecord(c->ev_aux, c->st_aux));
     c->next_S = S;
     c->next_nS = nS;
@@ -1139,6 +1143,67 @@ static int ensure_slots(ssn_ctx *c, int32_t T)
     return SSN_OK;
 }
 
+// Whether Alg. 2 runs in the row space of the sample (csr_dual.hip): a few thousand rows at most, and a residual that is not
+// asked to fall so far that the part of g the sampled rows span cancels in r.r (1e-16 g.g beside theta^2 g.g).
+static bool dual_ok(const ssn_ctx *c, const CscView &v, double theta, int32_t T)
+{
+    if (!(theta >= 1e-5) || v.nnz < 1 || !v.has_support || v.nrows > GRAM_ROWS_MAX) return false;
+    if (dual_blocks(v.nrows, c->K) > RED_MAX_PARTS) return false;
+    // Where the line lies: the Gram matrix against what T iterations save, in us as measured on text-like and evenly spread
+    // columns (direction with its preparation, nS rows; iteration on the sample's columns / in the row space, then the
+    // direction of ten products):
+    //   1355191 columns, 450 entries a row, K 19, fp64:  nS 100 40/10, 698/444; 1000 85/12, 1231/594; 2000 125/20, 1724/868
+    //   the same, K 1, fp32:                             nS 400 27/9,  447/325; 2000 29/13, 506/532 (refused)
+    //   20958 columns, 57 entries a row, K 4, fp64:      nS 1000 32/10, 469/293; 2000 35/14, 500/371
+    //   12500 columns, 400 entries a row, K 1, fp64:     nS 1000 24/11, 423/326; 2000 25/13, 460/532 (refused)
+    const double n = (double)v.nrows / 1000.0, nnz = (double)v.nnz, es = (double)c->es, K = (double)c->K;
+    const double iter = c->K == 1 ? 22.0 + nnz / 200e3 : 27.0 + (9.0 * (double)v.ncols + 2.0 * nnz) * K * es / 7e6;
+    const double here = 9.5 + n * n * (1.0 + K / 16.0), gram = 45.0 + 100.0 * n * nnz / 1e6;
+    return (double)T * (iter - here) * 0.9 > gram;
+}
+
+static int dual_enqueue(ssn_ctx *c, const void *G, double theta, int32_t T, void *P_out, int *n_slope, bool trace)
+{
+    CscView &v = c->csc_samp;
+    if (v.gram_rows != v.nrows) SSN_HIP(c, csc_gram(&v, c->d.dtype, c->st));
+    int nks = 0, kper = 0;
+    const int64_t need = dual_doubles(v.nrows, c->K, &nks, &kper);
+    if (c->dual_cap < need) {
+        if (c->dual) {
+            SSN_HIP(c, hipStreamSynchronize(c->st));
+            SSN_HIP(c, hipFree(c->dual));
+            c->dual = nullptr;
+            c->dual_cap = 0;
+        }
+        SSN_HIP(c, hipMalloc((void **)&c->dual, (size_t)need * sizeof(double)));
+        c->dual_cap = need;
+    }
+    const int vb = vec_blocks(c->d.p * (int64_t)c->K);
+    SSN_HIP(c, launch_dot_part(c->d.dtype, c->d.p, c->K, G, c->d.ldw, G, c->d.ldw, c->red_b, vb, nullptr, c->st));
+    SSN_HIP(c, launch_cg_init_state(c->red_b, vb, c->slots + T, c->st));
+    DualCg a{};
+    a.rowptr = c->d.rowptr;
+    a.colidx = c->d.colidx;
+    a.vals = c->d.vals;
+    a.S = c->S;
+    a.G = G;
+    a.ldg = c->d.ldw;
+    a.P = c->Pbuf;
+    a.KP = c->KP;
+    a.K = c->K;
+    a.n = (int32_t)v.nrows;
+    a.scale = scale_sample(c);
+    a.lambda = c->d.lambda;
+    a.theta = theta;
+    a.gram = v.gram;
+    a.trace = trace ? c->trace_dev : nullptr;
+    SSN_HIP(c, launch_dual_cg(c->d.dtype, a, c->slots, T, c->dual, c->Ubuf, c->KP, n_slope ? c->red_a : nullptr, c->st));
+    if (n_slope) *n_slope = dual_blocks(v.nrows, c->K);
+    SSN_HIP(c, launch_cg_expand_fill(c->d.dtype, c->d.p, c->K, G, c->d.ldw, P_out, c->d.ldw, c->slots + T, c->st));
+    SSN_HIP(c, launch_csc_apply(c->d.dtype, v, c->K, c->KP, c->Ubuf, 1.0, P_out, c->d.ldw, nullptr, nullptr, c->st));
+    return SSN_OK;
+}
+
 // every launch of Alg. 2; the final state waits in slots[T]
 // n_slope (nullable): on the CSR path the partials of <P_out, G> over the sample's columns are left in red_a,
 // *n_slope of them (the rest of the product is CgSlot::pibest * CgSlot::goff); 0 where they are not made
@@ -1179,6 +1244,7 @@ static int cg_enqueue(ssn_ctx *c, const void *G, double theta, int32_t T, void *
         SSN_HIP(c, launch_hess_small(c->d.dtype, hs, r, c->Pbuf, c->hess, h, c->st));
         return SSN_OK;
     }
+    if (!is_dense(c) && dual_ok(c, c->csc_samp, theta, T)) return dual_enqueue(c, G, theta, T, P_out, n_slope, !solve_W);
     if (!c->cg_p) {
         SSN_TRY(vec_bytes_alloc(c, &c->cg_p));
         SSN_TRY(vec_bytes_alloc(c, &c->cg_r));
@@ -1601,7 +1667,8 @@ int ssn_solve(ssn_ctx *c, void *W, const ssn_params *pr, ssn_iter_record *log, i
         bool first_mirrored = false;
         SOLVE_TRY(trial_enqueue(c, cur, c->dir, 1.0, ahead ? c->grad_next : nullptr, &first_mirrored, tail_fused, oth));
         // CSR: while the device works through the queue above, the view of the next sample is built beside it
-        if (!is_dense(c) && k + 1 < pr->iters) SOLVE_TRY(prebuild_sample_view(c, pr->S_all + (int64_t)(k + 1) * pr->nS, pr->nS));
+        if (!is_dense(c) && k + 1 < pr->iters)
+            SOLVE_TRY(prebuild_sample_view(c, pr->S_all + (int64_t)(k + 1) * pr->nS, pr->nS, pr->theta, pr->T));
         double f_first = 0.0;
         const int first_status = read_objective(c, first_mirrored, &f_first);       // the one wait of the iteration
         if (first_status != SSN_OK && first_status != SSN_E_NONFINITE) {

@@ -209,6 +209,8 @@ hipError_t launch_check_range_post(const int32_t *v, int count, int64_t lo, int6
                                    unsigned long long *ticket_host, unsigned long long ticket, hipStream_t st);
 hipError_t launch_check_rowptr(const int32_t *rowptr, int64_t n, int64_t nnz, int32_t *bad, hipStream_t st);
 
+constexpr int GRAM_ROWS_MAX = 2048;      // the most rows of a sample whose Gram matrix is formed
+
 // ---- column-sorted view of a set of CSR rows (csc.hip) --------------------------------------------
 struct CscView {
     int64_t nnz = 0;                 // entries in the view
@@ -235,6 +237,17 @@ struct CscView {
     bool has_support = false;
     int32_t ncols = 0;
     int32_t *cols = nullptr;         // ncols
+    int32_t *cstart = nullptr;       // ncols + 1: the columns' first entries in the sorted list
+    int64_t cap_cstart = 0;
+    // the positions (among the distinct ones) of the frequent columns (csc_frequent_columns), *nfreq_dev of them
+    int32_t *nfreq_dev = nullptr;
+    int32_t *freq = nullptr, *freq_tmp = nullptr;
+    int64_t cap_freq = 0, cap_freq_tmp = 0;
+    // the Gram matrix X_S X_S^T of the view's rows (csr_dual.hip), gram_ld(gram_rows) x gram_ld(gram_rows) in fp64;
+    // gram_rows == 0: not made since the view was built.  xfreq: the frequent columns as dense rows (scratch)
+    int64_t gram_rows = 0;
+    double *gram = nullptr, *xfreq = nullptr;
+    int64_t cap_gram = 0, cap_xfreq = 0;
     int32_t *ccol = nullptr;         // nnz
     int32_t *piece_cpos = nullptr;   // npieces + 4 (sentinels -1)
     int64_t cap_cols = 0, cap_ccol = 0, cap_pcpos = 0, cap_valin = 0;
@@ -264,6 +277,8 @@ hipError_t csc_build_filtered(CscView *v, const CscView &full, int dtype, const 
 hipError_t csr_max_row_len(const int32_t *rowptr, int64_t n, int32_t *scratch_dev, int32_t *out, hipStream_t st);
 // one weight column: index of the view's 64-entry windows for the lane-per-entry product kernel (call after a build)
 hipError_t csc_window_index(CscView *v, hipStream_t st);
+// the distinct columns of at least fmin entries of a view with its support, listed in v->freq
+hipError_t csc_frequent_columns(CscView *v, int fmin, hipStream_t st);
 void csc_free(CscView *v);
 void csc_free_scratch(CscView *v);
 // out += coef * X_view^T U (U rows indexed like the view's row selection); slot (nullable): multiply by
@@ -368,6 +383,32 @@ hipError_t launch_cg_tail_solve(int dtype, const CgVecs &v, const CgSlot *prev, 
 hipError_t launch_cg_tail(int dtype, const CgVecs &v, const CgSlot *prev, CgSlot *fin, const double *rr_in, int n_in,
                           double theta, double *trace, int k, int blocks, hipStream_t st);
 
+
+// ---- CSR: directions in the row space of a small sample (csr_dual.hip) ------------------------------------
+int64_t gram_ld(int64_t rows);           // rows and row length of a Gram matrix: whole tiles of 64
+// the Gram matrix of the view's rows (built with the support, at most GRAM_ROWS_MAX rows) into v->gram
+hipError_t csc_gram(CscView *v, int dtype, hipStream_t st);
+int64_t dual_doubles(int64_t n, int K, int *nks, int *kper);     // workspace of launch_dual_cg
+int dual_blocks(int64_t n, int K);       // slope partials it leaves (<= RED_MAX_PARTS is a condition of the launch)
+struct DualCg {
+    const int32_t *rowptr, *colidx, *S;
+    const void *vals, *G, *P;            // P: probabilities of the sample's rows, row stride KP
+    int64_t ldg;
+    int32_t KP, K, n;                    // n: sampled rows
+    double scale, lambda, theta;
+    const double *gram;
+    double *trace;
+    // set by the launcher
+    int32_t ld, nks, kper;
+    double *zg, *w, *u, *us, *xh, *yr, *ys, *yp, *ybest;     // X_S g; X_S r; U(X_S r); U(X_S s); X_S H s; coefficients of r, s, p
+    double *part, *zu_part;
+};
+// every launch of Alg. 2; slots[T] holds the initial state (launch_cg_init_state: g.g over all coordinates) on entry and the
+// final one behind it: the direction is pibest G + X_S^T yout, <direction, G> = pibest goff + the sum of slope_part (nullable)
+hipError_t launch_dual_cg(int dtype, DualCg a, CgSlot *slots, int T, double *work, void *yout, int KP, double *slope_part, hipStream_t st);
+// P_out = fin->pibest * G
+hipError_t launch_cg_expand_fill(int dtype, int64_t p, int K, const void *G, int64_t ldg, void *P_out, int64_t ldp, const CgSlot *fin,
+                                 hipStream_t st);
 
 // ---- small dense problems: H_S formed once, Alg. 2 in one workgroup (hess_small.hip) ---------------------
 struct HessSmall {

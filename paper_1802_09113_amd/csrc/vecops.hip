@@ -1349,24 +1349,33 @@ __global__ __launch_bounds__(VEC_BLOCK) void cg_expand_rows_kernel(int K, T *P, 
     }
 }
 
+hipError_t launch_cg_expand_fill(int dtype, int64_t p, int K, const void *G, int64_t ldg, void *P_out, int64_t ldp, const CgSlot *fin,
+                                 hipStream_t st)
+{
+    const int b1 = vec_blocks(p * K) * 4 > 4096 ? 4096 : vec_blocks(p * K) * 4;
+    if (dtype == SSN_F32)
+        hipLaunchKernelGGL(cg_expand_fill_kernel<float>, dim3(b1), dim3(VEC_BLOCK), 0, st, p, K, (const float *)G, ldg,
+                           (float *)P_out, ldp, fin);
+    else
+        hipLaunchKernelGGL(cg_expand_fill_kernel<double>, dim3(b1), dim3(VEC_BLOCK), 0, st, p, K, (const double *)G, ldg,
+                           (double *)P_out, ldp, fin);
+    return hipGetLastError();
+}
+
 hipError_t launch_cg_expand(int dtype, int64_t p, int K, const void *G, int64_t ldg, void *P_out, int64_t ldp,
                             const CgSlot *fin, const void *pb, const int32_t *cols, int64_t ncols, double *dot_part,
                             int *n_dot, hipStream_t st)
 {
-    const int b1 = vec_blocks(p * K) * 4 > 4096 ? 4096 : vec_blocks(p * K) * 4;
     const int b2 = vec_blocks(ncols * K);                  // <= RED_MAX_PARTS: one partial per block
     if (n_dot) *n_dot = b2;
-    if (dtype == SSN_F32) {
-        hipLaunchKernelGGL(cg_expand_fill_kernel<float>, dim3(b1), dim3(VEC_BLOCK), 0, st, p, K, (const float *)G, ldg,
-                           (float *)P_out, ldp, fin);
+    const hipError_t e = launch_cg_expand_fill(dtype, p, K, G, ldg, P_out, ldp, fin, st);
+    if (e != hipSuccess) return e;
+    if (dtype == SSN_F32)
         hipLaunchKernelGGL(cg_expand_rows_kernel<float>, dim3(b2), dim3(VEC_BLOCK), 0, st, K, (float *)P_out, ldp,
                            (const float *)pb, cols, ncols, (const float *)G, ldg, dot_part);
-    } else {
-        hipLaunchKernelGGL(cg_expand_fill_kernel<double>, dim3(b1), dim3(VEC_BLOCK), 0, st, p, K, (const double *)G, ldg,
-                           (double *)P_out, ldp, fin);
+    else
         hipLaunchKernelGGL(cg_expand_rows_kernel<double>, dim3(b2), dim3(VEC_BLOCK), 0, st, K, (double *)P_out, ldp,
                            (const double *)pb, cols, ncols, (const double *)G, ldg, dot_part);
-    }
     return hipGetLastError();
 }
 
