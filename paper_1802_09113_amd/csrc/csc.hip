@@ -20,6 +20,7 @@
 #include "ssn_math.h"
 
 #include <hipcub/hipcub.hpp>
+#include <type_traits>
 
 namespace ssn {
 
@@ -915,8 +916,21 @@ struct CscApply {
 // (piece_col may be the pieces' columns or their positions among the distinct columns: equal columns have
 // equal positions, and the result row written is whichever of the two the caller's `out` is indexed by)
 
-// lane group (slot) g of a wave = K lanes, one per class; NS = 64 / K groups per wave, one piece per group
-template <typename T> __global__ __launch_bounds__(256) void csc_piece_kernel(CscApply a)
+// Weight columns per lane of csc_piece_kernel: 16 bytes of a row of U where the row is that long
+template <typename T> static int piece_vec(int K)
+{
+    const int most = 16 / (int)sizeof(T);
+    return K >= most ? most : K >= 2 ? 2 : 1;
+}
+
+// A lane group of a wave = ceil(K / VEC) lanes, each with VEC weight columns; one piece per group, 64 / that many groups.
+// (The last lane's columns are the last VEC ones: where VEC does not divide K it forms some that its neighbour has, and
+// leaves them to it.)  Every lane of a group reads the piece's entries itself, four per load -- the same addresses across
+// the group -- and the gathers of U follow, eight in flight.
+// With a lane per weight column, entries handed round the group by lane shuffles and 8-byte gathers this kernel was bound
+// by instruction issue: 12 instructions per entry and three entries at a time at K = 19 (9 M entries of 817 000 columns,
+// K 19: 234 us in fp32 against 306 in fp64).
+template <typename T, int VEC> __global__ __launch_bounds__(256) void csc_piece_kernel(CscApply a)
 {
     if (a.skip && *a.skip) return;
     double coef = a.coef;
@@ -924,118 +938,79 @@ template <typename T> __global__ __launch_bounds__(256) void csc_piece_kernel(Cs
         if (a.slot->done || a.slot->brk) return;
         coef *= -a.slot->alpha;
     }
-    // no lane leaves before the shuffles below: a lane without a piece (spare lanes of the wave, groups past the
-    // last piece) walks through them with an empty piece
+    struct __attribute__((packed, aligned(sizeof(T)))) pack { T v[VEC]; };      // rows of U start at any element
+    struct __attribute__((packed, aligned(4))) four { int32_t r[4]; };
+    struct __attribute__((packed, aligned(sizeof(T)))) fourv { T v[4]; };
     const int lane = threadIdx.x & 63;
-    const int K = a.K, NS = 64 / K;
-    const int s = lane / K, c = lane - s * K;
+    const int K = a.K, L = (K + VEC - 1) / VEC, NS = 64 / L;
+    const int s = lane / L, cl = lane - s * L;
+    const int c0 = cl * VEC < K - VEC ? cl * VEC : K - VEC, own = cl * VEC - c0;       // columns c0 + own .. c0 + VEC - 1 are this lane's
     const int64_t pid = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * NS + s;
-    const bool active = s < NS && pid < a.npieces;
-    const T *val = (const T *)a.val;
-    const T *U = (const T *)a.U;
-    const int64_t t0 = active ? a.piece_start[pid] : 0, t1 = active ? a.piece_start[pid + 1] : 0;
-    const int col = active ? a.piece_col[pid] : 0;
-    const bool head = active && ((pid == 0) || (a.piece_col[pid - 1] != col));
-    const bool more = active && a.piece_col[pid + 1] == col;
-    // the result element this piece adds into (a whole column in one piece) is fetched now: its trip to memory
-    // then overlaps the gathers below instead of following them
-    T *o = (T *)a.out + (int64_t)col * a.ldo + c;
-    const T oval = (head && !more) ? *o : T(0);
-    // Entries are fetched K at a time, one per lane of the group (one coalesced load of row positions and one
-    // of values instead of K broadcast loads each), and handed round the group by lane shuffles; the gathers
-    // of U, four in flight, are then the only loads in the loop.  The groups of a wave have different piece
-    // lengths, so the loops run to the longest and the shorter groups add zeros.
-    T a0 = 0, a1 = 0, a2 = 0, a3 = 0;
-    const int gbase = s * K;
-    const int len = (int)(t1 - t0);
-    if (K < 4) {
-        // Groups this narrow would fetch one to three entries per round of the exchange below, a chain of index ->
-        // gather round trips per entry.  Every lane of the group reads the entries itself instead (the same
-        // addresses across the group), eight in flight.
-        for (int b = 0; b < len; b += 8) {
-            int r[8];
-            T v[8], u[8];
+    if (s >= NS || pid >= a.npieces) return;
+    const T *val = (const T *)a.val, *U = (const T *)a.U + c0;
+    const int64_t t0 = a.piece_start[pid];
+    const int len = (int)(a.piece_start[pid + 1] - t0);
+    const int col = a.piece_col[pid];
+    const bool whole = a.piece_col[pid + 1] != col && (pid == 0 || a.piece_col[pid - 1] != col);
+    // the result elements this piece adds into (a whole column in one piece) are fetched now: their trip to memory then
+    // overlaps the gathers below instead of following them
+    T *o = (T *)a.out + (int64_t)col * a.ldo + c0;
+    pack ov;
 #pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                const bool have = b + k < len;
-                r[k] = have ? a.row[t0 + b + k] : -1;
-                v[k] = have ? val[t0 + b + k] : T(0);
-            }
+    for (int m = 0; m < VEC; ++m) ov.v[m] = T(0);
+    if (whole) ov = *(const pack *)o;
+    T acc[2][VEC];
 #pragma unroll
-            for (int k = 0; k < 8; ++k) u[k] = (r[k] >= 0) ? U[(int64_t)r[k] * a.KP + c] : T(0);
-            a0 += v[0] * u[0];
-            a1 += v[1] * u[1];
-            a2 += v[2] * u[2];
-            a3 += v[3] * u[3];
-            a0 += v[4] * u[4];
-            a1 += v[5] * u[5];
-            a2 += v[6] * u[6];
-            a3 += v[7] * u[7];
-        }
-        if (!active) return;
-        const T accn = (a0 + a1) + (a2 + a3);
-        if (head && !more) {
-            *o = (T)((double)oval + coef * (double)accn);
+    for (int m = 0; m < VEC; ++m) acc[0][m] = acc[1][m] = T(0);
+    // N entries from place b on; entries behind the piece's last are the first of the N with the value zero.  The loads may
+    // reach seven entries behind the list's end: its arrays are allocated with room for that (grow).
+    auto take = [&](auto n, int b) {
+        constexpr int N = decltype(n)::value;
+        int r[N];
+        T v[N];
+        pack u[N];
+        if constexpr (N == 1) {
+            r[0] = a.row[t0];
+            v[0] = val[t0];
         } else {
-            ((T *)a.piece_part)[pid * K + c] = accn;
-        }
-        return;
-    }
-    // Waves whose pieces all have at most four entries -- most of them, on text-like data, where most columns
-    // appear in a handful of the selected rows -- take them without the exchange: every lane of the group reads
-    // the (up to four) entries itself, all at once, and the gathers follow.
-    if (!__any(len > 4)) {
-        int r[4];
-        T v[4], u[4];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const bool have = k < len;
-            r[k] = have ? a.row[t0 + k] : -1;
-            v[k] = have ? val[t0 + k] : T(0);
-        }
+            for (int k = 0; k < N; k += 4) {
+                const four rr = *(const four *)(a.row + t0 + b + k);
+                const fourv vv = *(const fourv *)(val + t0 + b + k);
 #pragma unroll
-        for (int k = 0; k < 4; ++k) u[k] = (r[k] >= 0) ? U[(int64_t)r[k] * a.KP + c] : T(0);
-        if (!active) return;
-        const T accs = (v[0] * u[0] + v[1] * u[1]) + (v[2] * u[2] + v[3] * u[3]);
-        if (head && !more) {
-            *o = (T)((double)oval + coef * (double)accs);
-        } else {
-            ((T *)a.piece_part)[pid * K + c] = accs;
-        }
-        return;
-    }
-    int maxlen = len;
-    for (int off = 32; off > 0; off >>= 1) maxlen = max(maxlen, __shfl_xor(maxlen, off));
-    for (int b = 0; b < maxlen; b += K) {
-        const int mine = b + c;
-        const bool have = mine < len;
-        const int rmine = have ? a.row[t0 + mine] : 0;
-        const T vmine = have ? val[t0 + mine] : T(0);
-        const int nb = min(K, maxlen - b);                       // uniform over the wave
-        for (int j = 0; j < nb; j += 4) {
-            int r[4];
-            T v[4], u[4];
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const int src = gbase + ((j + k < K) ? j + k : 0);
-                r[k] = __shfl(rmine, src);
-                v[k] = __shfl(vmine, src);
-                if (j + k >= nb || b + j + k >= len) v[k] = T(0), r[k] = r[0];
+                for (int i = 0; i < 4; ++i) r[k + i] = rr.r[i], v[k + i] = vv.v[i];
             }
+            if (!__all(b + N <= len)) {
 #pragma unroll
-            for (int k = 0; k < 4; ++k) u[k] = U[(int64_t)r[k] * a.KP + c];
-            a0 += v[0] * u[0];
-            a1 += v[1] * u[1];
-            a2 += v[2] * u[2];
-            a3 += v[3] * u[3];
+                for (int k = 1; k < N; ++k)
+                    if (b + k >= len) r[k] = r[0], v[k] = T(0);
+            }
         }
+#pragma unroll
+        for (int k = 0; k < N; ++k) u[k] = *(const pack *)(U + (int64_t)r[k] * a.KP);
+#pragma unroll
+        for (int k = 0; k < N; ++k)
+#pragma unroll
+            for (int m = 0; m < VEC; ++m) acc[k & 1][m] += v[k] * u[k].v[m];
+    };
+    // waves whose pieces all have one entry, or at most four: most of them on text-like data
+    if (__all(len == 1)) take(std::integral_constant<int, 1>{}, 0);
+    else if (__all(len <= 4)) take(std::integral_constant<int, 4>{}, 0);
+    else
+        for (int b = 0; b < len; b += 8) take(std::integral_constant<int, 8>{}, b);
+    T *dst = whole ? o : (T *)a.piece_part + pid * K + c0;
+    pack out;
+#pragma unroll
+    for (int m = 0; m < VEC; ++m) {
+        const T x = acc[0][m] + acc[1][m];
+        out.v[m] = whole ? (T)((double)ov.v[m] + coef * (double)x) : x;
     }
-    const T acc = (a0 + a1) + (a2 + a3);
-    if (!active) return;
-    if (head && !more) {
-        *o = (T)((double)oval + coef * (double)acc);
+    if (own == 0) {
+        *(pack *)dst = out;
     } else {
-        ((T *)a.piece_part)[pid * K + c] = acc;
+#pragma unroll
+        for (int m = 0; m < VEC; ++m)
+            if (m >= own) dst[m] = out.v[m];
     }
 }
 
@@ -1345,7 +1320,8 @@ hipError_t launch_csc_apply(int dtype, const CscView &v, int K, int KP, const vo
     const bool windows = K == 1 && v.win_pid && v.win_npieces == v.npieces && v.key;
     const unsigned wblocks = (unsigned)((((v.nnz + 63) / 64) + 3) / 4);
     const unsigned pblocks = (unsigned)(((((int64_t)v.npieces + 63) / 64) + 3) / 4);
-    const int NS = 64 / K;
+    const int vec = dtype == SSN_F32 ? piece_vec<float>(K) : piece_vec<double>(K);
+    const int NS = 64 / ((K + vec - 1) / vec);
     const int64_t waves = ((int64_t)v.npieces + NS - 1) / NS;
     const unsigned blocks = (unsigned)((waves + 3) / 4);
     // a column has at most one entry per selected row: views of few rows have short columns everywhere, and the
@@ -1363,7 +1339,9 @@ hipError_t launch_csc_apply(int dtype, const CscView &v, int K, int KP, const vo
             hipLaunchKernelGGL(csc1_combine_kernel<float>, dim3(pblocks), dim3(256), 0, st, a);
             return hipGetLastError();
         }
-        hipLaunchKernelGGL(csc_piece_kernel<float>, dim3(blocks), dim3(256), 0, st, a);
+        if (vec == 4) hipLaunchKernelGGL((csc_piece_kernel<float, 4>), dim3(blocks), dim3(256), 0, st, a);
+        else if (vec == 2) hipLaunchKernelGGL((csc_piece_kernel<float, 2>), dim3(blocks), dim3(256), 0, st, a);
+        else hipLaunchKernelGGL((csc_piece_kernel<float, 1>), dim3(blocks), dim3(256), 0, st, a);
         if (grouped) {
             hipLaunchKernelGGL(csc_run_kernel<float>, dim3(cblocks), dim3(256), 0, st, a);
             hipLaunchKernelGGL((csc_combine_kernel<float, true>), dim3(cblocks), dim3(256), 0, st, a);
@@ -1376,7 +1354,8 @@ hipError_t launch_csc_apply(int dtype, const CscView &v, int K, int KP, const vo
             hipLaunchKernelGGL(csc1_combine_kernel<double>, dim3(pblocks), dim3(256), 0, st, a);
             return hipGetLastError();
         }
-        hipLaunchKernelGGL(csc_piece_kernel<double>, dim3(blocks), dim3(256), 0, st, a);
+        if (vec == 2) hipLaunchKernelGGL((csc_piece_kernel<double, 2>), dim3(blocks), dim3(256), 0, st, a);
+        else hipLaunchKernelGGL((csc_piece_kernel<double, 1>), dim3(blocks), dim3(256), 0, st, a);
         if (grouped) {
             hipLaunchKernelGGL(csc_run_kernel<double>, dim3(cblocks), dim3(256), 0, st, a);
             hipLaunchKernelGGL((csc_combine_kernel<double, true>), dim3(cblocks), dim3(256), 0, st, a);
