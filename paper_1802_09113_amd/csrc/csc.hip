@@ -18,6 +18,7 @@
 // view from the whole matrix's and the product kernels are hand-written.
 #include "ssn_internal.h"
 #include "ssn_math.h"
+#include "csr_margin.h"
 
 #include <hipcub/hipcub.hpp>
 #include <type_traits>
@@ -916,13 +917,6 @@ struct CscApply {
 // (piece_col may be the pieces' columns or their positions among the distinct columns: equal columns have
 // equal positions, and the result row written is whichever of the two the caller's `out` is indexed by)
 
-// Weight columns per lane of csc_piece_kernel: 16 bytes of a row of U where the row is that long
-template <typename T> static int piece_vec(int K)
-{
-    const int most = 16 / (int)sizeof(T);
-    return K >= most ? most : K >= 2 ? 2 : 1;
-}
-
 // A lane group of a wave = ceil(K / VEC) lanes, each with VEC weight columns; one piece per group, 64 / that many groups.
 // (The last lane's columns are the last VEC ones: where VEC does not divide K it forms some that its neighbour has, and
 // leaves them to it.)  Every lane of a group reads the piece's entries itself, four per load -- the same addresses across
@@ -1320,7 +1314,7 @@ hipError_t launch_csc_apply(int dtype, const CscView &v, int K, int KP, const vo
     const bool windows = K == 1 && v.win_pid && v.win_npieces == v.npieces && v.key;
     const unsigned wblocks = (unsigned)((((v.nnz + 63) / 64) + 3) / 4);
     const unsigned pblocks = (unsigned)(((((int64_t)v.npieces + 63) / 64) + 3) / 4);
-    const int vec = dtype == SSN_F32 ? piece_vec<float>(K) : piece_vec<double>(K);
+    const int vec = dtype == SSN_F32 ? row_vec<float>(K) : row_vec<double>(K);
     const int NS = 64 / ((K + vec - 1) / vec);
     const int64_t waves = ((int64_t)v.npieces + NS - 1) / NS;
     const unsigned blocks = (unsigned)((waves + 3) / 4);

@@ -6,6 +6,7 @@
 // are contiguous (feature-major weights), so one stored entry fetches one contiguous K-vector.
 #include "ssn_internal.h"
 #include "ssn_math.h"
+#include "csr_margin.h"
 
 #include <limits>
 
@@ -99,7 +100,7 @@ __device__ __forceinline__ T csr_row_margin(const RowsArgs &a, int64_t b, int64_
 // LDS, and every wave adds the four in the same order; wave 0 does the row's stores and sums.  All waves of a
 // workgroup walk the same rows, so the barrier is reached by all; the partials alternate between two buffers, so one
 // barrier per row is enough.
-template <typename T, int MODE, bool SPLIT = false>
+template <typename T, int MODE, int VEC, bool SPLIT = false>
 __global__ __launch_bounds__(64 * ROWS_WAVES_PER_BLOCK) void csr_rows_kernel(RowsArgs a)
 {
     if (a.skip && *a.skip) return;
@@ -107,8 +108,12 @@ __global__ __launch_bounds__(64 * ROWS_WAVES_PER_BLOCK) void csr_rows_kernel(Row
     const int64_t nwaves = SPLIT ? (int64_t)gridDim.x : (int64_t)gridDim.x * ROWS_WAVES_PER_BLOCK;    // stride over the rows
     const int64_t wave = (int64_t)blockIdx.x * ROWS_WAVES_PER_BLOCK + wib;
     const int K = a.K;
-    const int NS = 64 / K;
+    const int NS = 64 / ((K + VEC - 1) / VEC);
     const bool cv = lane < K && (!SPLIT || wib == 0);            // lanes that hold (and store) a row's K values
+    auto margin = [&](const RowsArgs &r, int64_t rb, int64_t re) {
+        if constexpr (VEC == 1) return csr_row_margin<T>(r, rb, re, lane, K, NS);
+        else return csr_row_margin_vec<T, T, VEC>(r.colidx, (const T *)r.vals, (const T *)r.M, r.ldm, rb, re, lane, K);
+    };
     __shared__ T zs[SPLIT ? 2 * ROWS_WAVES_PER_BLOCK * 64 : 1];
     int par = 0;
     const T NEG = -std::numeric_limits<T>::infinity();
@@ -139,12 +144,12 @@ __global__ __launch_bounds__(64 * ROWS_WAVES_PER_BLOCK) void csr_rows_kernel(Row
             const int64_t per = ((e - b + ROWS_WAVES_PER_BLOCK * NS - 1) / (ROWS_WAVES_PER_BLOCK * NS)) * NS;
             const int64_t wb = (b + wib * per < e) ? b + wib * per : e, we = (wb + per < e) ? wb + per : e;
             T *zp = zs + par * (ROWS_WAVES_PER_BLOCK * 64);
-            zp[wib * 64 + lane] = csr_row_margin<T>(a, wb, we, lane, K, NS);
+            zp[wib * 64 + lane] = margin(a, wb, we);
             __syncthreads();
             z = (zp[lane] + zp[64 + lane]) + (zp[128 + lane] + zp[192 + lane]);
             par ^= 1;
         } else {
-            z = csr_row_margin<T>(a, b, e, lane, K, NS);
+            z = margin(a, b, e);
         }
         if constexpr (MODE == ROW_GRAD) {
             if (a.Zkeep && cv) ((T *)a.Zkeep)[sv * (2 * K) + lane] = z;
@@ -156,7 +161,7 @@ __global__ __launch_bounds__(64 * ROWS_WAVES_PER_BLOCK) void csr_rows_kernel(Row
             }
             RowsArgs b2 = a;
             b2.M = a.M2;
-            const T z2 = csr_row_margin<T>(b2, b, e, lane, K, NS);
+            const T z2 = margin(b2, b, e);
             if (cv) {
                 ((T *)a.UP)[sv * a.KP + lane] = z;
                 ((T *)a.UP)[sv * a.KP + K + lane] = z2;
@@ -409,6 +414,30 @@ template <typename T, int MODE> __global__ __launch_bounds__(256) void csr1_roww
     }
 }
 
+// more than one weight column, VEC of them to a lane
+template <typename T, int VEC> static hipError_t csr_rows_go(const RowsArgs &a, int blocks, hipStream_t st)
+{
+    dim3 grid(blocks), block(64 * ROWS_WAVES_PER_BLOCK);
+    if (a.csr_split) {                   // a workgroup per row (the launcher asks for it on the modes below only)
+        switch (a.mode) {
+        case ROW_PREP: hipLaunchKernelGGL((csr_rows_kernel<T, ROW_PREP, VEC, true>), grid, block, 0, st, a); break;
+        case ROW_APPLY: hipLaunchKernelGGL((csr_rows_kernel<T, ROW_APPLY, VEC, true>), grid, block, 0, st, a); break;
+        default: return hipErrorInvalidValue;
+        }
+        return hipGetLastError();
+    }
+    switch (a.mode) {
+    case ROW_OBJ: hipLaunchKernelGGL((csr_rows_kernel<T, ROW_OBJ, VEC>), grid, block, 0, st, a); break;
+    case ROW_GRAD: hipLaunchKernelGGL((csr_rows_kernel<T, ROW_GRAD, VEC>), grid, block, 0, st, a); break;
+    case ROW_PREP: hipLaunchKernelGGL((csr_rows_kernel<T, ROW_PREP, VEC>), grid, block, 0, st, a); break;
+    case ROW_APPLY: hipLaunchKernelGGL((csr_rows_kernel<T, ROW_APPLY, VEC>), grid, block, 0, st, a); break;
+    case ROW_PRED: hipLaunchKernelGGL((csr_rows_kernel<T, ROW_PRED, VEC>), grid, block, 0, st, a); break;
+    case ROW_MARGIN: hipLaunchKernelGGL((csr_rows_kernel<T, ROW_MARGIN, VEC>), grid, block, 0, st, a); break;
+    default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
 template <typename T> static hipError_t csr_rows_dispatch(const RowsArgs &a, int blocks, hipStream_t st)
 {
     dim3 grid(blocks), block(64 * ROWS_WAVES_PER_BLOCK);
@@ -429,26 +458,16 @@ template <typename T> static hipError_t csr_rows_dispatch(const RowsArgs &a, int
         case ROW_PREP: hipLaunchKernelGGL((csr_rows1_kernel<T, ROW_PREP>), grid, block, 0, st, a); return hipGetLastError();
         case ROW_APPLY: hipLaunchKernelGGL((csr_rows1_kernel<T, ROW_APPLY>), grid, block, 0, st, a); return hipGetLastError();
         case ROW_PRED: hipLaunchKernelGGL((csr_rows1_kernel<T, ROW_PRED>), grid, block, 0, st, a); return hipGetLastError();
-        default: break;                  // ROW_MARGIN: the general kernel
+        default: break;                  // ROW_MARGIN
         }
     }
-    if (a.csr_split) {                   // a workgroup per row (the launcher asks for it on the modes below only)
-        switch (a.mode) {
-        case ROW_PREP: hipLaunchKernelGGL((csr_rows_kernel<T, ROW_PREP, true>), grid, block, 0, st, a); return hipGetLastError();
-        case ROW_APPLY: hipLaunchKernelGGL((csr_rows_kernel<T, ROW_APPLY, true>), grid, block, 0, st, a); return hipGetLastError();
-        default: return hipErrorInvalidValue;
-        }
+    if (a.K == 1) {                      // ROW_MARGIN
+        if (a.csr_split || a.mode != ROW_MARGIN) return hipErrorInvalidValue;
+        hipLaunchKernelGGL((csr_rows_kernel<T, ROW_MARGIN, 1>), grid, block, 0, st, a);
+        return hipGetLastError();
     }
-    switch (a.mode) {
-    case ROW_OBJ: hipLaunchKernelGGL((csr_rows_kernel<T, ROW_OBJ>), grid, block, 0, st, a); break;
-    case ROW_GRAD: hipLaunchKernelGGL((csr_rows_kernel<T, ROW_GRAD>), grid, block, 0, st, a); break;
-    case ROW_PREP: hipLaunchKernelGGL((csr_rows_kernel<T, ROW_PREP>), grid, block, 0, st, a); break;
-    case ROW_APPLY: hipLaunchKernelGGL((csr_rows_kernel<T, ROW_APPLY>), grid, block, 0, st, a); break;
-    case ROW_PRED: hipLaunchKernelGGL((csr_rows_kernel<T, ROW_PRED>), grid, block, 0, st, a); break;
-    case ROW_MARGIN: hipLaunchKernelGGL((csr_rows_kernel<T, ROW_MARGIN>), grid, block, 0, st, a); break;
-    default: return hipErrorInvalidValue;
-    }
-    return hipGetLastError();
+    if (row_vec<T>(a.K) == 2) return csr_rows_go<T, 2>(a, blocks, st);
+    return csr_rows_go<T, 16 / (int)sizeof(T)>(a, blocks, st);
 }
 
 hipError_t launch_csr_rows(int dtype, const RowsArgs &a, int blocks, hipStream_t st)

@@ -19,6 +19,7 @@
 // the ratio of the two between 0.05 and 7.4, 1.03 in the geometric mean.
 #include "ssn_internal.h"
 #include "ssn_math.h"
+#include "csr_margin.h"
 
 namespace ssn {
 
@@ -243,36 +244,14 @@ hipError_t csc_gram(CscView *v, int dtype, hipStream_t st)
 // ---- Alg. 2 ------------------------------------------------------------------------------------------------
 // X_S g, and the start: r_0 = -g; a workgroup per row, its waves share the row's entries (a sample's rows are few)
 constexpr int START_WAVES = 8;
-template <typename T> __global__ __launch_bounds__(64 * START_WAVES) void dual_start_kernel(DualCg a)
+template <typename T, int VEC> __global__ __launch_bounds__(64 * START_WAVES) void dual_start_kernel(DualCg a)
 {
     __shared__ double zs[START_WAVES * 64];
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, K = a.K, NS = 64 / K;
-    const int s = lane / K, c = lane - s * K;
-    const T *vals = (const T *)a.vals, *G = (const T *)a.G;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, K = a.K, NS = 64 / ((K + VEC - 1) / VEC);
     const int64_t r = a.S[blockIdx.x], b = a.rowptr[r], e = a.rowptr[r + 1];
     const int64_t per = ((e - b + START_WAVES * NS - 1) / (START_WAVES * NS)) * NS;
     const int64_t wb = b + w * per < e ? b + w * per : e, we = wb + per < e ? wb + per : e;
-    double acc = 0.0;
-    if (s < NS) {
-        for (int64_t t = wb + s; t < we; t += 8 * NS) {
-            int64_t cc[8];
-            double x[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) cc[u] = (t + u * NS < we) ? (int64_t)a.colidx[t + u * NS] : (int64_t)-1;
-#pragma unroll
-            for (int u = 0; u < 8; ++u) x[u] = (t + u * NS < we) ? (double)vals[t + u * NS] : 0.0;
-#pragma unroll
-            for (int u = 0; u < 8; ++u) x[u] *= (cc[u] >= 0) ? (double)G[cc[u] * a.ldg + c] : 0.0;
-            acc += ((x[0] + x[1]) + (x[2] + x[3])) + ((x[4] + x[5]) + (x[6] + x[7]));
-        }
-    }
-    int top = 1;
-    while (top < NS) top <<= 1;
-    for (int h = top >> 1; h >= 1; h >>= 1) {
-        const double o = __shfl(acc, (lane + h * K) & 63);
-        if (s + h < NS) acc += o;
-    }
-    zs[w * 64 + lane] = acc;
+    zs[w * 64 + lane] = csr_row_margin_vec<T, double, VEC>(a.colidx, (const T *)a.vals, (const T *)a.G, a.ldg, wb, we, lane, K);
     __syncthreads();
     if ((int)threadIdx.x >= K) return;
     double z = 0.0;
@@ -560,7 +539,11 @@ template <typename T> static hipError_t dual_go(DualCg a, CgSlot *slots, int T_,
 {
     const int nb = dual_blocks(a.n, a.K);
     const dim3 grid((unsigned)(a.ld / 64), (unsigned)a.nks), block(256);
-    hipLaunchKernelGGL(dual_start_kernel<T>, dim3((unsigned)a.n), dim3(64 * START_WAVES), 0, st, a);
+    const int vec = row_vec<T>(a.K);
+    const dim3 rows((unsigned)a.n), waves(64 * START_WAVES);
+    if (vec == 1) hipLaunchKernelGGL((dual_start_kernel<T, 1>), rows, waves, 0, st, a);
+    else if (vec == 2) hipLaunchKernelGGL((dual_start_kernel<T, 2>), rows, waves, 0, st, a);
+    else hipLaunchKernelGGL((dual_start_kernel<T, 16 / (int)sizeof(T)>), rows, waves, 0, st, a);
     for (int k = 0; k < T_; ++k) {
         const CgSlot *prev = k ? slots + (k - 1) : slots + T_;       // the initial state waits in the last slot
         const int32_t *skip = &prev->done;
