@@ -541,23 +541,15 @@ __global__ __launch_bounds__(SPLIT ? 1024 : 64 * ROWS_WAVES_PER_BLOCK) void dens
         }
     }
 
-    // one partial per wave; SPLIT: the block's four partial slots are wave 0's sum and three zeros
+    // one partial per wave; SPLIT: one per workgroup, wave 0's
     if (SPLIT && wib != 0) return;
     if constexpr (MODE == ROW_OBJ || MODE == ROW_GRAD || MODE == ROW_APPLY) {
         if constexpr (MODE != ROW_APPLY) loss += log(lprod);
         for (int off = 32; off > 0; off >>= 1) loss += __shfl_xor(loss, off);
-        if constexpr (SPLIT) {
-            if (lane < ROWS_WAVES_PER_BLOCK) a.loss_part[wave * ROWS_WAVES_PER_BLOCK + lane] = (lane == 0) ? loss : 0.0;
-        } else {
-            if (lane == 0) a.loss_part[wave] = loss;
-        }
+        if (lane == 0) a.loss_part[wave] = loss;
     } else if constexpr (MODE == ROW_PRED) {
         for (int off = 32; off > 0; off >>= 1) hits += __shfl_xor(hits, off);
-        if constexpr (SPLIT) {
-            if (lane < ROWS_WAVES_PER_BLOCK) a.hit_part[wave * ROWS_WAVES_PER_BLOCK + lane] = (lane == 0) ? hits : 0;
-        } else {
-            if (lane == 0) a.hit_part[wave] = hits;
-        }
+        if (lane == 0) a.hit_part[wave] = hits;
     }
 }
 
@@ -882,20 +874,36 @@ void dense_rows_plan(int dtype, int64_t nrows, int64_t p, int K, int num_cus, in
     const int64_t nblk = (nrows + 15) / 16;
     const size_t es = dtype == SSN_F32 ? 4 : 8;
     const int nb = (K + 15) / 16;
-    *split_waves = 0;
-    *blocks = rows_grid_blocks(nrows, num_cus);
-    if (nblk <= (int64_t)num_cus * 2 && p >= 512) {
-        int w = p >= 2048 ? 16 : 8;
-        if ((size_t)w * nb * 256 * es > 32768) w = 8;
-        *split_waves = w;
-        *blocks = (int)(nblk < 1 ? 1 : nblk);
-    } else if (p >= 2048) {
-        // all rows of a wide matrix: a wave that streams a whole row block alone keeps too little in flight; four
-        // waves per block do better (50000 x 3072: fp64 objective 303 -> 280 us, fp32 180 -> 150 us; at 784
-        // features the plain form wins)
-        *split_waves = 4;
+    // A wave per row block puts as many waves on the chip as there are row blocks, each with a chain of loads as long as a
+    // row; a workgroup per row block shares the row out.  Its waves per block, by row blocks per compute unit (nblk /
+    // num_cus) and features, as measured on 1000 to 120000 rows of 64 to 2000 features with 2, 9 and 23 weight columns
+    // (objective call, us: wave per row block / this):
+    //   up to 2:     4 from 128 features, 8 from 256, 16 from 2048   fp64, K 23, 1000 x 331 22/13; fp32 13/10
+    //   up to 2.5:   4 from 128                                      fp64, K 9, 8300 x 1300 71/29; fp32, K 23, x 331 14/13
+    //   up to 4.25:  2 from 128, 4 from 256                          fp64, K 23, 16300 x 400 31/24; fp32, K 9, x 1900 56/32
+    //   up to 6:     2 from 128                                      fp64, K 9, 24000 x 784 54/36; fp32, K 23, x 256 16.1/15.2
+    //   up to 8:     2 from 512, one class tile                      fp64, K 9, 30000 x 512 38/32; K 23, x 1900 159/166 (not)
+    //   up to 10:    2 from 512, 4 from 768, one class tile; 4 from 512 (fp64) or 768 (fp32), two
+    //                                                                fp64, K 9, 33000 x 1300 133/87; fp32, K 23, 40000 x 784 46/44
+    //   beyond:      4 from 1280                                     fp64, K 9, 60000 x 1300 162/142, 50000 x 3072 303/280;
+    //                                                                fp32, K 9, 60000 x 784 44/47 (not)
+    const double per_cu = (double)nblk / (double)num_cus;
+    const bool f32 = dtype == SSN_F32;
+    int w = 0;
+    if (per_cu <= 2.0) w = p >= 2048 ? 16 : p >= 256 ? 8 : p >= 128 ? 4 : 0;
+    else if (p >= 1280 && per_cu > 8.0) w = 4;
+    else if (per_cu <= 2.5) w = p >= 128 ? 4 : 0;
+    else if (per_cu <= 4.25) w = p >= 256 ? 4 : p >= 128 ? 2 : 0;
+    else if (per_cu <= 6.0) w = p >= 128 ? 2 : 0;
+    else if (per_cu <= 8.0) w = nb == 1 && p >= 512 ? 2 : 0;
+    else if (per_cu <= 10.0) w = nb == 1 ? (p >= 768 ? 4 : p >= 512 ? 2 : 0) : (p >= (f32 ? 768 : 512) ? 4 : 0);
+    if ((size_t)w * nb * 256 * es > 32768) w = 8;
+    *split_waves = w;
+    if (w > 0) {
         const int64_t cap = (int64_t)num_cus * 16;           // beyond that the workgroups stride over the row blocks
-        *blocks = (int)(nblk < cap ? nblk : cap);
+        *blocks = (int)(nblk < 1 ? 1 : nblk < cap ? nblk : cap);
+    } else {
+        *blocks = rows_grid_blocks(nrows, num_cus);
     }
 }
 
