@@ -867,6 +867,195 @@ hipError_t launch_dense_zpart(int dtype, const RowsArgs &a, void *Zpart, int nsl
     return hipGetLastError();
 }
 
+// ---- long passes over wide matrices, one class tile --------------------------------------------------------
+// The rows kernels read all of W (221 KB in fp64 at p = 3072) next to every row block (393 KB) through the same path from
+// L2, which is what bounds them on wide matrices.  Here W stays in registers: a persistent workgroup of eight waves keeps
+// a slice of the features, each wave NL vector loads of them with the operands of W that go with them, and walks row
+// blocks.  A wave's next row block is requested load by load between the matrix instructions of the current one, so 12 KB
+// per wave are on the way at all times, also while the eight partial margins of a block are added through LDS (two buffers
+// in turn, one barrier per block; the two halves of the workgroup take turns at adding).  The slices' partial margins
+// Zpart[s][row][16] are added, and the per-row work done, by dense_wide_finish_kernel.  50000 x 3072, ten classes:
+// margins of the gradient pass 284 -> 244 + 12 us in fp64 (5.0 TB/s); in fp32 142 -> 113 us before the
+// finish.
+template <typename T, int NL>
+__global__ __launch_bounds__(512) void dense_wide_kernel(RowsArgs a, T *Zpart, int nslices)
+{
+    if (a.skip && *a.skip) return;
+    constexpr int VEC = 16 / (int)sizeof(T), STEP = 4 * VEC;
+    typedef typename V4<T>::type v4;
+    struct __attribute__((packed, aligned(sizeof(T)))) pack { T v[VEC]; };      // rows of any alignment
+    __shared__ T zs[2][8 * 256];
+    const int lane = threadIdx.x & 63, wib = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int q = lane & 15, g = lane >> 4;
+    const int sl = blockIdx.x % nslices;
+    const int64_t nwg = gridDim.x / nslices, zrows = (a.nrows + 15) / 16 * 16, nblk = zrows / 16;
+    // the wave's NL * STEP features; a window that would end behind the last feature is moved back, and the `skip` features
+    // it then has in common with the wave before it count as zeros
+    const int64_t nominal = ((int64_t)sl * 8 + wib) * (NL * STEP), start = nominal + NL * STEP <= a.p ? nominal : a.p - NL * STEP;
+    const int skip = (int)(nominal - start < NL * STEP ? nominal - start : NL * STEP) - VEC * g;
+    const int K = a.K, cols = a.M2 ? 2 * K : K;
+    T wv[NL][VEC];
+    {
+        const T *mcol = a.M2 && q >= K ? (const T *)a.M2 + (q < cols ? q - K : 0) : (const T *)a.M + (q < K ? q : K - 1);
+        mcol += (start + VEC * g) * a.ldm;
+#pragma unroll
+        for (int j = 0; j < NL; ++j)
+#pragma unroll
+            for (int m = 0; m < VEC; ++m) wv[j][m] = mcol[(int64_t)(j * STEP + m) * a.ldm];
+        // all of them are on their way before the first is looked at (left to itself the compiler puts each behind its guard)
+#pragma unroll
+        for (int j = 0; j < NL; ++j)
+#pragma unroll
+            for (int m = 0; m < VEC; ++m) asm volatile("" : "+v"(wv[j][m]));
+#pragma unroll
+        for (int j = 0; j < NL; ++j)
+#pragma unroll
+            for (int m = 0; m < VEC; ++m) wv[j][m] = (j * STEP + m >= skip && q < cols) ? wv[j][m] : T(0);
+    }
+    const T *X = (const T *)a.X + start + VEC * g;
+    auto row_of = [&](int64_t rb) -> const T * {
+        const int64_t si = rb * 16 + q;
+        return X + (si < a.nrows ? si : a.nrows - 1) * a.ldx;        // rows beyond the last: computed, never used
+    };
+    auto walk = [&](auto whole) {
+        auto multiply = [&](const pack &x, int j, v4 &z) {
+#pragma unroll
+            for (int m = 0; m < VEC; ++m) {
+                const T t = (decltype(whole)::value || j * STEP + m >= skip) ? x.v[m] : T(0);
+                z = mfma16(t, wv[j][m], z);
+            }
+        };
+        pack xv[NL];
+        int64_t rb = blockIdx.x / nslices;           // (strides; consecutive blocks per workgroup: fp32 113 -> 121 us)
+        if (rb >= nblk) return;
+        const T *x = row_of(rb);
+#pragma unroll
+        for (int j = 0; j < NL; ++j) xv[j] = *(const pack *)(x + j * STEP);
+        int par = 0;
+        auto leave = [&](const v4 &z, int64_t r) {
+#pragma unroll
+            for (int v = 0; v < 4; ++v) zs[par][(wib * 4 + v) * 64 + lane] = z[v];
+            __syncthreads();
+            if ((wib >> 2) == par) {
+                const int v = wib & 3;
+                T t = zs[par][v * 64 + lane];
+#pragma unroll
+                for (int w = 1; w < 8; ++w) t += zs[par][(w * 4 + v) * 64 + lane];
+                Zpart[((int64_t)sl * zrows + r * 16 + d_row<T>(g, v)) * 16 + q] = t;
+            }
+            par ^= 1;
+        };
+        for (; rb + nwg < nblk; rb += nwg) {
+            x = row_of(rb + nwg);
+            v4 z = v4{0, 0, 0, 0};
+#pragma unroll
+            for (int j = 0; j < NL; ++j) {
+                multiply(xv[j], j, z);
+                xv[j] = *(const pack *)(x + j * STEP);
+            }
+            leave(z, rb);
+        }
+        v4 z = v4{0, 0, 0, 0};
+#pragma unroll
+        for (int j = 0; j < NL; ++j) multiply(xv[j], j, z);
+        leave(z, rb);
+    };
+    if (nominal == start) walk(std::true_type{});
+    else walk(std::false_type{});
+}
+
+template <typename T, int MODE>
+__global__ __launch_bounds__(64 * ROWS_WAVES_PER_BLOCK) void dense_wide_finish_kernel(RowsArgs a, const T *Zpart, int nslices)
+{
+    if (a.skip && *a.skip) return;
+    typedef typename V4<T>::type v4;
+    const int lane = threadIdx.x & 63, q = lane & 15, g = lane >> 4;
+    const int64_t wave = (int64_t)blockIdx.x * ROWS_WAVES_PER_BLOCK + (threadIdx.x >> 6), nwaves = (int64_t)gridDim.x * ROWS_WAVES_PER_BLOCK;
+    const int64_t zrows = (a.nrows + 15) / 16 * 16;
+    double loss = 0.0, lprod = 1.0;
+    int hits = 0;
+    for (int64_t rb = wave; rb * 16 < a.nrows; rb += nwaves) {
+        v4 acc[1];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const T *z = Zpart + (rb * 16 + d_row<T>(g, v)) * 16 + q;
+            T t = z[0];
+            for (int s = 1; s < nslices; ++s) t += z[(int64_t)s * zrows * 16];      // slices in a fixed order
+            acc[0][v] = t;
+        }
+        row_epilogue<T, 1, MODE>(acc, a, rb, lane, loss, lprod, hits);
+    }
+    if constexpr (MODE == ROW_OBJ || MODE == ROW_GRAD) {
+        loss += log(lprod);
+        for (int off = 32; off > 0; off >>= 1) loss += __shfl_xor(loss, off);
+        if (lane == 0) a.loss_part[wave] = loss;
+    } else if constexpr (MODE == ROW_PRED) {
+        for (int off = 32; off > 0; off >>= 1) hits += __shfl_xor(hits, off);
+        if (lane == 0) a.hit_part[wave] = hits;
+    }
+}
+
+bool dense_wide_plan(int dtype, int64_t nrows, int64_t p, int K, int num_cus, DenseWide *w)
+{
+    if (K > 16) return false;
+    if (p < 1024) return false;
+    const int64_t per_load = dtype == SSN_F32 ? 8 * 16 : 8 * 8;     // features of a workgroup per load of its waves
+    w->nslices = (int)((p + 24 * per_load - 1) / (24 * per_load));
+    const int64_t each = (p + w->nslices - 1) / w->nslices;
+    const int64_t loads = (each + per_load - 1) / per_load;
+    w->loads = loads <= 8 ? 8 : (int)((loads + 1) / 2 * 2);
+    if (w->nslices > num_cus) return false;
+    // The rows kernels hold their own while the cache behind L2 (256 MB) feeds them; in fp64 their waves also divide some row
+    // counts below 28000 well.  Objective call, ten classes, rows kernels / this, us:
+    //   fp32  30000 x 1300 39.6/40.3, 30000 x 2048 52.9/53.2 (246 MB: not); 50000 x 1300 60.0/58.1, 40000 x 1700 62.8/55.3,
+    //         24000 x 3072 74.9/65.3, 50000 x 3072 146/129, 16400 x 5000 98.7/74.4; few rows: 12000 x 5000 52.1/53.4 (not)
+    //   fp64  24000 x 1536 63.3/63.9, 24000 x 2048 86.9/89.6, 24000 x 4000 158/159, 12000 x 8000 157/166 (not; 16400 x 2048
+    //         would be 78.7/58.3); 30000 x 1300 77.4/72.5, 50000 x 1536 142/131, 30000 x 2048 126/108, 50000 x 3072 263/241
+    if (nrows * p < (dtype == SSN_F32 ? 64000000 : 37500000) || nrows < (dtype == SSN_F32 ? 16384 : 28000)) return false;
+    const int64_t nblk = (nrows + 15) / 16;
+    int64_t per = num_cus / w->nslices;
+    if (per > nblk) per = nblk;
+    w->grid = (int)(per * w->nslices);
+    int64_t fb = (nblk + ROWS_WAVES_PER_BLOCK - 1) / ROWS_WAVES_PER_BLOCK;
+    if (fb > (int64_t)num_cus * 16) fb = (int64_t)num_cus * 16;
+    w->finish = (int)fb;
+    w->elems = (int64_t)w->nslices * nblk * 256;
+    return true;
+}
+
+template <typename T> static hipError_t wide_go(const RowsArgs &a, const DenseWide &w, T *Z, hipStream_t st)
+{
+    const dim3 grid((unsigned)w.grid), block(512);
+    switch (w.loads) {
+    case 8: hipLaunchKernelGGL((dense_wide_kernel<T, 8>), grid, block, 0, st, a, Z, w.nslices); break;
+    case 10: hipLaunchKernelGGL((dense_wide_kernel<T, 10>), grid, block, 0, st, a, Z, w.nslices); break;
+    case 12: hipLaunchKernelGGL((dense_wide_kernel<T, 12>), grid, block, 0, st, a, Z, w.nslices); break;
+    case 14: hipLaunchKernelGGL((dense_wide_kernel<T, 14>), grid, block, 0, st, a, Z, w.nslices); break;
+    case 16: hipLaunchKernelGGL((dense_wide_kernel<T, 16>), grid, block, 0, st, a, Z, w.nslices); break;
+    case 18: hipLaunchKernelGGL((dense_wide_kernel<T, 18>), grid, block, 0, st, a, Z, w.nslices); break;
+    case 20: hipLaunchKernelGGL((dense_wide_kernel<T, 20>), grid, block, 0, st, a, Z, w.nslices); break;
+    case 22: hipLaunchKernelGGL((dense_wide_kernel<T, 22>), grid, block, 0, st, a, Z, w.nslices); break;
+    default: hipLaunchKernelGGL((dense_wide_kernel<T, 24>), grid, block, 0, st, a, Z, w.nslices); break;
+    }
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    const dim3 fgrid((unsigned)w.finish), fblock(64 * ROWS_WAVES_PER_BLOCK);
+    switch (a.mode) {
+    case ROW_OBJ: hipLaunchKernelGGL((dense_wide_finish_kernel<T, ROW_OBJ>), fgrid, fblock, 0, st, a, Z, w.nslices); break;
+    case ROW_GRAD: hipLaunchKernelGGL((dense_wide_finish_kernel<T, ROW_GRAD>), fgrid, fblock, 0, st, a, Z, w.nslices); break;
+    case ROW_PRED: hipLaunchKernelGGL((dense_wide_finish_kernel<T, ROW_PRED>), fgrid, fblock, 0, st, a, Z, w.nslices); break;
+    case ROW_MARGIN: hipLaunchKernelGGL((dense_wide_finish_kernel<T, ROW_MARGIN>), fgrid, fblock, 0, st, a, Z, w.nslices); break;
+    default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
+hipError_t launch_dense_wide(int dtype, const RowsArgs &a, const DenseWide &w, void *Z, hipStream_t st)
+{
+    if (a.S || a.mode == ROW_PREP || a.mode == ROW_APPLY || (a.mode == ROW_MARGIN) != (a.M2 != nullptr)) return hipErrorInvalidValue;
+    return dtype == SSN_F32 ? wide_go<float>(a, w, (float *)Z, st) : wide_go<double>(a, w, (double *)Z, st);
+}
+
 // Workgroups and waves per workgroup of the wave-per-row-block kernel: *split_waves == 0 is the plain
 // form (4 waves, one row block each); otherwise each workgroup of *split_waves waves shares a row block.
 void dense_rows_plan(int dtype, int64_t nrows, int64_t p, int K, int num_cus, int *blocks, int *split_waves)

@@ -105,6 +105,8 @@ struct ssn_ctx {
     void *grad_next = nullptr;                 // gradient at the first line-search trial (look-ahead of ssn_solve)
     CgSlot *slots = nullptr;
     int slots_cap = 0;
+    void *zwide = nullptr;                     // dense, wide: partial margins of feature slices (dense_wide_kernel); zwide_elems
+    int64_t zwide_elems = 0;
     void *tail_row = nullptr;                  // dense one-pass path: zero-padded copy of row n-1 (tail_len elements)
     int tail_len = 0;
     int cg_gg_parts = 0;                       // dense CG: partials of g.g in red_a the first finalize forms slot 0 from (0: slot 0 is set)
@@ -315,6 +317,16 @@ int launch_rows(ssn_ctx *c, const RowsArgs &a, int *nparts)
         if (grid * 4 > c->wave_parts || grid > c->max_chunks) return fail(c, SSN_E_INVALID_ARG, "internal: partial overflow");
         SSN_HIP(c, launch_dense_fused(c->d.dtype, a, grid, c->st));
         if (nparts) *nparts = grid * 4;          // loss / hit partials; the X^T U partials number `grid`
+        return SSN_OK;
+    }
+    DenseWide wide{};
+    const bool full_margins = !a.S && a.mode != ROW_PREP && a.mode != ROW_APPLY;
+    if (c->zwide && full_margins &&
+        dense_wide_plan(c->d.dtype, a.nrows, c->d.p, a.mode == ROW_MARGIN ? 2 * c->K : c->K, c->num_cus, &wide) &&
+        wide.elems <= c->zwide_elems) {
+        if (wide.finish * ROWS_WAVES_PER_BLOCK > c->wave_parts) return fail(c, SSN_E_INVALID_ARG, "internal: wave partial overflow");
+        SSN_HIP(c, launch_dense_wide(c->d.dtype, a, wide, c->zwide, c->st));
+        if (nparts) *nparts = wide.finish * ROWS_WAVES_PER_BLOCK;
         return SSN_OK;
     }
     // dense: one wave per 16-row block; CSR: one wave per row
@@ -840,7 +852,7 @@ int ssn_destroy(ssn_ctx *c)
     if (c->st_aux) (void)hipStreamSynchronize(c->st_aux);      // a view of the next sample may still be in the making
     void *dev[] = {c->Zbuf, c->ls_dots, c->Ubuf, c->Pbuf, c->part, c->loss_part, c->hit_part, c->red_a, c->red_b, c->red_c, c->red_sq, c->scal_dev, c->int_dev,
                    c->cg_p, c->cg_r, c->cg_s, c->cg_hs, c->cg_parts, c->cg_pb, c->trial, c->grad, c->grad_next, c->dir, c->slots, c->trace_dev,
-                   c->tail_row, c->csr1_rwin, c->csr1_zrow, c->csr1_zhead, c->hess, c->dual};
+                   c->tail_row, c->csr1_rwin, c->csr1_zrow, c->csr1_zhead, c->hess, c->dual, c->zwide};
     for (void *p : dev)
         if (p) (void)hipFree(p);
     if (c->host_pin) (void)hipHostFree(c->host_pin);
@@ -954,6 +966,14 @@ int ssn_create(ssn_ctx **out, const ssn_desc *d)
             CREATE_HIP(hipMemsetAsync(c->tail_row, 0, (size_t)len * c->es, c->st));
             CREATE_HIP(hipMemcpyAsync(c->tail_row, (const char *)d->X + (size_t)(d->n - 1) * d->ldx * c->es, (size_t)d->p * c->es,
                                       hipMemcpyDeviceToDevice, c->st));
+        }
+        DenseWide wide{};
+        if (!c->fused && !c->binary && dense_wide_plan(d->dtype, d->n, d->p, K, c->num_cus, &wide)) {
+            if (hipMalloc(&c->zwide, (size_t)wide.elems * c->es) == hipSuccess) c->zwide_elems = wide.elems;
+            else {
+                c->zwide = nullptr;              // no room: the rows kernels do without
+                (void)hipGetLastError();
+            }
         }
         c->part_elems = (int64_t)c->max_chunks * d->p * K;
         CREATE_HIP(hipMalloc(&c->part, (size_t)c->part_elems * c->es));

@@ -128,6 +128,14 @@ hipError_t launch_dense_xtu(int dtype, const XtuArgs &a, hipStream_t st);
 // rwin[w] = the row that holds stored entry 64 w (w < ceil(nnz / 64)); rows may be empty
 hipError_t launch_csr_window_rows(const int32_t *rowptr, int64_t n, int64_t nnz, int32_t *rwin, hipStream_t st);
 hipError_t launch_dense_zpart(int dtype, const RowsArgs &a, void *Zpart, int nslices, int64_t fper, hipStream_t st);
+// long passes over wide matrices, at most 16 columns (K; two operands: 2 K): weights in registers (dense_wide_kernel)
+struct DenseWide {
+    int nslices, loads;      // feature slices; vector loads per wave and row block
+    int grid, finish;        // workgroups of the two kernels; 4 * finish loss / hit partials
+    int64_t elems;           // of the workspace Z
+};
+bool dense_wide_plan(int dtype, int64_t nrows, int64_t p, int K, int num_cus, DenseWide *w);
+hipError_t launch_dense_wide(int dtype, const RowsArgs &a, const DenseWide &w, void *Z, hipStream_t st);
 bool dense_fused_supported(int dtype, const RowsArgs &a);
 int dense_fused_grid(int dtype, const RowsArgs &a, int num_cus);
 int dense_fused_waves(int dtype, const RowsArgs &a);

@@ -25,6 +25,12 @@ CASES = [
     (32784, 513, 18, 520, None),          # fp64 four, fp32 a wave per row block
     (32784, 1280, 2, None, None),         # binary kernels next to it: one weight column
     (32784, 1281, 3, None, None),         # four
+    # weights in registers: from 64 million elements and 16384 rows (fp32), 37.5 million and 28000 (fp64) on
+    (28000, 1536, 17, None, 18),          # fp64: sixteen weight columns, one slice of whole windows
+    (28010, 1345, 9, 1346, None),         # fp64: the last window moved back; margins of two operands in one tile
+    (28001, 2049, 4, None, None),         # fp64: odd rows of any alignment, two slices
+    (16384, 4096, 3, None, None),         # fp32: two slices of whole windows
+    (28001, 2301, 3, 2303, 3),            # one slice in fp32, two in fp64, windows far back
 ]
 
 
@@ -51,6 +57,11 @@ def test_rows_shared_by_a_workgroup(n, p, C, ldx, ldw, dtype):
     clear = top[:, -1] - top[:, -2] > 1e-4                # elsewhere rounding may decide in fp32
     assert np.array_equal(pred.cpu().numpy()[clear], ref[clear])
     assert abs(acc - float(np.mean(ref == labels))) <= float(np.mean(~clear)) + 1e-12
+    if 2 * (C - 1) <= 16:                                 # a line search that backs off: the margins of both operands
+        Ph, Pd = pair.block(-40.0 * G_ref)
+        Gh, Gd = pair.block(G_ref)
+        ls, ref_ls = pair.gpu.ssn_linesearch(Wd, Pd, Gd, f, imax=6), pair.oracle.linesearch(Wh, Ph, Gh, f_ref, imax=6)
+        assert ls["alpha"] == ref_ls["alpha"] and rel_scalar(ls["f_new"], ref_ls["f_new"]) <= TOL[dtype]
     S = g.integers(0, n, min(n, 3000))
     Vh, Vd = pair.block(g.standard_normal((p, C - 1)))
     HV = pair.gpu.ssn_hessvec(Wd, pair.idx(S), Vd)
