@@ -19,6 +19,7 @@
 #include "ssn_internal.h"
 #include "ssn_math.h"
 #include "csr_margin.h"
+#include "csc_piece1.h"
 
 #include <hipcub/hipcub.hpp>
 #include <type_traits>
@@ -1049,7 +1050,7 @@ template <typename T> __global__ __launch_bounds__(256) void csc1_window_kernel(
     if (piece) {
         const T sum = (T)((b > 0) ? Pe - Pb : Pe);
         const bool head = ocol != pcol, more = ncol == ocol;
-        if (head && !more) {
+        if (a.out && head && !more) {                            // (no result block: every piece leaves its sum)
             T *o = (T *)a.out + (int64_t)ocol * a.ldo;
             *o = (T)((double)*o + coef * (double)sum);
         } else {
@@ -1075,53 +1076,11 @@ template <typename T> __global__ __launch_bounds__(256) void csc1_combine_kernel
     const int lane = threadIdx.x & 63;
     const int64_t base = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * 64;
     if (base >= a.npieces) return;                               // the whole wave
-    const int64_t pid = base + lane;
-    const bool have = pid < a.npieces;
     const T *pp = (const T *)a.piece_part;
-    const int col = have ? a.piece_col[pid] : -1;
-    const int prevc = (have && pid > 0) ? a.piece_col[pid - 1] : -2;
-    const int nextc = have ? a.piece_col[pid + 1] : -3;          // (sentinels -1 behind the last piece)
-    const bool head = have && col != prevc, more = have && nextc == col;
-    const bool multi = have && !(head && !more);                 // piece of a column of several pieces: it left a partial sum
-    T x = multi ? pp[pid] : T(0);
-    const int below = __shfl_up(col, 1);                         // (every lane takes part in the exchange)
-    const bool start = lane == 0 || col != below;
-    const unsigned long long starts = __ballot(start);
-    const unsigned long long above = (lane == 63) ? 0ull : ((starts >> (lane + 1)) << (lane + 1));
-    const int send = above ? (__ffsll((long long)above) - 2) : 63;
-    for (int d = 1; d < 64; d <<= 1) {
-        const T y = __shfl_down(x, d);
-        if (lane + d <= send) x += y;
-    }
-    // The column of the wave's last piece may run on behind it; this wave follows it if the column starts here
-    // (the wave where it starts does otherwise).
-    const int lastcol = __shfl(col, 63);
-    const int lastnext = __shfl(nextc, 63);
-    const int laststart = 63 - __clzll(starts);                  // first lane of the last segment (lane 0 always starts one)
-    const int lasthead = __shfl((int)head, laststart);
-    T csum = T(0);
-    if (lastcol >= 0 && lastnext == lastcol && lasthead) {       // uniform over the wave
-        // 256 pieces per step, all their loads requested together (a piece that is not this column's is read and
-        // dropped); the step's sum is the last lane's value of a scan over the lanes
-        for (int64_t j0 = base + 64;; j0 += 256) {
-            T y[4];
-            bool m[4];
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const int64_t j = j0 + 64 * k + lane, jc = j < a.npieces ? j : (int64_t)a.npieces - 1;
-                const int c = a.piece_col[jc];
-                const T pv = pp[jc];
-                m[k] = j < a.npieces && c == lastcol;
-                y[k] = m[k] ? pv : T(0);
-            }
-            const double t = ((double)y[0] + (double)y[1]) + ((double)y[2] + (double)y[3]);
-            csum += (T)__shfl(wave_inclusive_scan(t), 63);
-            if (!__all(m[3])) break;
-        }
-    }
-    if (start && head && more) {                                 // first piece of a column of several: the column's writer
-        const T total = (send == 63) ? x + csum : x;
-        T *o = (T *)a.out + (int64_t)col * a.ldo;
+    const Piece1<T> q = piece1_load<T, false>(a.piece_col, a.npieces, pp, base, lane);
+    const T total = piece1_column_sum(q, a.piece_col, a.npieces, pp, base, lane);
+    if (q.head && q.more) {                                      // first piece of a column of several: the column's writer
+        T *o = (T *)a.out + (int64_t)q.col * a.ldo;
         *o = (T)((double)*o + coef * (double)total);
     }
 }
@@ -1283,6 +1242,32 @@ template <typename T, bool GROUPED> __global__ __launch_bounds__(256) void csc_c
     }
 }
 
+bool csc_windows(const CscView &v, int K) { return K == 1 && v.win_pid && v.win_npieces == v.npieces && v.key && v.npieces > 0; }
+
+// One weight column: the sum of every piece of X_view^T U into v.piece_part; the columns are left to the caller's next launch.
+hipError_t launch_csc1_pieces(int dtype, const CscView &v, int KP, const void *U, const int32_t *skip, hipStream_t st)
+{
+    if (!csc_windows(v, 1)) return hipErrorInvalidValue;
+    CscApply a{};
+    a.row = v.row;
+    a.piece_start = v.piece_start;
+    a.piece_col = v.piece_col;
+    a.val = v.val;
+    a.npieces = v.npieces;
+    a.nnz = v.nnz;
+    a.K = 1;
+    a.KP = KP;
+    a.U = U;
+    a.piece_part = v.piece_part;
+    a.skip = skip;
+    a.key = v.key;
+    a.win_pid = v.win_pid;
+    const unsigned wblocks = (unsigned)((((v.nnz + 63) / 64) + 3) / 4);
+    if (dtype == SSN_F32) hipLaunchKernelGGL(csc1_window_kernel<float>, dim3(wblocks), dim3(256), 0, st, a);
+    else hipLaunchKernelGGL(csc1_window_kernel<double>, dim3(wblocks), dim3(256), 0, st, a);
+    return hipGetLastError();
+}
+
 // out += coef * X_view^T U  (out already holds whatever the product is added to: lambda * M, or the CG
 // residual).  K <= 64.
 hipError_t launch_csc_apply(int dtype, const CscView &v, int K, int KP, const void *U, double coef, void *out, int64_t ldo,
@@ -1311,7 +1296,7 @@ hipError_t launch_csc_apply(int dtype, const CscView &v, int K, int KP, const vo
     a.key = v.key;
     a.win_pid = v.win_pid;
     // one weight column: a lane per entry (csc1_window_kernel) where the view carries its window index
-    const bool windows = K == 1 && v.win_pid && v.win_npieces == v.npieces && v.key;
+    const bool windows = csc_windows(v, K);
     const unsigned wblocks = (unsigned)((((v.nnz + 63) / 64) + 3) / 4);
     const unsigned pblocks = (unsigned)(((((int64_t)v.npieces + 63) / 64) + 3) / 4);
     const int vec = dtype == SSN_F32 ? row_vec<float>(K) : row_vec<double>(K);

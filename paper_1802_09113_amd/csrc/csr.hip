@@ -277,7 +277,18 @@ template <typename T, int MODE> __global__ __launch_bounds__(64 * ROWS_WAVES_PER
         if (++cnt == 64) flush();
     }
     flush();
-    if constexpr (MODE == ROW_OBJ || MODE == ROW_GRAD || MODE == ROW_APPLY) {
+    if constexpr (MODE == ROW_APPLY) {                           // one per workgroup: every block of the CG step adds them all
+        __shared__ double sums[ROWS_WAVES_PER_BLOCK];
+        loss = wave_sum(loss);
+        if (lane == 0) sums[wib] = loss;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            double t = sums[0];
+#pragma unroll
+            for (int k = 1; k < ROWS_WAVES_PER_BLOCK; ++k) t += sums[k];
+            a.loss_part[blockIdx.x] = t;
+        }
+    } else if constexpr (MODE == ROW_OBJ || MODE == ROW_GRAD) {
         loss = wave_sum(loss);
         if (lane == 0) a.loss_part[wave] = loss;
     } else if constexpr (MODE == ROW_PRED) {

@@ -376,7 +376,8 @@ int launch_rows(ssn_ctx *c, const RowsArgs &a, int *nparts)
     else SSN_HIP(c, launch_csr_rows(c->d.dtype, a, blocks, c->st));
     // a partial per wave; dense, a workgroup per row block: one per workgroup (fewer to add: 3125 instead of 12500 at 50000
     // rows, the objective's sum 10.8 -> 8.9 us)
-    if (nparts) *nparts = split_waves > 0 ? blocks : blocks * ROWS_WAVES_PER_BLOCK;
+    const bool per_block = is_dense(c) ? split_waves > 0 : c->K == 1 && a.mode == ROW_APPLY;
+    if (nparts) *nparts = per_block ? blocks : blocks * ROWS_WAVES_PER_BLOCK;
     return SSN_OK;
 }
 
@@ -1175,11 +1176,11 @@ static bool dual_ok(const ssn_ctx *c, const CscView &v, double theta, int32_t T)
     // columns (direction with its preparation, nS rows; iteration on the sample's columns / in the row space, then the
     // direction of ten products):
     //   1355191 columns, 450 entries a row, K 19, fp64:  nS 100 40/10, 698/444; 1000 85/12, 1231/594; 2000 125/20, 1724/868
-    //   the same, K 1, fp32:                             nS 400 27/9,  447/325; 2000 29/13, 506/532 (refused)
+    //   the same, K 1, fp32:                             nS 400 16/9,  336/321; 1000 16/11, 357/360 (refused)
     //   20958 columns, 57 entries a row, K 4, fp64:      nS 1000 32/10, 469/293; 2000 35/14, 500/371
-    //   12500 columns, 400 entries a row, K 1, fp64:     nS 1000 24/11, 423/326; 2000 25/13, 460/532 (refused)
+    //   12500 columns, 400 entries a row, K 1, fp64:     nS 400 17/9,  343/317; 1000 16/11, 345/367 (refused)
     const double n = (double)v.nrows / 1000.0, nnz = (double)v.nnz, es = (double)c->es, K = (double)c->K;
-    const double iter = c->K == 1 ? 22.0 + nnz / 200e3 : 27.0 + (9.0 * (double)v.ncols + 2.0 * nnz) * K * es / 7e6;
+    const double iter = c->K == 1 ? 15.1 + nnz / 400e3 : 27.0 + (9.0 * (double)v.ncols + 2.0 * nnz) * K * es / 7e6;
     const double here = 9.5 + n * n * (1.0 + K / 16.0), gram = 45.0 + 100.0 * n * nnz / 1e6;
     return (double)T * (iter - here) * 0.9 > gram;
 }
@@ -1223,6 +1224,64 @@ static int dual_enqueue(ssn_ctx *c, const void *G, double theta, int32_t T, void
     if (n_slope) *n_slope = dual_blocks(v.nrows, c->K);
     SSN_HIP(c, launch_cg_expand_fill(c->d.dtype, c->d.p, c->K, G, c->d.ldw, P_out, c->d.ldw, c->slots + T, c->st));
     SSN_HIP(c, launch_csc_apply(c->d.dtype, v, c->K, c->KP, c->Ubuf, 1.0, P_out, c->d.ldw, nullptr, nullptr, c->st));
+    return SSN_OK;
+}
+
+// Alg. 2 on a CSR sample with one weight column, T > 0: three launches per product (csc1_cg_kernel).  v: the vectors on the
+// sample's columns; blocks: of the initialisation, which also walks all coordinates of g
+static int csc1_cg_enqueue(ssn_ctx *c, const CgVecs &v, double theta, int32_t T, void *P_out, int blocks, int *n_slope)
+{
+    const CscView &sv = c->csc_samp;
+    SSN_HIP(c, launch_csc1_cg_init(c->d.dtype, v, c->d.p, c->d.ldw, sv.cols, c->cg_hs, c->red_a, c->red_b, blocks, c->st));
+    const int nb = csc1_cg_blocks(sv.npieces);
+    for (int k = 0; k < T; ++k) {
+        // the theta test for r_k is made behind product k: the flag its launches look at is the one before it
+        const int32_t *skip = k > 0 ? (const int32_t *)((const char *)(c->slots + (k - 1)) + offsetof(CgSlot, done)) : nullptr;
+        RowsArgs a = rows_base(c);
+        a.S = nullptr;
+        a.nrows = c->nS;
+        a.M = v.r;
+        a.mode = ROW_APPLY;
+        a.Pin = c->Pbuf;
+        a.UP = c->Ubuf;
+        a.skip = skip;
+        a.rowptr = sv.off;
+        a.colidx = sv.ccol;
+        a.vals = sv.val_in;
+        a.p = v.p;
+        a.ldm = v.ld;
+        int nparts = 0;
+        SSN_TRY(launch_rows(c, a, &nparts));
+        SSN_HIP(c, launch_csc1_pieces(c->d.dtype, sv, c->KP, c->Ubuf, skip, c->st));
+        double *in = c->cg_parts + (size_t)((k + 1) & 1) * 2 * RED_MAX_PARTS;
+        double *out = c->cg_parts + (size_t)(k & 1) * 2 * RED_MAX_PARTS;
+        FinCgArgs g{};
+        g.prev = k > 0 ? c->slots + (k - 1) : nullptr;
+        g.cur = c->slots + k;
+        g.first = k == 0;
+        g.gg_part = c->red_a;
+        g.theta = theta;
+        g.pv = v.pv;
+        g.r = v.r;
+        g.s = v.s;
+        g.hs = c->cg_hs;
+        g.pbest = v.pbest;
+        g.zu_part = c->loss_part;
+        g.n_zu = nparts;
+        g.rr_in = in;
+        g.rhs_in = k == 0 ? c->red_b : in + RED_MAX_PARTS;
+        g.n_in = k == 0 ? blocks : nb;
+        g.rr_out = out;
+        g.rhs_out = out + RED_MAX_PARTS;
+        g.trace = c->trace_dev;
+        g.k = k;
+        SSN_HIP(c, launch_csc1_cg(c->d.dtype, sv, scale_sample(c), c->d.lambda, g, c->st));
+    }
+    const double *last = c->cg_parts + (size_t)((T - 1) & 1) * 2 * RED_MAX_PARTS;
+    SSN_HIP(c, launch_csc1_cg_tail(c->d.dtype, c->d.p, v.G, c->d.ldw, P_out, c->d.ldw, c->slots + (T - 1), c->slots + T, last, nb, theta,
+                                   c->d.lambda, c->trace_dev, T, c->st));
+    SSN_HIP(c, launch_cg_expand_rows(c->d.dtype, v, P_out, c->d.ldw, c->d.ldw, c->slots + T, sv.cols, n_slope ? c->red_a : nullptr,
+                                     n_slope, c->st));
     return SSN_OK;
 }
 
@@ -1272,7 +1331,12 @@ static int cg_enqueue(ssn_ctx *c, const void *G, double theta, int32_t T, void *
         SSN_TRY(vec_bytes_alloc(c, &c->cg_r));
         SSN_TRY(vec_bytes_alloc(c, &c->cg_s));
     }
-    if (is_dense(c) && !c->cg_hs) {
+    // One weight column: three launches per product (csc1_cg_kernel), up to three pieces per thread of its largest grid.
+    // Ten products with their preparation, six launches / three, us: 100 rows of 57 entries 351/271 (fp32), 5000 of 57
+    // 399/305, 5000 of 450 in 1355191 columns 659/608 (fp32) and 703/672 (fp64); 20000 of 450 (900 000 pieces) 1918/1957 (fp64)
+    const bool csc1 = !is_dense(c) && T > 0 && c->csc_samp.has_support && csc_windows(c->csc_samp, c->K) &&
+                      c->csc_samp.npieces <= 3 * RED_MAX_PARTS * VEC_BLOCK;
+    if ((is_dense(c) || csc1) && !c->cg_hs) {
         SSN_TRY(vec_bytes_alloc(c, &c->cg_hs));
         SSN_HIP(c, hipMalloc((void **)&c->cg_parts, sizeof(double) * 4 * RED_MAX_PARTS));
     }
@@ -1313,6 +1377,12 @@ static int cg_enqueue(ssn_ctx *c, const void *G, double theta, int32_t T, void *
             SSN_HIP(c, hipMalloc(&c->cg_pb, (size_t)(need + need / 8 + 64) * c->es));
             c->cg_pb_cap = need + need / 8 + 64;
         }
+        if (csc1) {
+            v.p = sv.ncols;
+            v.ld = 1;
+            v.pbest = c->cg_pb;
+            return csc1_cg_enqueue(c, v, theta, T, P_out, vb, n_slope);
+        }
         // g.g over all coordinates (red_b) next to g.g over the sample's columns (red_a)
         SSN_HIP(c, launch_dot_part(c->d.dtype, c->d.p, c->K, G, c->d.ldw, G, c->d.ldw, c->red_b, vb, nullptr, c->st));
         const int vb_full = vb;
@@ -1344,10 +1414,10 @@ static int cg_enqueue(ssn_ctx *c, const void *G, double theta, int32_t T, void *
         }
     }
     if (!is_dense(c)) {
-        // the best iterate may still live only in p (it is copied lazily); then all coordinates of the direction
-        if (T > 0) SSN_HIP(c, launch_cg_finish(c->d.dtype, v, c->slots + T, vb, c->st));
-        SSN_HIP(c, launch_cg_expand(c->d.dtype, c->d.p, c->K, G, c->d.ldw, P_out, c->d.ldw, c->slots + T, c->cg_pb,
-                                    c->csc_samp.cols, c->csc_samp.ncols, n_slope ? c->red_a : nullptr, n_slope, c->st));
+        // all coordinates of the direction; the best iterate may still live only in p (it is copied lazily)
+        SSN_HIP(c, launch_cg_expand_fill(c->d.dtype, c->d.p, c->K, G, c->d.ldw, P_out, c->d.ldw, c->slots + T, c->st));
+        SSN_HIP(c, launch_cg_expand_rows(c->d.dtype, v, P_out, c->d.ldw, c->d.ldw, c->slots + T, c->csc_samp.cols,
+                                         n_slope ? c->red_a : nullptr, n_slope, c->st));
     }
     return SSN_OK;
 }

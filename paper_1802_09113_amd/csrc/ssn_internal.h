@@ -294,6 +294,9 @@ void csc_free_scratch(CscView *v);
 // support_coords: `out` has one row per distinct column of the view (ncols rows) instead of one per column
 hipError_t launch_csc_apply(int dtype, const CscView &v, int K, int KP, const void *U, double coef, void *out, int64_t ldo,
                             const CgSlot *slot, const int32_t *skip, hipStream_t st, bool support_coords = false);
+// one weight column on a view with its window index: the sums of the pieces alone, into v.piece_part
+bool csc_windows(const CscView &v, int K);
+hipError_t launch_csc1_pieces(int dtype, const CscView &v, int KP, const void *U, const int32_t *skip, hipStream_t st);
 
 // ---- unit-column-norm preprocessing (preprocess.hip); synchronises the stream ------------------------
 hipError_t normalize_columns(int layout, int dtype, int64_t n, int64_t p, void *X, int64_t ldx, const int32_t *rowptr,
@@ -340,22 +343,19 @@ hipError_t launch_cg_init_state(const double *gg_part, int nparts, CgSlot *slot0
 // CG on the support of the sample: the vectors of v (ld = K, v.p = ncols rows) start from the rows cols[] of G
 hipError_t launch_cg_init_support(int dtype, const CgVecs &v, const void *G, int64_t ldg, const int32_t *cols,
                                   double *gg_part, double *ss_part, int blocks, hipStream_t st);
-// P_out = fin->pibest * G everywhere, then rows cols[] of it = the rows of pb (ncols x K, ld = K)
-// dot_part (nullable): partials of <pb, rows cols[] of G>, *n_dot of them (<= RED_MAX_PARTS)
-hipError_t launch_cg_expand(int dtype, int64_t p, int K, const void *G, int64_t ldg, void *P_out, int64_t ldp,
-                            const CgSlot *fin, const void *pb, const int32_t *cols, int64_t ncols, double *dot_part,
-                            int *n_dot, hipStream_t st);
+// rows cols[] of P_out = the rows of the best iterate (v.pbest, or v.pv where *fin says so; v.p = ncols rows)
+// dot_part (nullable): partials of <best, rows cols[] of v.G>, *n_dot of them (<= RED_MAX_PARTS)
+hipError_t launch_cg_expand_rows(int dtype, const CgVecs &v, void *P_out, int64_t ldp, int64_t ldg, const CgSlot *fin,
+                                 const int32_t *cols, double *dot_part, int *n_dot, hipStream_t st);
 // CSR path, lines 10-12 (the dense paths do all of lines 7-12 in finalize_cg_kernel).  ss_part (nullable): one partial
 // of s.s per block for the new direction; update_p: also p += cur->alpha * s, and p_best is then kept lazily
-// (CgSlot::best_cur): launch_cg_finish after the last product completes it; lambda: for the off-support scalars
+// (CgSlot::best_cur, for launch_cg_expand_rows); lambda: for the off-support scalars
 hipError_t launch_cg_step2(int dtype, const CgVecs &v, const CgSlot *cur, CgSlot *next, const double *rr_part,
                            int n_rr, double theta, double *trace_k, double *ss_part, bool update_p, int blocks,
                            hipStream_t st, double lambda = 0.0);
 // CSR path, lines 7-9 in pieces: cur->alpha from the partials of sum_i z_i . u_i and of s.s (one block); then the
 // sparse part of r -= alpha H s goes through the column-sorted gather (launch_csc_apply) and the rest,
 // r -= alpha lambda s with the partials of the new r.r, through launch_cg_r_update
-// p_best = p where the final state says the best iterate is still only in p
-hipError_t launch_cg_finish(int dtype, const CgVecs &v, const CgSlot *fin, int blocks, hipStream_t st);
 hipError_t launch_cg_alpha(CgSlot *cur, const double *zu_part, int n_zu, const double *ss_part, int n_ss, double scale,
                            double lambda, double *trace_k, hipStream_t st);
 hipError_t launch_cg_r_update(int dtype, const CgVecs &v, const CgSlot *cur, double lambda, double *rr_part, int blocks,
@@ -379,6 +379,15 @@ struct FinCgArgs {
     int32_t k;
 };
 hipError_t launch_finalize_cg(int dtype, const FinArgs &a, const FinCgArgs &g, int blocks, hipStream_t st);
+// CSR, one weight column: lines 7-12 on the sample's columns from the sums of their pieces (g.gg_part, g.rhs_in at k == 0:
+// n_in partials of g.g on those columns and over all coordinates; else csc1_cg_blocks(npieces) partials of each)
+int csc1_cg_blocks(int64_t npieces);
+hipError_t launch_csc1_cg_init(int dtype, const CgVecs &v, int64_t p, int64_t ldg, const int32_t *cols, void *hs, double *gg_part,
+                               double *full_part, int blocks, hipStream_t st);
+hipError_t launch_csc1_cg(int dtype, const CscView &v, double scale, double lambda, const FinCgArgs &g, hipStream_t st);
+// after the last product: the final state, P = pibest G on all coordinates (launch_cg_expand_rows follows)
+hipError_t launch_csc1_cg_tail(int dtype, int64_t p, const void *G, int64_t ldg, void *P, int64_t ldp, const CgSlot *prev, CgSlot *fin,
+                               const double *rr_in, int n_in, double theta, double lambda, double *trace, int k, hipStream_t st);
 // small blocks: lines 1-5 and the initial state in one launch (one block)
 hipError_t launch_cg_init_small(int dtype, const CgVecs &v, CgSlot *slot0, hipStream_t st);
 // inside ssn_solve: the tail, the slope <p_best, G>, the trial point W + p_best and the publication of F(x_k) (*f_dev),

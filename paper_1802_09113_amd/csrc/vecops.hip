@@ -6,6 +6,7 @@
 // the state slot k and block 0 writes slot k+1, so no slot is read and written by the same launch.
 #include "ssn_internal.h"
 #include "ssn_math.h"
+#include "csc_piece1.h"
 
 namespace ssn {
 
@@ -1328,18 +1329,21 @@ __global__ __launch_bounds__(VEC_BLOCK) void cg_expand_fill_kernel(int64_t p, in
         P[off_of(e, K, ldp)] = (T)(pibest * (double)G[off_of(e, K, ldg)]);
 }
 
-// rows cols[] of P = the rows of pb; dot_part (nullable): one partial per block of <pb, rows cols[] of G>
+// rows cols[] of P = the rows of the best iterate, which is in pb or still in pv; dot_part (nullable): one partial per block
+// of <best, rows cols[] of G>
 template <typename T>
-__global__ __launch_bounds__(VEC_BLOCK) void cg_expand_rows_kernel(int K, T *P, int64_t ldp, const T *pb, const int32_t *cols,
-                                                                    int64_t ncols, const T *G, int64_t ldg, double *dot_part)
+__global__ __launch_bounds__(VEC_BLOCK) void cg_expand_rows_kernel(int K, T *P, int64_t ldp, const T *pb, const T *pv,
+                                                                    const CgSlot *fin, const int32_t *cols, int64_t ncols, const T *G,
+                                                                    int64_t ldg, double *dot_part)
 {
+    const T *best = (fin->best_cur || fin->best_pending) ? pv : pb;
     const int64_t total = ncols * K;
     double local = 0.0;
     for (int64_t e = (int64_t)blockIdx.x * VEC_BLOCK + threadIdx.x; e < total; e += (int64_t)gridDim.x * VEC_BLOCK) {
         const int64_t t = e / K;
         const int c = (int)(e - t * K);
         const int64_t col = cols[t];
-        const T v = pb[e];
+        const T v = best[e];
         P[col * ldp + c] = v;
         if (dot_part) local += (double)v * (double)G[col * ldg + c];
     }
@@ -1362,20 +1366,17 @@ hipError_t launch_cg_expand_fill(int dtype, int64_t p, int K, const void *G, int
     return hipGetLastError();
 }
 
-hipError_t launch_cg_expand(int dtype, int64_t p, int K, const void *G, int64_t ldg, void *P_out, int64_t ldp,
-                            const CgSlot *fin, const void *pb, const int32_t *cols, int64_t ncols, double *dot_part,
-                            int *n_dot, hipStream_t st)
+hipError_t launch_cg_expand_rows(int dtype, const CgVecs &v, void *P_out, int64_t ldp, int64_t ldg, const CgSlot *fin,
+                                 const int32_t *cols, double *dot_part, int *n_dot, hipStream_t st)
 {
-    const int b2 = vec_blocks(ncols * K);                  // <= RED_MAX_PARTS: one partial per block
-    if (n_dot) *n_dot = b2;
-    const hipError_t e = launch_cg_expand_fill(dtype, p, K, G, ldg, P_out, ldp, fin, st);
-    if (e != hipSuccess) return e;
+    const int b = vec_blocks(v.p * v.K);                   // <= RED_MAX_PARTS: one partial per block
+    if (n_dot) *n_dot = b;
     if (dtype == SSN_F32)
-        hipLaunchKernelGGL(cg_expand_rows_kernel<float>, dim3(b2), dim3(VEC_BLOCK), 0, st, K, (float *)P_out, ldp,
-                           (const float *)pb, cols, ncols, (const float *)G, ldg, dot_part);
+        hipLaunchKernelGGL(cg_expand_rows_kernel<float>, dim3(b), dim3(VEC_BLOCK), 0, st, v.K, (float *)P_out, ldp,
+                           (const float *)v.pbest, (const float *)v.pv, fin, cols, v.p, (const float *)v.G, ldg, dot_part);
     else
-        hipLaunchKernelGGL(cg_expand_rows_kernel<double>, dim3(b2), dim3(VEC_BLOCK), 0, st, K, (double *)P_out, ldp,
-                           (const double *)pb, cols, ncols, (const double *)G, ldg, dot_part);
+        hipLaunchKernelGGL(cg_expand_rows_kernel<double>, dim3(b), dim3(VEC_BLOCK), 0, st, v.K, (double *)P_out, ldp,
+                           (const double *)v.pbest, (const double *)v.pv, fin, cols, v.p, (const double *)v.G, ldg, dot_part);
     return hipGetLastError();
 }
 
@@ -1492,25 +1493,6 @@ hipError_t launch_cg_step2(int dtype, const CgVecs &v, const CgSlot *cur, CgSlot
     return hipGetLastError();
 }
 
-template <typename T> __global__ __launch_bounds__(VEC_BLOCK) void cg_finish_kernel(CgVecs v, const CgSlot *fin)
-{
-    if (!fin->best_cur) return;
-    const int64_t total = v.p * v.K;
-    const T *pw = (const T *)v.pv;
-    T *pb = (T *)v.pbest;
-    for (int64_t e = (int64_t)blockIdx.x * VEC_BLOCK + threadIdx.x; e < total; e += (int64_t)gridDim.x * VEC_BLOCK) {
-        const int64_t o = off_of(e, v.K, v.ld);
-        pb[o] = pw[o];
-    }
-}
-
-hipError_t launch_cg_finish(int dtype, const CgVecs &v, const CgSlot *fin, int blocks, hipStream_t st)
-{
-    if (dtype == SSN_F32) hipLaunchKernelGGL(cg_finish_kernel<float>, dim3(blocks), dim3(VEC_BLOCK), 0, st, v, fin);
-    else hipLaunchKernelGGL(cg_finish_kernel<double>, dim3(blocks), dim3(VEC_BLOCK), 0, st, v, fin);
-    return hipGetLastError();
-}
-
 __global__ __launch_bounds__(VEC_BLOCK) void cg_alpha_kernel(CgSlot *cur, const double *zu_part, int n_zu,
                                                               const double *ss_part, int n_ss, double scale, double lambda,
                                                               double *trace_k)
@@ -1568,6 +1550,231 @@ hipError_t launch_cg_r_update(int dtype, const CgVecs &v, const CgSlot *cur, dou
         hipLaunchKernelGGL(cg_r_update_kernel<float>, dim3(blocks), dim3(VEC_BLOCK), 0, st, v, cur, lambda, rr_part);
     else
         hipLaunchKernelGGL(cg_r_update_kernel<double>, dim3(blocks), dim3(VEC_BLOCK), 0, st, v, cur, lambda, rr_part);
+    return hipGetLastError();
+}
+
+// ---- CSR with one weight column: CG in three launches per iteration ------------------------------------------
+// Margins of the sampled rows, sums of the columns' pieces, and one launch for all the rest.  The scheme is that of
+// finalize_cg_kernel -- the product is applied to the residual, H s kept as a vector, every scalar formed from partials the
+// launches before have left -- so no launch exists only to make alpha or to add r.r.  The vectors live on the sample's
+// columns; on all others r, s, p and H s are multiples of g (CgSlot::rho, sigma, pi and lambda sigma).  What bounds it is
+// launches: 2000 to 20000 elements per vector.  5000 rows of 57 entries, 20958 columns, fp32: an iteration of six launches
+// (products of s, alpha and r.r in kernels of their own) 24 us, this 15 us; ten products with their preparation 399 -> 305 us.
+
+// lines 1-5: the vectors on the sample's columns, partials of g.g there (gg_part) and over all coordinates (full_part)
+template <typename T>
+__global__ __launch_bounds__(VEC_BLOCK) void csc1_cg_init_kernel(CgVecs v, const T *G, int64_t p, int64_t ldg, const int32_t *cols,
+                                                                  T *hs, double *gg_part, double *full_part)
+{
+    const int64_t first = (int64_t)blockIdx.x * VEC_BLOCK + threadIdx.x, stride = (int64_t)gridDim.x * VEC_BLOCK;
+    T *pv = (T *)v.pv, *r = (T *)v.r, *s = (T *)v.s, *pb = (T *)v.pbest;
+    double local = 0.0, all = 0.0;
+    for (int64_t e = first; e < v.p; e += stride) {
+        const T gv = G[(int64_t)cols[e] * ldg];
+        pv[e] = T(0);
+        r[e] = -gv;
+        s[e] = T(0);
+        hs[e] = T(0);
+        pb[e] = -gv;
+        local += (double)gv * (double)gv;
+    }
+    for (int64_t j0 = first; j0 < p; j0 += 4 * stride) {
+        T t[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) t[u] = G[(j0 + u * stride < p ? j0 + u * stride : j0) * ldg];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) all += j0 + u * stride < p ? (double)t[u] * (double)t[u] : 0.0;
+    }
+    double a, b;
+    block_sum2(local, all, a, b);
+    if (threadIdx.x == 0) {
+        gg_part[blockIdx.x] = a;
+        full_part[blockIdx.x] = b;
+    }
+}
+
+// the state before product k from the one before product k - 1 and the sum of r_k.r_k over the sample's columns
+__device__ __forceinline__ CgSlot csc1_advance(const CgSlot &prev, double rr_cols, double theta, double lambda)
+{
+    const bool ended = prev.done || prev.brk;
+    const double rho = ended ? prev.rho : prev.rho - prev.alpha * lambda * prev.sigma;
+    const double pi = ended ? prev.pi : prev.pi + prev.alpha * prev.sigma;
+    CgSlot c = cg_advance(prev, rr_cols + rho * rho * prev.goff, theta);
+    c.goff = prev.goff;
+    c.rho = rho;
+    c.pi = pi;
+    c.sigma = prev.sigma;
+    c.pibest = c.best_pending ? pi : prev.pibest;
+    return c;
+}
+
+__device__ __forceinline__ void slot_store(CgSlot *w, const CgSlot &c)
+{
+    w->rr = c.rr;
+    w->rbest = c.rbest;
+    w->gnorm = c.gnorm;
+    w->done = c.done;
+    w->iters = c.iters;
+    w->flags = c.flags;
+    w->brk = c.brk;
+    w->alpha = c.alpha;
+    w->best_cur = 0;
+    w->best_pending = c.best_pending;
+    w->sHs = c.sHs;
+    w->goff = c.goff;
+    w->rho = c.rho;
+    w->sigma = c.sigma;
+    w->pi = c.pi;
+    w->pibest = c.pibest;
+}
+
+// lines 7-12: a lane per piece; the lane of a column's first piece has the column's element of the vectors
+template <typename T>
+__global__ __launch_bounds__(VEC_BLOCK) void csc1_cg_kernel(const int32_t *piece_col, int64_t npieces, const T *pp, double scale,
+                                                             double lambda, FinCgArgs g)
+{
+    const int lane = threadIdx.x & 63;
+    const int64_t stride = (int64_t)gridDim.x * VEC_BLOCK;
+    int64_t base = ((int64_t)blockIdx.x * VEC_BLOCK + threadIdx.x) / 64 * 64;
+    T *pv = (T *)g.pv, *r = (T *)g.r, *sv = (T *)g.s, *hsv = (T *)g.hs, *pb = (T *)g.pbest;
+    CgSlot prev{};
+    if (!g.first) prev = *g.prev;
+    // pieces, partials and the vectors' elements go out together
+    Piece1<T> q = piece1_load<T, true>(piece_col, npieces, pp, base, lane);
+    const double *rin = g.first ? g.gg_part : g.rr_in;       // first: g.g on the sample's columns, and over all coordinates
+    const double vz = thread_parts(g.zu_part, g.n_zu), vr = thread_parts(rin, g.n_in), vh = thread_parts(g.rhs_in, g.n_in);
+    T pe = q.head ? pv[q.col] : T(0), re = q.head ? r[q.col] : T(0), se = q.head ? sv[q.col] : T(0), he = q.head ? hsv[q.col] : T(0);
+    double zu, rr_sum, h_sum;
+    block_sum3(vz, vr, vh, zu, rr_sum, h_sum);
+    CgSlot c;
+    double beta = 0.0, sHs;
+    if (g.first) {
+        const double off = h_sum - rr_sum, gg = rr_sum + (off > 0.0 ? off : 0.0);
+        c.goff = off > 0.0 ? off : 0.0;
+        c.rho = c.sigma = c.pibest = -1.0;
+        c.pi = 0.0;
+        c.rr = gg;
+        c.rbest = c.gnorm = sqrt(gg);
+        c.done = gg == 0.0 ? 1 : 0;
+        c.iters = c.flags = c.best_cur = c.best_pending = 0;
+        sHs = scale * zu + lambda * c.rr;
+    } else {
+        c = csc1_advance(prev, rr_sum, g.theta, lambda);
+        beta = c.done ? 0.0 : c.rr / prev.rr;
+        if (!c.done) c.sigma = c.rho + beta * prev.sigma;
+        const double rhs = h_sum + c.rho * lambda * prev.sigma * c.goff;
+        sHs = scale * zu + lambda * c.rr + 2.0 * beta * rhs + beta * beta * prev.sHs;
+    }
+    const bool brk = !c.done && !(sHs > 0.0);                // not positive definite in floating point: stop, keep p_best
+    const double alpha = (c.done || brk) ? 0.0 : c.rr / sHs;
+    c.brk = brk ? 1 : 0;
+    c.alpha = alpha;
+    c.sHs = sHs;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        slot_store(g.cur, c);
+        if (!g.first && !prev.done && !prev.brk) g.trace[3 * (g.k - 1) + 1] = sqrt(c.rr);
+        if (!c.done) {
+            g.trace[3 * g.k] = alpha;
+            g.trace[3 * g.k + 2] = sHs;
+            if (brk) g.trace[3 * g.k + 1] = sqrt(c.rr);
+        }
+    }
+    const bool update = !c.done && !brk;
+    if (!c.best_pending && !update) return;
+    double lrr = 0.0, lrh = 0.0;
+    while (base < npieces) {                                 // uniform over the wave
+        const T sum = piece1_column_sum(q, piece_col, npieces, pp, base, lane);
+        if (q.head) {
+            if (c.best_pending) pb[q.col] = pe;              // line 10 for the iterate the last product left
+            if (update) {
+                const T hr = (T)(scale * (double)sum + lambda * (double)re);          // the element of H r, rounded as if stored
+                const T hs = (T)((double)hr + beta * (double)he);
+                const T sn = (T)((double)re + beta * (double)se);                     // line 12
+                const T rn = (T)((double)re - alpha * (double)hs);                    // line 9
+                hsv[q.col] = hs;
+                sv[q.col] = sn;
+                pv[q.col] = (T)((double)pe + alpha * (double)sn);                     // line 8
+                r[q.col] = rn;
+                lrr += (double)rn * (double)rn;
+                lrh += (double)rn * (double)hs;
+            }
+        }
+        base += stride;
+        if (base >= npieces) break;
+        q = piece1_load<T, true>(piece_col, npieces, pp, base, lane);
+        if (q.head) {
+            pe = pv[q.col];
+            re = r[q.col];
+            se = sv[q.col];
+            he = hsv[q.col];
+        }
+    }
+    if (!update) return;
+    double rr_o, rh_o;
+    block_sum2(lrr, lrh, rr_o, rh_o);
+    if (threadIdx.x == 0) {
+        g.rr_out[blockIdx.x] = rr_o;
+        g.rhs_out[blockIdx.x] = rh_o;
+    }
+}
+
+// lines 10-11 for r_T, the final state, and the direction outside the sample's columns: pibest * g
+template <typename T>
+__global__ __launch_bounds__(VEC_BLOCK) void csc1_cg_tail_kernel(int64_t p, const T *G, int64_t ldg, T *P, int64_t ldp,
+                                                                  const CgSlot *prev_p, CgSlot *fin, const double *rr_in, int n_in,
+                                                                  double theta, double lambda, double *trace, int k)
+{
+    const CgSlot prev = *prev_p;
+    CgSlot c = csc1_advance(prev, sum_parts(rr_in, n_in), theta, lambda);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        c.sHs = prev.sHs;
+        slot_store(fin, c);
+        if (!prev.done && !prev.brk) trace[3 * (k - 1) + 1] = sqrt(c.rr);
+    }
+    for (int64_t j = (int64_t)blockIdx.x * VEC_BLOCK + threadIdx.x; j < p; j += (int64_t)gridDim.x * VEC_BLOCK)
+        P[j * ldp] = (T)(c.pibest * (double)G[j * ldg]);
+}
+
+int csc1_cg_blocks(int64_t npieces)
+{
+    const int64_t b = (npieces + VEC_BLOCK - 1) / VEC_BLOCK;
+    return (int)(b > RED_MAX_PARTS ? RED_MAX_PARTS : b < 1 ? 1 : b);
+}
+
+hipError_t launch_csc1_cg_init(int dtype, const CgVecs &v, int64_t p, int64_t ldg, const int32_t *cols, void *hs, double *gg_part,
+                               double *full_part, int blocks, hipStream_t st)
+{
+    if (dtype == SSN_F32)
+        hipLaunchKernelGGL(csc1_cg_init_kernel<float>, dim3(blocks), dim3(VEC_BLOCK), 0, st, v, (const float *)v.G, p, ldg, cols,
+                           (float *)hs, gg_part, full_part);
+    else
+        hipLaunchKernelGGL(csc1_cg_init_kernel<double>, dim3(blocks), dim3(VEC_BLOCK), 0, st, v, (const double *)v.G, p, ldg, cols,
+                           (double *)hs, gg_part, full_part);
+    return hipGetLastError();
+}
+
+hipError_t launch_csc1_cg(int dtype, const CscView &v, double scale, double lambda, const FinCgArgs &g, hipStream_t st)
+{
+    const int blocks = csc1_cg_blocks(v.npieces);
+    if (dtype == SSN_F32)
+        hipLaunchKernelGGL(csc1_cg_kernel<float>, dim3(blocks), dim3(VEC_BLOCK), 0, st, v.piece_cpos, (int64_t)v.npieces,
+                           (const float *)v.piece_part, scale, lambda, g);
+    else
+        hipLaunchKernelGGL(csc1_cg_kernel<double>, dim3(blocks), dim3(VEC_BLOCK), 0, st, v.piece_cpos, (int64_t)v.npieces,
+                           (const double *)v.piece_part, scale, lambda, g);
+    return hipGetLastError();
+}
+
+hipError_t launch_csc1_cg_tail(int dtype, int64_t p, const void *G, int64_t ldg, void *P, int64_t ldp, const CgSlot *prev, CgSlot *fin,
+                               const double *rr_in, int n_in, double theta, double lambda, double *trace, int k, hipStream_t st)
+{
+    const int blocks = vec_blocks(p);
+    if (dtype == SSN_F32)
+        hipLaunchKernelGGL(csc1_cg_tail_kernel<float>, dim3(blocks), dim3(VEC_BLOCK), 0, st, p, (const float *)G, ldg, (float *)P, ldp,
+                           prev, fin, rr_in, n_in, theta, lambda, trace, k);
+    else
+        hipLaunchKernelGGL(csc1_cg_tail_kernel<double>, dim3(blocks), dim3(VEC_BLOCK), 0, st, p, (const double *)G, ldg, (double *)P,
+                           ldp, prev, fin, rr_in, n_in, theta, lambda, trace, k);
     return hipGetLastError();
 }
 
