@@ -224,9 +224,12 @@ template <typename T, int EL> __global__ __launch_bounds__(VEC_BLOCK) void final
     }
 }
 
-// elements per block: wide rows of partials are read in long contiguous runs, small ones use more
-// chunk lanes per element
-static int finalize_el(int64_t total) { return total >= 32768 ? 32 : (total >= 2048 ? 16 : 4); }
+// Elements per block.  Small totals need the chunk lanes; from 8192 on it pays to have fewer blocks, because in CG every one
+// of them first adds up all partials the launch before has left, one per block: about 256 of them, and no second group in a
+// block (the grid ends at RED_MAX_PARTS).  Directions of twenty products, 16 / 32 elements, us: 9000 fp32 416/377, 13500 fp64
+// 462/422, but an iteration of the solver at 7056 fp64 916/922 (not); 32 / 64: 18000 fp64 438/424, 27648 fp32 568/539,
+// 29900 fp32 617/562, 124000 fp64 1183/1109, but 9000 fp32 363/371 and 16000 (one column) fp64 623/627 (not).
+static int finalize_el(int64_t total) { return total > 16384 ? 64 : total >= 8192 ? 32 : total >= 2048 ? 16 : 4; }
 
 int finalize_blocks(int64_t p, int K)
 {
@@ -240,7 +243,8 @@ int finalize_blocks(int64_t p, int K)
 template <typename T> static void finalize_launch(const FinArgs &a, int blocks, hipStream_t st)
 {
     const int el = finalize_el(a.p * a.K);
-    if (el == 32) hipLaunchKernelGGL((finalize_kernel<T, 32>), dim3(blocks), dim3(VEC_BLOCK), 0, st, a);
+    if (el == 64) hipLaunchKernelGGL((finalize_kernel<T, 64>), dim3(blocks), dim3(VEC_BLOCK), 0, st, a);
+    else if (el == 32) hipLaunchKernelGGL((finalize_kernel<T, 32>), dim3(blocks), dim3(VEC_BLOCK), 0, st, a);
     else if (el == 16) hipLaunchKernelGGL((finalize_kernel<T, 16>), dim3(blocks), dim3(VEC_BLOCK), 0, st, a);
     else hipLaunchKernelGGL((finalize_kernel<T, 4>), dim3(blocks), dim3(VEC_BLOCK), 0, st, a);
 }
@@ -473,7 +477,8 @@ template <typename T, int EL> __global__ __launch_bounds__(VEC_BLOCK) void final
 template <typename T> static void finalize_cg_launch(const FinArgs &a, const FinCgArgs &g, int blocks, hipStream_t st)
 {
     const int el = finalize_el(a.p * a.K);
-    if (el == 32) hipLaunchKernelGGL((finalize_cg_kernel<T, 32>), dim3(blocks), dim3(VEC_BLOCK), 0, st, a, g);
+    if (el == 64) hipLaunchKernelGGL((finalize_cg_kernel<T, 64>), dim3(blocks), dim3(VEC_BLOCK), 0, st, a, g);
+    else if (el == 32) hipLaunchKernelGGL((finalize_cg_kernel<T, 32>), dim3(blocks), dim3(VEC_BLOCK), 0, st, a, g);
     else if (el == 16) hipLaunchKernelGGL((finalize_cg_kernel<T, 16>), dim3(blocks), dim3(VEC_BLOCK), 0, st, a, g);
     else hipLaunchKernelGGL((finalize_cg_kernel<T, 4>), dim3(blocks), dim3(VEC_BLOCK), 0, st, a, g);
 }
