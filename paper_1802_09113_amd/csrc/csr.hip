@@ -1,9 +1,9 @@
 // CSR kernels: row-per-wavefront SpMM with the per-row epilogue fused in (the transposed product is in
 // csc.hip).
 //
-// rows kernel: one wavefront owns one row at a time.  Lanes are split as (slot, class): NS = 64/K
-// stored entries are processed per step, lane (s,c) gathers M[col_s, c] -- the K values of one feature
-// are contiguous (feature-major weights), so one stored entry fetches one contiguous K-vector.
+// rows kernel: one wavefront owns one row at a time.  Lanes are split as (slot, group of weight columns): a lane
+// gathers up to 16 bytes of the K contiguous values of one feature (feature-major weights; csr_margin.h).  With one
+// weight column every lane is a slot.
 #include "ssn_internal.h"
 #include "ssn_math.h"
 #include "csr_margin.h"

@@ -377,8 +377,8 @@ __device__ __forceinline__ void row_epilogue(const typename V4<T>::type (&acc)[N
 // One wave per 16-row block; grid-stride over row blocks.  UP / Pin have ceil(nrows/16)*16 rows.
 //
 // SPLIT: for a few thousand rows there are too few row blocks to fill the chip with one wave each, and a
-// wave that walks all p features alone is a long chain of dependent loads.  Then a whole workgroup (8 or
-// 16 waves; 4 on full passes over matrices of 2048 features and more) shares one row block: the waves take
+// wave that walks all p features alone is a long chain of dependent loads.  Then a whole workgroup (2, 4, 8
+// or 16 waves, dense_rows_plan) shares one row block: the waves take
 // the feature groups in turn, their partial margins are added through LDS in wave order, and wave 0 does the
 // per-row work.
 //
