@@ -80,7 +80,8 @@ typedef struct {
     int64_t ldx;              /*       leading dimension in elements, >= p; storage of n*ldx     */
                               /*       elements, or (n-1)*ldx + p when ldx == p                  */
     const int32_t *rowptr;    /* [dev] CSR: n+1 offsets                                          */
-    const int32_t *colidx;    /* [dev] CSR: nnz column ids in [0,p), ascending inside a row      */
+    const int32_t *colidx;    /* [dev] CSR: nnz column ids in [0,p), ascending inside a row; an  */
+                              /*       id stored twice in a row stands for the sum of its values */
     const void *vals;         /* [dev] CSR: nnz values of type T                                 */
     int64_t nnz;              /*       CSR: number of stored entries (< 2^31)                    */
     const int32_t *labels;    /* [dev] n labels in [0,C)                                         */

@@ -49,7 +49,8 @@ int64_t gram_ld(int64_t rows) { return (rows + 63) / 64 * 64; }
 
 static int gram_freq_min(int64_t rows) { return rows > 512 ? (int)(rows / 8) : 64; }
 
-// xf[h][i] = the entry of frequent column h in sampled row i; rows of zeros behind them up to a multiple of sixteen
+// xf[h][i] = the entry of frequent column h in sampled row i (one at most: the caller serves no matrix whose rows store a
+// column twice); rows of zeros behind them up to a multiple of sixteen
 template <typename T>
 __global__ __launch_bounds__(256) void gram_dense_kernel(const int32_t *freq, const int32_t *nfreq_dev, const int32_t *cstart, const int32_t *row,
                                                          const T *val, double *xf, int ld)

@@ -55,6 +55,7 @@ struct ssn_ctx {
     bool next_ready = false;
     bool csc_full_built = false;
     int32_t csr_max_len = 0;      // longest row of the CSR matrix (read when the whole matrix's view is built)
+    bool csr_distinct = false;    // no row stores a column twice (every row's columns ascend strictly)
     // CSR with one weight column: what the lane-per-entry kernels of the full passes need (csr1_flat_kernel) -- the row
     // of every 64th stored entry, the rows' margins, the windows' leading partial sums
     int32_t *csr1_rwin = nullptr;
@@ -1003,6 +1004,9 @@ int ssn_create(ssn_ctx **out, const ssn_desc *d)
             CREATE_HIP(launch_check_range(d->colidx, d->nnz, 0, d->p, c->int_dev, c->st));
             if (read_int(c, c->int_dev, &bad) != SSN_OK) return bail(SSN_E_HIP);
             if (bad) return bail(SSN_E_BAD_INDEX);
+            CREATE_HIP(launch_check_ascending(d->rowptr, d->colidx, d->n, c->int_dev, c->st));
+            if (read_int(c, c->int_dev, &bad) != SSN_OK) return bail(SSN_E_HIP);
+            c->csr_distinct = bad == 0;
         }
         if (c->K == 1 && d->nnz > 0) {
             const int64_t nwin = (d->nnz + 63) / 64;
@@ -1170,6 +1174,9 @@ static int ensure_slots(ssn_ctx *c, int32_t T)
 // asked to fall so far that the part of g the sampled rows span cancels in r.r (1e-16 g.g beside theta^2 g.g).
 static bool dual_ok(const ssn_ctx *c, const CscView &v, double theta, int32_t T)
 {
+    // A column stored twice in a row would be one value of two in the Gram matrix's dense columns, and its products would be
+    // added in no fixed order: such matrices keep the vectors on the sample's columns, where entries are only ever summed.
+    if (!c->csr_distinct) return false;
     if (!(theta >= 1e-5) || v.nnz < 1 || !v.has_support || v.nrows > GRAM_ROWS_MAX) return false;
     if (dual_blocks(v.nrows, c->K) > RED_MAX_PARTS) return false;
     // Where the line lies: the Gram matrix against what T iterations save, in us as measured on text-like and evenly spread

@@ -216,6 +216,7 @@ constexpr int CHECK_POST_MAX = 65536;
 hipError_t launch_check_range_post(const int32_t *v, int count, int64_t lo, int64_t hi, double *out_host,
                                    unsigned long long *ticket_host, unsigned long long ticket, hipStream_t st);
 hipError_t launch_check_rowptr(const int32_t *rowptr, int64_t n, int64_t nnz, int32_t *bad, hipStream_t st);
+hipError_t launch_check_ascending(const int32_t *rowptr, const int32_t *colidx, int64_t n, int32_t *bad, hipStream_t st);
 
 constexpr int GRAM_ROWS_MAX = 2048;      // the most rows of a sample whose Gram matrix is formed
 

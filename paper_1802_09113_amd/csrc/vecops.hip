@@ -1168,6 +1168,25 @@ hipError_t launch_check_rowptr(const int32_t *rowptr, int64_t n, int64_t nnz, in
     return hipGetLastError();
 }
 
+// entries whose column is not beyond the one before it in their row; sixteen lanes to a row
+__global__ __launch_bounds__(VEC_BLOCK) void check_ascending_kernel(const int32_t *rowptr, const int32_t *colidx, int64_t n, int32_t *bad)
+{
+    int local = 0;
+    for (int64_t i = ((int64_t)blockIdx.x * VEC_BLOCK + threadIdx.x) / 16; i < n; i += (int64_t)gridDim.x * (VEC_BLOCK / 16)) {
+        const int64_t e = rowptr[i + 1];
+        for (int64_t t = (int64_t)rowptr[i] + 1 + (threadIdx.x & 15); t < e; t += 16) local += colidx[t] <= colidx[t - 1];
+    }
+    if (local) atomicAdd(bad, local);
+}
+
+hipError_t launch_check_ascending(const int32_t *rowptr, const int32_t *colidx, int64_t n, int32_t *bad, hipStream_t st)
+{
+    hipLaunchKernelGGL(zero_int_kernel, dim3(1), dim3(1), 0, st, bad);
+    const int64_t blocks = (n + VEC_BLOCK / 16 - 1) / (VEC_BLOCK / 16);
+    hipLaunchKernelGGL(check_ascending_kernel, dim3((unsigned)(blocks < 8192 ? blocks : 8192)), dim3(VEC_BLOCK), 0, st, rowptr, colidx, n, bad);
+    return hipGetLastError();
+}
+
 // ---- Alg. 2 on the device -------------------------------------------------------------------
 // lines 1-5: p = 0, r = -g, s = r, p_best = s; partials of g.g
 template <typename T>
