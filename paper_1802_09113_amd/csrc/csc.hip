@@ -155,6 +155,10 @@ static int grid_for(int64_t n)
         if (e_ != hipSuccess) return e_;                \
     } while (0)
 
+// Entries csc_piece_kernel may read behind the last one of the sorted list (row, val): part of what is asked for, as a view
+// that is built again gets by with the capacity it has
+constexpr int64_t ENTRY_ROOM = 7;
+
 static hipError_t grow(void **ptr, int64_t *cap, int64_t need, size_t elem)
 {
     if (*cap >= need) return hipSuccess;
@@ -238,8 +242,8 @@ hipError_t csc_build(CscView *v, int dtype, const int32_t *rowptr, const int32_t
 
     // 2. expand (column, position, sample row, value), sort by column (stable: rows stay in sample order)
     CSC_HIP(grow((void **)&v->key, &v->cap, nnz, sizeof(int32_t)));
-    CSC_HIP(grow((void **)&v->row, &v->cap_row, nnz, sizeof(int32_t)));
-    CSC_HIP(grow(&v->val, &v->cap_val, nnz, es));
+    CSC_HIP(grow((void **)&v->row, &v->cap_row, nnz + ENTRY_ROOM, sizeof(int32_t)));
+    CSC_HIP(grow(&v->val, &v->cap_val, nnz + ENTRY_ROOM, es));
     {
         int64_t c0 = v->cap_in, c1 = v->cap_in, c2 = v->cap_in, c3 = v->cap_in, c4 = v->cap_valin;
         CSC_HIP(grow((void **)&v->key_in, &c0, nnz, sizeof(int32_t)));
@@ -824,8 +828,8 @@ hipError_t csc_build_filtered(CscView *v, const CscView &full, int dtype, const 
     CSC_HIP(grow((void **)&v->toff, &v->cap_toff, 4 * area, sizeof(int32_t)));        // four scratch areas of the prefix sums
     CSC_HIP(grow((void **)&v->ftoff, &v->cap_ftoff, ftiles + 2, sizeof(int32_t)));
     CSC_HIP(grow((void **)&v->key, &v->cap, bound, sizeof(int32_t)));
-    CSC_HIP(grow((void **)&v->row, &v->cap_row, bound, sizeof(int32_t)));
-    CSC_HIP(grow(&v->val, &v->cap_val, bound, es));
+    CSC_HIP(grow((void **)&v->row, &v->cap_row, bound + ENTRY_ROOM, sizeof(int32_t)));
+    CSC_HIP(grow(&v->val, &v->cap_val, bound + ENTRY_ROOM, es));
     CSC_HIP(grow((void **)&v->piece_start, &v->cap_piece, bound + 1, sizeof(int32_t)));
     CSC_HIP(grow((void **)&v->piece_col, &v->cap_pcol, bound + 4, sizeof(int32_t)));
     // every piece may leave a partial sum and every run of pieces another
@@ -958,7 +962,7 @@ template <typename T, int VEC> __global__ __launch_bounds__(256) void csc_piece_
 #pragma unroll
     for (int m = 0; m < VEC; ++m) acc[0][m] = acc[1][m] = T(0);
     // N entries from place b on; entries behind the piece's last are the first of the N with the value zero.  The loads may
-    // reach seven entries behind the list's end: its arrays are allocated with room for that (grow).
+    // reach ENTRY_ROOM entries behind the list's end, which its arrays have room for (checked at the launch).
     auto take = [&](auto n, int b) {
         constexpr int N = decltype(n)::value;
         int r[N];
@@ -1297,6 +1301,7 @@ hipError_t launch_csc_apply(int dtype, const CscView &v, int K, int KP, const vo
     a.win_pid = v.win_pid;
     // one weight column: a lane per entry (csc1_window_kernel) where the view carries its window index
     const bool windows = csc_windows(v, K);
+    if (!windows && (v.cap_row < v.nnz + ENTRY_ROOM || v.cap_val < v.nnz + ENTRY_ROOM)) return hipErrorInvalidValue;
     const unsigned wblocks = (unsigned)((((v.nnz + 63) / 64) + 3) / 4);
     const unsigned pblocks = (unsigned)(((((int64_t)v.npieces + 63) / 64) + 3) / 4);
     const int vec = dtype == SSN_F32 ? row_vec<float>(K) : row_vec<double>(K);
