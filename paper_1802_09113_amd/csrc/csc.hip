@@ -961,13 +961,15 @@ template <typename T, int VEC> __global__ __launch_bounds__(256) void csc_piece_
     T acc[2][VEC];
 #pragma unroll
     for (int m = 0; m < VEC; ++m) acc[0][m] = acc[1][m] = T(0);
-    // N entries from place b on; entries behind the piece's last are the first of the N with the value zero.  The loads may
-    // reach ENTRY_ROOM entries behind the list's end, which its arrays have room for (checked at the launch).
+    // N entries from place b on.  Entries behind the piece's last count as 0 * 0 -- not as 0 * U, which is no zero where U is
+    // infinite -- and their row is the first of the N.  The loads may reach ENTRY_ROOM entries behind the list's end, which its
+    // arrays have room for (checked at the launch).
     auto take = [&](auto n, int b) {
         constexpr int N = decltype(n)::value;
         int r[N];
         T v[N];
         pack u[N];
+        const bool part = N > 1 && !__all(b + N <= len);
         if constexpr (N == 1) {
             r[0] = a.row[t0];
             v[0] = val[t0];
@@ -979,7 +981,7 @@ template <typename T, int VEC> __global__ __launch_bounds__(256) void csc_piece_
 #pragma unroll
                 for (int i = 0; i < 4; ++i) r[k + i] = rr.r[i], v[k + i] = vv.v[i];
             }
-            if (!__all(b + N <= len)) {
+            if (part) {
 #pragma unroll
                 for (int k = 1; k < N; ++k)
                     if (b + k >= len) r[k] = r[0], v[k] = T(0);
@@ -987,6 +989,12 @@ template <typename T, int VEC> __global__ __launch_bounds__(256) void csc_piece_
         }
 #pragma unroll
         for (int k = 0; k < N; ++k) u[k] = *(const pack *)(U + (int64_t)r[k] * a.KP);
+        if (part) {
+#pragma unroll
+            for (int k = 1; k < N; ++k)
+#pragma unroll
+                for (int m = 0; m < VEC; ++m) u[k].v[m] = b + k < len ? u[k].v[m] : T(0);
+        }
 #pragma unroll
         for (int k = 0; k < N; ++k)
 #pragma unroll

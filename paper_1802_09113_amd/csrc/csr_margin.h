@@ -30,33 +30,36 @@ __device__ __forceinline__ A csr_row_margin_vec(const int32_t *colidx, const T *
     A acc[2][VEC];
 #pragma unroll
     for (int m = 0; m < VEC; ++m) acc[0][m] = acc[1][m] = A(0);
-    // N entries per slot from place t on; those behind the row's end are its last with the value zero
-    auto take = [&](auto n, int64_t t) {
+    // N entries per slot from place t on.  ALL: every slot has its N; otherwise places behind the row's end read its last entry
+    // and count as 0 * 0 -- not as 0 * M, which is no zero where a weight is infinite.
+    auto take = [&](auto n, auto all, int64_t t) {
         constexpr int N = decltype(n)::value;
+        constexpr bool ALL = decltype(all)::value;
         int64_t cc[N];
         T vv[N];
         pack mm[N];
 #pragma unroll
-        for (int u = 0; u < N; ++u) cc[u] = colidx[t + u * NS < e ? t + u * NS : e - 1];
+        for (int u = 0; u < N; ++u) cc[u] = colidx[ALL || t + u * NS < e ? t + u * NS : e - 1];
 #pragma unroll
-        for (int u = 0; u < N; ++u) vv[u] = vals[t + u * NS < e ? t + u * NS : e - 1];
+        for (int u = 0; u < N; ++u) vv[u] = vals[ALL || t + u * NS < e ? t + u * NS : e - 1];
 #pragma unroll
         for (int u = 0; u < N; ++u) mm[u] = *(const pack *)(M + cc[u] * ldm);
 #pragma unroll
         for (int u = 0; u < N; ++u) {
-            const A x = t + u * NS < e ? (A)vv[u] : A(0);
+            const bool in = ALL || t + u * NS < e;
+            const A x = in ? (A)vv[u] : A(0);
 #pragma unroll
-            for (int m = 0; m < VEC; ++m) acc[u & 1][m] += x * (A)mm[u].v[m];
+            for (int m = 0; m < VEC; ++m) acc[u & 1][m] += x * (in ? (A)mm[u].v[m] : A(0));
         }
     };
     if (s < NS) {
-        for (int64_t t = b; t < e; t += 8 * NS) {               // (t and e are the same for the whole wave)
-            const int64_t left = e - t;
-            if (left > 4 * NS) take(std::integral_constant<int, 8>{}, t + s);
-            else if (left > 2 * NS) take(std::integral_constant<int, 4>{}, t + s);
-            else if (left > NS) take(std::integral_constant<int, 2>{}, t + s);
-            else take(std::integral_constant<int, 1>{}, t + s);
-        }
+        int64_t t = b;                                          // (t and e are the same for the whole wave)
+        for (; t + 8 * NS <= e; t += 8 * NS) take(std::integral_constant<int, 8>{}, std::true_type{}, t + s);
+        const int64_t left = e - t;
+        if (left > 4 * NS) take(std::integral_constant<int, 8>{}, std::false_type{}, t + s);
+        else if (left > 2 * NS) take(std::integral_constant<int, 4>{}, std::false_type{}, t + s);
+        else if (left > NS) take(std::integral_constant<int, 2>{}, std::false_type{}, t + s);
+        else if (left > 0) take(std::integral_constant<int, 1>{}, std::false_type{}, t + s);
     }
     int top = 1;
     while (top < NS) top <<= 1;
