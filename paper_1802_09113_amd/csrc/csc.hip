@@ -961,9 +961,10 @@ template <typename T, int VEC> __global__ __launch_bounds__(256) void csc_piece_
     T acc[2][VEC];
 #pragma unroll
     for (int m = 0; m < VEC; ++m) acc[0][m] = acc[1][m] = T(0);
-    // N entries from place b on.  Entries behind the piece's last count as 0 * 0 -- not as 0 * U, which is no zero where U is
-    // infinite -- and their row is the first of the N.  The loads may reach ENTRY_ROOM entries behind the list's end, which its
-    // arrays have room for (checked at the launch).
+    // N entries from place b on, added up in two sums of their own (a piece of 64 entries: eight additions of those, each of four
+    // products).  Entries behind the piece's last count as 0 * 0 -- not as 0 * U, which is no zero where U is infinite -- and
+    // their row is the first of the N.  The loads may reach ENTRY_ROOM entries behind the list's end, which its arrays have
+    // room for (checked at the launch).
     auto take = [&](auto n, int b) {
         constexpr int N = decltype(n)::value;
         int r[N];
@@ -996,9 +997,14 @@ template <typename T, int VEC> __global__ __launch_bounds__(256) void csc_piece_
                 for (int m = 0; m < VEC; ++m) u[k].v[m] = b + k < len ? u[k].v[m] : T(0);
         }
 #pragma unroll
-        for (int k = 0; k < N; ++k)
+        for (int m = 0; m < VEC; ++m) {
+            T t[2] = {v[0] * u[0].v[m], T(0)};
+            if constexpr (N > 1) t[1] = v[1] * u[1].v[m];
 #pragma unroll
-            for (int m = 0; m < VEC; ++m) acc[k & 1][m] += v[k] * u[k].v[m];
+            for (int k = 2; k < N; ++k) t[k & 1] += v[k] * u[k].v[m];
+            acc[0][m] += t[0];
+            if constexpr (N > 1) acc[1][m] += t[1];
+        }
     };
     // waves whose pieces all have one entry, or at most four: most of them on text-like data
     if (__all(len == 1)) take(std::integral_constant<int, 1>{}, 0);

@@ -30,8 +30,9 @@ __device__ __forceinline__ A csr_row_margin_vec(const int32_t *colidx, const T *
     A acc[2][VEC];
 #pragma unroll
     for (int m = 0; m < VEC; ++m) acc[0][m] = acc[1][m] = A(0);
-    // N entries per slot from place t on.  ALL: every slot has its N; otherwise places behind the row's end read its last entry
-    // and count as 0 * 0 -- not as 0 * M, which is no zero where a weight is infinite.
+    // N entries per slot from place t on, added up in two sums of their own (a row's chain of additions is one per round, and
+    // four within).  ALL: every slot has its N; otherwise places behind the row's end read its last entry and count as 0 * 0
+    // -- not as 0 * M, which is no zero where a weight is infinite.
     auto take = [&](auto n, auto all, int64_t t) {
         constexpr int N = decltype(n)::value;
         constexpr bool ALL = decltype(all)::value;
@@ -44,12 +45,21 @@ __device__ __forceinline__ A csr_row_margin_vec(const int32_t *colidx, const T *
         for (int u = 0; u < N; ++u) vv[u] = vals[ALL || t + u * NS < e ? t + u * NS : e - 1];
 #pragma unroll
         for (int u = 0; u < N; ++u) mm[u] = *(const pack *)(M + cc[u] * ldm);
+        A sum[2][VEC];
 #pragma unroll
         for (int u = 0; u < N; ++u) {
             const bool in = ALL || t + u * NS < e;
             const A x = in ? (A)vv[u] : A(0);
 #pragma unroll
-            for (int m = 0; m < VEC; ++m) acc[u & 1][m] += x * (in ? (A)mm[u].v[m] : A(0));
+            for (int m = 0; m < VEC; ++m) {
+                const A w = in ? (A)mm[u].v[m] : A(0);
+                sum[u & 1][m] = u < 2 ? x * w : sum[u & 1][m] + x * w;
+            }
+        }
+#pragma unroll
+        for (int m = 0; m < VEC; ++m) {
+            acc[0][m] += sum[0][m];
+            if constexpr (N > 1) acc[1][m] += sum[1][m];
         }
     };
     if (s < NS) {
