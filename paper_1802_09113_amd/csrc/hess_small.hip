@@ -272,14 +272,6 @@ __device__ __forceinline__ void hc_leave(double v, double *red)      // this wav
     v = wave_inclusive_scan(v);
     if ((threadIdx.x & 63) == 63) red[threadIdx.x >> 6] = v;
 }
-// 1 / a: hardware estimate and two Newton steps, about one ulp (a division is some 30 instructions of every wave)
-__device__ __forceinline__ double hc_rcp(double a)
-{
-    double x = __builtin_amdgcn_rcp(a);
-    x = fma(fma(-a, x, 1.0), x, x);
-    x = fma(fma(-a, x, 1.0), x, x);
-    return x;
-}
 
 __device__ __forceinline__ void hc_state(CgSlot *w, double rr, double rbest, double gnorm, int done, int iters, int flags, double sHs)
 {
@@ -303,13 +295,14 @@ __device__ __forceinline__ void hc_state(CgSlot *w, double rr, double rbest, dou
 // time, every strip of the thread uses the same eight, and leaves two partial sums per strip, one for each of the
 // classes: at (class, other class, chunk, row), so that the K * nc partials of an element are one stride apart.  Element e
 // is feature e % p of class e / p, so that neighbouring threads read neighbouring partials.  What bounds it is instruction
-// issue on one compute unit: hence the waves without elements skip the sums and scalars, quotients are estimates with
-// Newton steps, the tests compare squares, and the partials are added by all threads (46 -> 34 us for fp32, p 54, K 6).
+// issue on one compute unit: hence the waves without elements skip the sums and scalars, and the partials are added by all
+// threads.
 template <typename T, int UPT> __global__ __launch_bounds__(HC_THREADS) void hess_cg_kernel(HessCg a)
 {
     extern __shared__ __align__(16) unsigned char hess_lds[];
     __shared__ double red[2][HC_THREADS / 64], fold[HC_THREADS];
     __shared__ int ended;
+    __shared__ double norm0;                 // ||g|| for the final state (a register less in the loop)
     const int K = a.K, p = a.p, nc = a.nc, pl = a.pl;
     T *sl = (T *)hess_lds, *pt = sl + K * pl;
     const int tid = threadIdx.x;
@@ -357,11 +350,14 @@ template <typename T, int UPT> __global__ __launch_bounds__(HC_THREADS) void hes
     if (el) sl[ec * pl + ej] = se;
     if (ew) hc_leave((double)gv * (double)gv, red[0]);
     __syncthreads();
-    // the tests of lines 10-11 compare squares
-    double rr = hc_total(red[0]), rbest2 = rr, sHs = 0.0;
-    const double gg = rr, stop2 = a.theta * a.theta * gg;
+    double rr = hc_total(red[0]), sHs = 0.0;
+    double rbest = sqrt(rr);
+    const double stop_at = a.theta * rbest;
     int iters = 0, flags = 0;
-    if (tid == 0) ended = rr == 0.0 ? 1 : 0;
+    if (tid == 0) {
+        ended = rr == 0.0 ? 1 : 0;
+        norm0 = rbest;
+    }
     __syncthreads();
     while (!ended) {                         // the same in every thread: written behind a barrier, read in front of the next
         if (mine) {
@@ -421,7 +417,7 @@ template <typename T, int UPT> __global__ __launch_bounds__(HC_THREADS) void hes
             sHs = hc_total(red[0]);
             brk = !(sHs > 0.0);              // not positive definite in floating point: stop, keep p_best
             if (!brk) {
-                alpha = rr * hc_rcp(sHs);
+                alpha = rr / sHs;
                 pe = (T)((double)pe + alpha * (double)se);            // lines 8, 9
                 re = (T)((double)re - alpha * (double)hs);
                 hc_leave((double)re * (double)re, red[1]);
@@ -429,23 +425,23 @@ template <typename T, int UPT> __global__ __launch_bounds__(HC_THREADS) void hes
         }
         __syncthreads();
         if (ew) {
-            const double rrn = brk ? rr : hc_total(red[1]);
-            const bool stop = !brk && rrn <= stop2;
+            const double rrn = brk ? rr : hc_total(red[1]), rnorm = sqrt(rrn);
+            const bool stop = !brk && rnorm <= stop_at;              // line 11
             if (tid == 0) {
                 if (a.trace) {
                     a.trace[3 * iters] = alpha;
-                    a.trace[3 * iters + 1] = sqrt(rrn);
+                    a.trace[3 * iters + 1] = rnorm;
                     a.trace[3 * iters + 2] = sHs;
                 }
                 ended = (brk || stop || iters + 1 >= a.T) ? 1 : 0;
             }
             ++iters;
             flags |= (stop ? 1 : 0) | (brk ? 2 : 0);
-            if (!brk && rrn <= rbest2) {                              // line 10
+            if (!brk && rnorm <= rbest) {                             // line 10
                 pb = pe;
-                rbest2 = rrn;
+                rbest = rnorm;
             }
-            se = (T)((double)re + rrn * hc_rcp(rr) * (double)se);     // line 12
+            se = (T)((double)re + rrn / rr * (double)se);     // line 12
             rr = rrn;
             if (el) sl[ec * pl + ej] = se;
         }
@@ -460,13 +456,14 @@ template <typename T, int UPT> __global__ __launch_bounds__(HC_THREADS) void hes
         slope = hc_total(red[0]);
     }
     if (tid != 0) return;
-    const bool zero = gg == 0.0;
-    hc_state(a.fin, rr, sqrt(rbest2), sqrt(gg), zero || flags, iters, flags, sHs);
+    const double gnorm = norm0;
+    const bool zero = gnorm == 0.0;
+    hc_state(a.fin, rr, rbest, gnorm, zero || flags, iters, flags, sHs);
     if (!a.trial) return;
     *a.slope_dev = slope;
     a.host_out[0] = *a.f_dev;
     a.host_out[1] = slope;
-    hc_state((CgSlot *)(a.host_out + 2), rr, sqrt(rbest2), sqrt(gg), zero || flags, iters, flags, sHs);
+    hc_state((CgSlot *)(a.host_out + 2), rr, rbest, gnorm, zero || flags, iters, flags, sHs);
 }
 
 template <typename T, int NT> static hipError_t form_go(const HessForm &f, int blocks, hipStream_t st)

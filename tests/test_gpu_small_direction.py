@@ -81,3 +81,41 @@ def test_formed_hessian_and_an_indefinite_product(dtype):
     assert (out["iters"], out["flags"]) == (ref["iters"], ref["flags"]) == (1, 2)
     np.testing.assert_array_equal(pair.host(out["p"]), -Gh)
     pair.close()
+
+
+@pytest.mark.parametrize("dtype", [F64, F32], ids=["f64", "f32"])
+@pytest.mark.parametrize("theta", [-1.0, 0.0])
+def test_formed_hessian_and_a_tolerance_that_is_never_met(theta, dtype):
+    """||r|| <= theta ||g|| does not hold for a theta of zero or below while a residual is left: all T products are made."""
+    n, p, C, nS, T = 500, 40, 3, 200, 6
+    g = np.random.default_rng(5)
+    X = g.standard_normal((n, p)) / np.sqrt(p)
+    pair = Pair(dict(layout="dense", X=X, labels=g.integers(0, C, n).astype(np.int32), n=n, p=p, C=C, K=C - 1, lam=0.05), dtype)
+    Wh, Wd = pair.block(0.1 * g.standard_normal((p, C - 1)))
+    S = g.permutation(n)[:nS]
+    Gh, Gd = pair.block(pair.oracle.gradient(Wh)[0])
+    pair.gpu.ssn_hess_prepare(Wd, pair.idx(S))
+    ref, out = pair.oracle.cg(Wh, S, Gh, theta, T), pair.gpu.ssn_cg(Gd, theta, T)
+    torch.cuda.synchronize()
+    assert (out["iters"], out["flags"]) == (ref["iters"], ref["flags"]) == (T, 0)
+    assert rel_err(pair.host(out["p"]), ref["p"]) <= (1e-10 if dtype == F64 else 2e-3)
+    pair.close()
+
+
+def test_formed_hessian_and_products_below_the_normal_numbers():
+    """Data of 1e-78: s^T H s of about 1e-312 is a subnormal number with some eleven digits, whose reciprocal overflows; the steps
+    ||r||^2 / s^T H s are ordinary ones of 1e156.  Sums of fp64 products to 1e-12, then three iterations."""
+    n, p, C, nS = 300, 24, 3, 150
+    g = np.random.default_rng(6)
+    X = 1e-78 * g.standard_normal((n, p))
+    pair = Pair(dict(layout="dense", X=X, labels=g.integers(0, C, n).astype(np.int32), n=n, p=p, C=C, K=C - 1, lam=0.0), F64)
+    Wh, Wd = pair.block(np.zeros((p, C - 1)))
+    S = g.permutation(n)[:nS]
+    Gh, Gd = pair.block(pair.oracle.gradient(Wh)[0])
+    pair.gpu.ssn_hess_prepare(Wd, pair.idx(S))
+    ref, out = pair.oracle.cg(Wh, S, Gh, 1e-4, 3), pair.gpu.ssn_cg(Gd, 1e-4, 3)
+    torch.cuda.synchronize()
+    assert (out["iters"], out["flags"]) == (ref["iters"], ref["flags"]) == (3, 0)
+    np.testing.assert_allclose(out["alpha"], ref["alpha"], rtol=1e-7)
+    assert rel_err(pair.host(out["p"]) * 1e-78, ref["p"] * 1e-78) <= 1e-7
+    pair.close()
