@@ -101,7 +101,7 @@ struct ssn_ctx {
     int64_t cg_pb_cap = 0;
     double *dual = nullptr;                    // CSR: workspace of directions in the sample's row space
     int64_t dual_cap = 0;
-    void *hess = nullptr;                      // dense, small p K: blocks of the formed sub-sampled Hessian, per row chunk
+    double *hess = nullptr;                     // dense, small p K: blocks of the formed sub-sampled Hessian, per row chunk
     int64_t hess_cap = 0;
     void *grad_next = nullptr;                 // gradient at the first line-search trial (look-ahead of ssn_solve)
     CgSlot *slots = nullptr;
@@ -176,8 +176,8 @@ int ensure_rows(ssn_ctx *c, void **buf, int64_t *have, int64_t rows)
     return SSN_OK;
 }
 
-// make sure a workspace has at least `need` elements
-int ensure_elems(ssn_ctx *c, void **buf, int64_t *have, int64_t need)
+// make sure a workspace has at least `need` doubles
+int ensure_doubles(ssn_ctx *c, double **buf, int64_t *have, int64_t need)
 {
     if (*have >= need) return SSN_OK;
     if (*buf) {
@@ -186,7 +186,7 @@ int ensure_elems(ssn_ctx *c, void **buf, int64_t *have, int64_t need)
         *buf = nullptr;
         *have = 0;
     }
-    SSN_HIP(c, hipMalloc(buf, (size_t)need * c->es));
+    SSN_HIP(c, hipMalloc((void **)buf, (size_t)need * sizeof(double)));
     *have = need;
     return SSN_OK;
 }
@@ -1198,16 +1198,7 @@ static int dual_enqueue(ssn_ctx *c, const void *G, double theta, int32_t T, void
     if (v.gram_rows != v.nrows) SSN_HIP(c, csc_gram(&v, c->d.dtype, c->st));
     int nks = 0, kper = 0;
     const int64_t need = dual_doubles(v.nrows, c->K, &nks, &kper);
-    if (c->dual_cap < need) {
-        if (c->dual) {
-            SSN_HIP(c, hipStreamSynchronize(c->st));
-            SSN_HIP(c, hipFree(c->dual));
-            c->dual = nullptr;
-            c->dual_cap = 0;
-        }
-        SSN_HIP(c, hipMalloc((void **)&c->dual, (size_t)need * sizeof(double)));
-        c->dual_cap = need;
-    }
+    SSN_TRY(ensure_doubles(c, &c->dual, &c->dual_cap, need));
     const int vb = vec_blocks(c->d.p * (int64_t)c->K);
     SSN_HIP(c, launch_dot_part(c->d.dtype, c->d.p, c->K, G, c->d.ldw, G, c->d.ldw, c->red_b, vb, nullptr, c->st));
     SSN_HIP(c, launch_cg_init_state(c->red_b, vb, c->slots + T, c->st));
@@ -1307,7 +1298,7 @@ static int cg_enqueue(ssn_ctx *c, const void *G, double theta, int32_t T, void *
     SSN_TRY(ensure_slots(c, T));
     HessSmall hs{};
     if (is_dense(c) && hess_small_plan(c->d.dtype, c->d.p, c->K, c->nS, T, c->num_cus, &hs)) {
-        SSN_TRY(ensure_elems(c, &c->hess, &c->hess_cap, hs.chunks * hs.elems));
+        SSN_TRY(ensure_doubles(c, &c->hess, &c->hess_cap, hs.work));
         RowsArgs r = rows_base(c);
         r.S = c->S;
         r.nrows = c->nS;

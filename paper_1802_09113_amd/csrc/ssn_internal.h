@@ -435,12 +435,14 @@ struct HessSmall {
     int upt;                 // strips per thread of the CG kernel
     int nsup, chunks;        // pairs of feature blocks, row chunks of the forming kernel
     int lds;
-    int64_t rows_per_chunk, elems;           // elems: of one chunk's blocks; the workspace holds chunks * elems
+    bool summed;             // a launch of its own adds the chunks
+    int64_t rows_per_chunk, elems, work;     // elems: of one chunk's blocks; work: doubles of the workspace
 };
 // whether this form serves T products on nS sampled rows, and how
 bool hess_small_plan(int dtype, int64_t p, int K, int64_t nS, int T, int num_cus, HessSmall *h);
 struct HessCg {
-    const void *H;           // set by the launcher, with the sizes below
+    const void *H;           // set by the launcher, with the sizes below: the blocks, or (nsum > 0) nsum chunks' shares of them
+    const double *part;
     int64_t elems;
     int32_t nsum, p, K, pairs, nc, pl;
     double scale, lambda, theta;
@@ -457,6 +459,6 @@ struct HessCg {
     double *slope_dev, *host_out;
 };
 // r: the sample's rows (S, nrows) and the row stride KP of their probabilities P
-hipError_t launch_hess_small(int dtype, const HessSmall &h, const RowsArgs &r, const void *P, void *part, HessCg a, hipStream_t st);
+hipError_t launch_hess_small(int dtype, const HessSmall &h, const RowsArgs &r, const void *P, double *part, HessCg a, hipStream_t st);
 
 }  // namespace ssn
