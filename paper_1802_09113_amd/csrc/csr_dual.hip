@@ -6,17 +6,21 @@
 // and what the method asks of a vector needs no column of the matrix:
 //   X_S v = a (X_S g) + A Y,  A = X_S X_S^T (nS x nS, once per sample),   <v, v> = a (a g.g + Y . X_S g) + Y . X_S v.
 // A text sample of 1000 rows of 450 entries touches 127 000 columns; with 19 weight columns a vector of Alg. 2 on those is
-// 2.4 million numbers, and 19 000 here.  A CG iteration is two launches: the product U(X_S r) and A U on the matrix cores
-// (dual_product_kernel), then all scalars and updates (dual_update_kernel, the counterpart of finalize_cg_kernel, with
-// the product applied to the residual and every dot product left as partials by the launch before).  The direction is
-// p g + X_S^T Y_p at the end: one gather.  Everything here is in fp64 whatever the data's precision.
+// 2.4 million numbers, and 19 000 here.  A CG iteration is two launches: the new direction's X_S s = X_S r + beta X_S s,
+// U(X_S s) and A U on the matrix cores (dual_product_kernel), then the step and all updates (dual_update_kernel, the
+// counterpart of finalize_cg_kernel: every dot product is left as partials by the launch before).  The curvature is that of s
+// itself, sum of X_S s . U(X_S s) + lambda s . s: formed from the residual's, r . H r + 2 beta r . H s + beta^2 s . H s, as the
+// dense paths do, it cancels where lambda is small, and the directions were 3 (lambda 1e-3) to 16 times (1e-4) as far from
+// extended precision as those of CG on the columns.  The direction is p g + X_S^T Y_p at the end: one gather.  Everything
+// here is in fp64 whatever the data's precision.
 //
-// 20000 x 1355191, 450 entries a row, K 19, fp64, 1000 sampled rows: an iteration 85 -> 12 us (product 4.6, update 4.5), the
-// Gram matrix 75, a direction of ten products with its preparation 1222 -> 590; two Newton steps 4291 -> 2987 us.
+// 20000 x 1355191, 450 entries a row, K 19, fp64, 1000 sampled rows: an iteration 85 -> 14 us (product 8.0, update 5.0), the
+// Gram matrix 75, a direction of ten products with its preparation 1222 -> 600; two Newton steps 4291 -> 3020 us.
 // Precision: what the scalars lose is the part of g that the sampled rows span, as r . r forms from terms of the size of
-// rho^2 g.g; but rho falls with r (it is the residual on every coordinate outside the rows' span), and on 25 text samples
-// of five shapes the directions are as far from extended precision as those of CG on the columns: 1e-16 to 1e-7 by shape,
-// the ratio of the two between 0.05 and 7.4, 1.03 in the geometric mean.
+// rho^2 g.g; but rho falls with r (it is the residual on every coordinate outside the rows' span).  On 25 text samples of five
+// shapes the directions are as far from extended precision as those of CG on the columns: 1e-16 to 1e-7 by shape, the ratio of
+// the two between 0.07 and 10, 0.80 in the geometric mean; on well conditioned samples of 100 to 400 short rows 0.84 (lambda
+// 1e-2), 2.0 (1e-3) and 4.4 (1e-4: 1.2e-15 against 2.8e-16).
 #include "ssn_internal.h"
 #include "ssn_math.h"
 #include "csr_margin.h"
@@ -264,73 +268,6 @@ template <typename T, int VEC> __global__ __launch_bounds__(64 * START_WAVES) vo
     a.yr[o] = a.yp[o] = a.ybest[o] = 0.0;
 }
 
-// U(w) of the rows [ks * kper, + kper) of the sample, 64 at a time, and their share of gram * U for 64 rows: a workgroup
-// of four waves, one 16-row tile each; part[ks] receives the share.  Both operands of the matrix instruction come in whole
-// lines: gram is symmetric, so its rows serve as columns, and U goes through LDS.  The workgroups of the first row tile
-// also store U and leave their sum of w . U(w).
-template <typename T, int NB> __global__ __launch_bounds__(256) void dual_product_kernel(DualCg a, const int32_t *skip)
-{
-    if (*skip) return;
-    constexpr int UL = NB * 16 + 1;
-    __shared__ double us[64 * UL];
-    __shared__ double red[4];
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, q = lane >> 4, f = lane & 15;
-    const int K = a.K, n = a.n, it = blockIdx.x, ks = blockIdx.y;
-    const T *P = (const T *)a.P;
-    const int k1 = (ks + 1) * a.kper < a.ld ? (ks + 1) * a.kper : a.ld;
-    dv4 acc[NB];
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb) acc[nb] = dv4{0, 0, 0, 0};
-    double zu = 0.0;
-    for (int kb = ks * a.kper; kb < k1; kb += 64) {
-        double g[16];
-#pragma unroll
-        for (int s = 0; s < 16; ++s) g[s] = a.gram[(int64_t)(kb + 4 * s + q) * a.ld + it * 64 + w * 16 + f];
-        const int r = kb + (tid >> 2), sub = tid & 3;
-        double pv[NB * 4], wv[NB * 4], t = 0.0;
-#pragma unroll
-        for (int m = 0; m < NB * 4; ++m) {
-            const int c = sub + 4 * m;
-            const bool in = r < n && c < K;
-            pv[m] = in ? (double)P[(int64_t)r * a.KP + c] : 0.0;
-            wv[m] = in ? a.w[(int64_t)r * K + c] : 0.0;
-        }
-#pragma unroll
-        for (int m = 0; m < NB * 4; ++m) t += pv[m] * wv[m];
-        t += __shfl_xor(t, 1);
-        t += __shfl_xor(t, 2);
-        if (kb > ks * a.kper) __syncthreads();                       // the rows before these have been used
-#pragma unroll
-        for (int m = 0; m < NB * 4; ++m) {
-            const int c = sub + 4 * m;
-            const double u = pv[m] * wv[m] - pv[m] * t;              // eq. (12); zero in padded rows and classes
-            us[(tid >> 2) * UL + c] = u;
-            if (it == 0 && r < n && c < K) {
-                a.u[(int64_t)r * K + c] = u;
-                zu += wv[m] * u;
-            }
-        }
-        __syncthreads();
-#pragma unroll
-        for (int s = 0; s < 16; ++s)
-#pragma unroll
-            for (int nb = 0; nb < NB; ++nb) acc[nb] = dmfma(g[s], us[(4 * s + q) * UL + nb * 16 + f], acc[nb]);
-    }
-    double *out = a.part + (int64_t)ks * n * K;
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int r = it * 64 + w * 16 + 4 * v + q, c = nb * 16 + f;
-            if (r < n && c < K) out[(int64_t)r * K + c] = acc[nb][v];
-        }
-    if (it != 0) return;                                             // the whole workgroup
-    zu = wave_inclusive_scan(zu);
-    if (lane == 63) red[w] = zu;
-    __syncthreads();
-    if (tid == 0) a.zu_part[ks] = (red[0] + red[1]) + (red[2] + red[3]);
-}
-
 // sums of N values over the block, the same bits in every thread
 template <int N> __device__ __forceinline__ void dual_sums(double (&v)[N])
 {
@@ -376,9 +313,123 @@ __device__ __forceinline__ DualState dual_advance(const CgSlot &prev, double rr_
     return s;
 }
 
+// What both launches of product k form alike from the state before product k - 1 (product 0: that of the initialisation,
+// whose residual is -g) and the partials of Y_r . X_S g and Y_r . X_S r_k behind it.
+struct DualBefore {
+    DualState s;
+    double rho, sigma, gg, beta;
+};
+__device__ __forceinline__ DualBefore dual_before(const CgSlot &prev, bool first, double yz, double yw, double theta)
+{
+    DualBefore b;
+    b.gg = first ? prev.rr : prev.goff;
+    b.rho = first ? -1.0 : prev.rho;
+    b.sigma = first ? 0.0 : prev.sigma;
+    b.s = dual_advance(prev, dual_rr(b.rho, b.gg, yz, yw), theta);
+    if (first) {
+        b.s.rr = prev.rr;
+        b.s.rbest = prev.rbest;
+        b.s.pibest = prev.pibest;
+        b.s.done = prev.done;
+        b.s.iters = 0;
+        b.s.flags = prev.flags;
+        b.s.better = 0;
+    }
+    b.beta = (first || b.s.done) ? 0.0 : b.s.rr / prev.rr;
+    return b;
+}
+
+// X_S s of the new direction (line 12) and its U for the rows [ks * kper, + kper) of the sample, 64 at a time, and their share
+// of gram * U for 64 rows: a workgroup of four waves, one 16-row tile each; part[ks] receives the share.  Both operands of the
+// matrix instruction come in whole lines: gram is symmetric, so its rows serve as columns, and U goes through LDS.  The
+// workgroups of the first row tile also store X_S s (beside the one before, which the others still read) and U and leave
+// their sum of X_S s . U.
+template <typename T, int NB>
+__global__ __launch_bounds__(256) void dual_product_kernel(DualCg a, const CgSlot *prev_p, int k, const double *din, int nb)
+{
+    const bool first = k == 0;
+    const CgSlot prev = *prev_p;
+    if (prev.done || (!first && prev.brk)) return;
+    constexpr int UL = NB * 16 + 1;
+    __shared__ double us[64 * UL];
+    __shared__ double red[4];
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, q = lane >> 4, f = lane & 15;
+    const int K = a.K, n = a.n, it = blockIdx.x, ks = blockIdx.y;
+    const T *P = (const T *)a.P;
+    const double *xs_old = k & 1 ? a.xs[0] : a.xs[1];
+    double *xs_new = k & 1 ? a.xs[1] : a.xs[0];
+    const int k0 = ks * a.kper, k1 = k0 + a.kper < a.ld ? k0 + a.kper : a.ld;
+    double g[16];
+    auto fetch = [&](int kb) {
+#pragma unroll
+        for (int s = 0; s < 16; ++s) g[s] = a.gram[(int64_t)(kb + 4 * s + q) * a.ld + it * 64 + w * 16 + f];
+    };
+    fetch(k0);                               // on the way while the scalars are formed
+    double v[2] = {0.0, 0.0};
+    if (!first)
+        for (int i = tid; i < nb; i += 256) {
+            v[0] += din[i];
+            v[1] += din[nb + i];
+        }
+    dual_sums<2>(v);
+    const DualBefore b = dual_before(prev, first, v[0], v[1], a.theta);
+    if (b.s.done) return;                    // the same in every workgroup
+    dv4 acc[NB];
+#pragma unroll
+    for (int nb_ = 0; nb_ < NB; ++nb_) acc[nb_] = dv4{0, 0, 0, 0};
+    double zu = 0.0;
+    for (int kb = k0; kb < k1; kb += 64) {
+        if (kb > k0) fetch(kb);
+        const int r = kb + (tid >> 2), sub = tid & 3;
+        double pv[NB * 4], xv[NB * 4], t = 0.0;
+#pragma unroll
+        for (int m = 0; m < NB * 4; ++m) {
+            const int c = sub + 4 * m;
+            const bool in = r < n && c < K;
+            pv[m] = in ? (double)P[(int64_t)r * a.KP + c] : 0.0;
+            xv[m] = in ? a.w[(int64_t)r * K + c] : 0.0;
+            if (!first && in) xv[m] += b.beta * xs_old[(int64_t)r * K + c];
+        }
+#pragma unroll
+        for (int m = 0; m < NB * 4; ++m) t += pv[m] * xv[m];
+        t += __shfl_xor(t, 1);
+        t += __shfl_xor(t, 2);
+        if (kb > k0) __syncthreads();                                // the rows before these have been used
+#pragma unroll
+        for (int m = 0; m < NB * 4; ++m) {
+            const int c = sub + 4 * m;
+            const double u = pv[m] * xv[m] - pv[m] * t;              // eq. (12); zero in padded rows and classes
+            us[(tid >> 2) * UL + c] = u;
+            if (it == 0 && r < n && c < K) {
+                xs_new[(int64_t)r * K + c] = xv[m];
+                a.u[(int64_t)r * K + c] = u;
+                zu += xv[m] * u;
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int s = 0; s < 16; ++s)
+#pragma unroll
+            for (int i = 0; i < NB; ++i) acc[i] = dmfma(g[s], us[(4 * s + q) * UL + i * 16 + f], acc[i]);
+    }
+    double *out = a.part + (int64_t)ks * n * K;
+#pragma unroll
+    for (int i = 0; i < NB; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int r = it * 64 + w * 16 + 4 * e + q, c = i * 16 + f;
+            if (r < n && c < K) out[(int64_t)r * K + c] = acc[i][e];
+        }
+    if (it != 0) return;                                             // the whole workgroup
+    zu = wave_inclusive_scan(zu);
+    if (lane == 63) red[w] = zu;
+    __syncthreads();
+    if (tid == 0) a.zu_part[ks] = (red[0] + red[1]) + (red[2] + red[3]);
+}
+
 // Behind product k: the scalars and lines 7-12 of Alg. 2 (see finalize_cg_kernel).  A state slot holds rho of r_{k+1}, sigma
-// of s_k, pi of p_{k+1} (r = rho g + X_S^T Y_r and so on) and g.g in goff; product 0 starts from slot *prev of the
-// initialisation, whose residual is -g.
+// of s_k, pi of p_{k+1} (r = rho g + X_S^T Y_r and so on), g.g in goff and s_k . s_k in sHs; product 0 starts from slot *prev
+// of the initialisation.
 __global__ __launch_bounds__(256) void dual_update_kernel(DualCg a, const CgSlot *prev_p, CgSlot *cur, int k, const double *din,
                                                           double *dout)
 {
@@ -386,19 +437,15 @@ __global__ __launch_bounds__(256) void dual_update_kernel(DualCg a, const CgSlot
     const CgSlot prev = *prev_p;
     const int64_t total = (int64_t)a.n * a.K, e = (int64_t)blockIdx.x * 256 + threadIdx.x, eo = e < total ? e : 0;
     const int nb = gridDim.x;
-    double u = a.u[eo], w = a.w[eo], zg = a.zg[eo], yr = a.yr[eo], yp = a.yp[eo];
-    double us = 0.0, xh = 0.0, ys = 0.0, gu = 0.0;
-    if (!first) {
-        us = a.us[eo];
-        xh = a.xh[eo];
-        ys = a.ys[eo];
-    }
-    double v[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+    const double *xs = k & 1 ? a.xs[1] : a.xs[0];
+    double w = a.w[eo], yr = a.yr[eo], yp = a.yp[eo], ys = first ? 0.0 : a.ys[eo], gu = 0.0;
+    const double u = a.u[eo], x = xs[eo], zg = a.zg[eo];
+    double v[4] = {0.0, 0.0, 0.0, 0.0};
     for (int i = threadIdx.x; i < a.nks; i += 256) v[0] += a.zu_part[i];
     if (!first)
         for (int i = threadIdx.x; i < nb; i += 256) {
 #pragma unroll
-            for (int j = 0; j < 4; ++j) v[1 + j] += din[j * nb + i];
+            for (int j = 0; j < 3; ++j) v[1 + j] += din[j * nb + i];
         }
     for (int c = 0; c < a.nks; c += 8) {
         double t[8];
@@ -407,27 +454,16 @@ __global__ __launch_bounds__(256) void dual_update_kernel(DualCg a, const CgSlot
 #pragma unroll
         for (int i = 0; i < 8; ++i) gu += (c + i < a.nks) ? t[i] : 0.0;
     }
-    dual_sums<5>(v);
-    const double gg = first ? prev.rr : prev.goff, rho = first ? -1.0 : prev.rho, sig = first ? 0.0 : prev.sigma;
-    const double pi = first ? 0.0 : prev.pi;
-    DualState s = dual_advance(prev, dual_rr(rho, gg, v[1], v[2]), a.theta);
-    if (first) {
-        s.rr = prev.rr;
-        s.rbest = prev.rbest;
-        s.pibest = prev.pibest;
-        s.done = prev.done;
-        s.iters = 0;
-        s.flags = prev.flags;
-        s.better = 0;
-    }
-    const double beta = (first || s.done) ? 0.0 : s.rr / prev.rr;
-    const double rHr = a.scale * v[0] + a.lambda * s.rr;
-    // r_k . (H s_{k-1}) = scale X_S r_k . U(X_S s_{k-1}) + lambda r_k . s_{k-1}
-    const double rhs = a.scale * v[3] + a.lambda * (sig * (rho * gg + v[1]) + v[4]);
-    const double sHs = first ? rHr : rHr + 2.0 * beta * rhs + beta * beta * prev.sHs;
+    dual_sums<4>(v);
+    const DualBefore b = dual_before(prev, first, v[1], v[2], a.theta);
+    const DualState &s = b.s;
+    const double beta = b.beta;
+    // s_k . s_k from r_k . s_{k-1} = sigma (rho g.g + Y_r . X_S g) + Y_s . X_S r_k, which is rounding and no more
+    const double ss = first ? s.rr : s.rr + 2.0 * beta * (b.sigma * (b.rho * b.gg + v[1]) + v[3]) + beta * beta * prev.sHs;
+    const double sHs = a.scale * v[0] + a.lambda * ss;
     const bool brk = !s.done && !(sHs > 0.0), update = !s.done && !brk;
     const double alpha = update ? s.rr / sHs : 0.0;
-    const double sig_n = update ? rho + beta * sig : sig;
+    const double sig_n = update ? b.rho + beta * b.sigma : b.sigma, pi = first ? 0.0 : prev.pi;
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         cur->rr = s.rr;
         cur->rbest = s.rbest;
@@ -439,9 +475,9 @@ __global__ __launch_bounds__(256) void dual_update_kernel(DualCg a, const CgSlot
         cur->alpha = alpha;
         cur->best_cur = 0;
         cur->best_pending = 0;
-        cur->sHs = sHs;
-        cur->goff = gg;
-        cur->rho = rho - alpha * a.lambda * sig_n;
+        cur->sHs = ss;
+        cur->goff = b.gg;
+        cur->rho = b.rho - alpha * a.lambda * sig_n;
         cur->sigma = sig_n;
         cur->pi = pi + alpha * sig_n;
         cur->pibest = s.pibest;
@@ -456,29 +492,24 @@ __global__ __launch_bounds__(256) void dual_update_kernel(DualCg a, const CgSlot
     }
     if (s.better && e < total) a.ybest[e] = yp;                      // line 10 for the iterate the last product left
     if (!update) return;
-    double d[4] = {0.0, 0.0, 0.0, 0.0};
+    double d[3] = {0.0, 0.0, 0.0};
     if (e < total) {
-        us = u + beta * us;
-        xh = (a.scale * gu + a.lambda * w) + beta * xh;
         ys = yr + beta * ys;                                         // line 12
         yp += alpha * ys;                                            // line 8
-        yr -= alpha * (a.scale * us + a.lambda * ys);                // line 9
-        w -= alpha * xh;
-        a.us[e] = us;
-        a.xh[e] = xh;
+        yr -= alpha * (a.scale * u + a.lambda * ys);                 // line 9
+        w -= alpha * (a.scale * gu + a.lambda * x);
         a.ys[e] = ys;
         a.yp[e] = yp;
         a.yr[e] = yr;
         a.w[e] = w;
         d[0] = yr * zg;
         d[1] = yr * w;
-        d[2] = w * us;
-        d[3] = ys * w;
+        d[2] = ys * w;
     }
-    dual_sums<4>(d);
+    dual_sums<3>(d);
     if (threadIdx.x == 0) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) dout[j * nb + blockIdx.x] = d[j];
+        for (int j = 0; j < 3; ++j) dout[j * nb + blockIdx.x] = d[j];
     }
 }
 
@@ -547,11 +578,10 @@ template <typename T> static hipError_t dual_go(DualCg a, CgSlot *slots, int T_,
     else hipLaunchKernelGGL((dual_start_kernel<T, 16 / (int)sizeof(T)>), rows, waves, 0, st, a);
     for (int k = 0; k < T_; ++k) {
         const CgSlot *prev = k ? slots + (k - 1) : slots + T_;       // the initial state waits in the last slot
-        const int32_t *skip = &prev->done;
-        if (a.K <= 16) hipLaunchKernelGGL((dual_product_kernel<T, 1>), grid, block, 0, st, a, skip);
-        else if (a.K <= 32) hipLaunchKernelGGL((dual_product_kernel<T, 2>), grid, block, 0, st, a, skip);
-        else hipLaunchKernelGGL((dual_product_kernel<T, 4>), grid, block, 0, st, a, skip);
         double *in = parts + (size_t)((k + 1) & 1) * 4 * RED_MAX_PARTS, *out = parts + (size_t)(k & 1) * 4 * RED_MAX_PARTS;
+        if (a.K <= 16) hipLaunchKernelGGL((dual_product_kernel<T, 1>), grid, block, 0, st, a, prev, k, in, nb);
+        else if (a.K <= 32) hipLaunchKernelGGL((dual_product_kernel<T, 2>), grid, block, 0, st, a, prev, k, in, nb);
+        else hipLaunchKernelGGL((dual_product_kernel<T, 4>), grid, block, 0, st, a, prev, k, in, nb);
         hipLaunchKernelGGL(dual_update_kernel, dim3((unsigned)nb), block, 0, st, a, prev, slots + k, k, in, out);
     }
     hipLaunchKernelGGL(dual_tail_kernel<T>, dim3((unsigned)nb), block, 0, st, a, slots + (T_ - 1), slots + T_, T_,
@@ -571,8 +601,8 @@ hipError_t launch_dual_cg(int dtype, DualCg a, CgSlot *slots, int T, double *wor
     a.zg = vecs[0];
     a.w = vecs[1];
     a.u = vecs[2];
-    a.us = vecs[3];
-    a.xh = vecs[4];
+    a.xs[0] = vecs[3];
+    a.xs[1] = vecs[4];
     a.yr = vecs[5];
     a.ys = vecs[6];
     a.yp = vecs[7];

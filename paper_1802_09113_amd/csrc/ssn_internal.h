@@ -315,7 +315,8 @@ struct CgSlot {          // state before product k
     double alpha;        // step length of product k, where a kernel of its own computes it (CSR path)
     int32_t best_cur;    // CSR path: the best iterate is the CURRENT p and has not been copied to p_best yet
     int32_t best_pending;// dense paths: r_k was the best so far, p_best <- p_k is still to be done (by the next pass over p)
-    double sHs;          // dense paths: curvature s_k^T H s_k of product k (written with alpha by that product's finalize)
+    double sHs;          // dense paths: curvature s_k^T H s_k of product k (written with alpha by that product's finalize); CSR
+                         // forms of two and three launches per product, whose curvature is s_k's own: s_k^T s_k
     // CSR path: the CG vectors are kept on the columns the sample touches only.  On every other coordinate j
     // H_S is lambda I, so r_j, s_j, p_j stay multiples of g_j; the multipliers and the sum of g_j^2 over those
     // coordinates (goff; 0 on the dense paths, where the terms below vanish) are all that is needed of them.
@@ -418,7 +419,7 @@ struct DualCg {
     double *trace;
     // set by the launcher
     int32_t ld, nks, kper;
-    double *zg, *w, *u, *us, *xh, *yr, *ys, *yp, *ybest;     // X_S g; X_S r; U(X_S r); U(X_S s); X_S H s; coefficients of r, s, p
+    double *zg, *w, *u, *xs[2], *yr, *ys, *yp, *ybest;       // X_S g; X_S r; U(X_S s); X_S s, this and the last; coefficients of r, s, p
     double *part, *zu_part;
 };
 // every launch of Alg. 2; slots[T] holds the initial state (launch_cg_init_state: g.g over all coordinates) on entry and the
