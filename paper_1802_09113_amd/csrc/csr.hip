@@ -225,9 +225,40 @@ template <typename T, int MODE> __global__ __launch_bounds__(64 * ROWS_WAVES_PER
     T zl = T(0);
     int64_t svl = 0;
     int labl = 0, cnt = 0;
+    // inside CG: the partials of r.r are on their way while the first margins are formed (RowsArgs::zs)
+    constexpr int RR = MODE == ROW_APPLY ? RED_MAX_PARTS / 64 : 1;
+    double rr_part[RR], beta = 0.0;
+    bool have_beta = true;
+    if constexpr (MODE == ROW_APPLY) {
+        have_beta = !(a.zs && a.cg_prev);
+        if (!have_beta) {
+#pragma unroll
+            for (int u = 0; u < RR; ++u) {
+                rr_part[u] = 0.0;
+                if (64 * u < a.cg_nrr && 64 * u + lane < a.cg_nrr) rr_part[u] = a.cg_rr[64 * u + lane];
+            }
+        }
+    }
     auto flush = [&]() {
+        if constexpr (MODE == ROW_APPLY) {
+            if (!have_beta) {
+                double v = 0.0;
+#pragma unroll
+                for (int u = 0; u < RR; ++u) v += rr_part[u];
+                v = __shfl(wave_inclusive_scan(v), 63);
+                const CgSlot *q = a.cg_prev;
+                const double rho = q->rho - q->alpha * a.cg_lambda * q->sigma;
+                beta = (q->done || q->brk) ? 0.0 : (v + rho * rho * q->goff) / q->rr;
+                have_beta = true;
+            }
+        }
         if (lane < cnt) {
             if constexpr (MODE == ROW_APPLY) {
+                if (a.zs) {
+                    const double z = (double)zl + (a.cg_prev ? beta * a.zs[svl] : 0.0);
+                    a.zs[svl] = z;
+                    zl = (T)z;
+                }
                 const T pin = ((const T *)a.Pin)[svl * a.KP];
                 const T t = pin * zl;
                 const T u = pin * zl - pin * t;              // eq. (12) with one class

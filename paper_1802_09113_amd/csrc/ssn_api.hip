@@ -99,7 +99,7 @@ struct ssn_ctx {
     double *cg_parts = nullptr;                // dense paths: 2 x 2 x RED_MAX_PARTS partials of r.r and r.(H s), double-buffered
     void *cg_pb = nullptr;                     // CSR: best iterate on the sample's columns (cg_pb_cap elements)
     int64_t cg_pb_cap = 0;
-    double *dual = nullptr;                    // CSR: workspace of directions in the sample's row space
+    double *dual = nullptr;                    // CSR: workspace of directions in the sample's row space; one weight column: X_S s
     int64_t dual_cap = 0;
     double *hess = nullptr;                     // dense, small p K: blocks of the formed sub-sampled Hessian, per row chunk
     int64_t hess_cap = 0;
@@ -1230,7 +1230,7 @@ static int dual_enqueue(ssn_ctx *c, const void *G, double theta, int32_t T, void
 static int csc1_cg_enqueue(ssn_ctx *c, const CgVecs &v, double theta, int32_t T, void *P_out, int blocks, int *n_slope)
 {
     const CscView &sv = c->csc_samp;
-    SSN_HIP(c, launch_csc1_cg_init(c->d.dtype, v, c->d.p, c->d.ldw, sv.cols, c->cg_hs, c->red_a, c->red_b, blocks, c->st));
+    SSN_HIP(c, launch_csc1_cg_init(c->d.dtype, v, c->d.p, c->d.ldw, sv.cols, c->red_a, c->red_b, blocks, c->st));
     const int nb = csc1_cg_blocks(sv.npieces);
     for (int k = 0; k < T; ++k) {
         // the theta test for r_k is made behind product k: the flag its launches look at is the one before it
@@ -1248,10 +1248,15 @@ static int csc1_cg_enqueue(ssn_ctx *c, const CgVecs &v, double theta, int32_t T,
         a.vals = sv.val_in;
         a.p = v.p;
         a.ldm = v.ld;
+        double *in = c->cg_parts + (size_t)((k + 1) & 1) * 2 * RED_MAX_PARTS;
+        a.zs = c->dual;
+        a.cg_prev = k > 0 ? c->slots + (k - 1) : nullptr;
+        a.cg_rr = in;
+        a.cg_nrr = nb;
+        a.cg_lambda = c->d.lambda;
         int nparts = 0;
         SSN_TRY(launch_rows(c, a, &nparts));
         SSN_HIP(c, launch_csc1_pieces(c->d.dtype, sv, c->KP, c->Ubuf, skip, c->st));
-        double *in = c->cg_parts + (size_t)((k + 1) & 1) * 2 * RED_MAX_PARTS;
         double *out = c->cg_parts + (size_t)(k & 1) * 2 * RED_MAX_PARTS;
         FinCgArgs g{};
         g.prev = k > 0 ? c->slots + (k - 1) : nullptr;
@@ -1262,7 +1267,6 @@ static int csc1_cg_enqueue(ssn_ctx *c, const CgVecs &v, double theta, int32_t T,
         g.pv = v.pv;
         g.r = v.r;
         g.s = v.s;
-        g.hs = c->cg_hs;
         g.pbest = v.pbest;
         g.zu_part = c->loss_part;
         g.n_zu = nparts;
@@ -1334,10 +1338,9 @@ static int cg_enqueue(ssn_ctx *c, const void *G, double theta, int32_t T, void *
     // 399/305, 5000 of 450 in 1355191 columns 659/608 (fp32) and 703/672 (fp64); 20000 of 450 (900 000 pieces) 1918/1957 (fp64)
     const bool csc1 = !is_dense(c) && T > 0 && c->csc_samp.has_support && csc_windows(c->csc_samp, c->K) &&
                       c->csc_samp.npieces <= 3 * RED_MAX_PARTS * VEC_BLOCK;
-    if ((is_dense(c) || csc1) && !c->cg_hs) {
-        SSN_TRY(vec_bytes_alloc(c, &c->cg_hs));
-        SSN_HIP(c, hipMalloc((void **)&c->cg_parts, sizeof(double) * 4 * RED_MAX_PARTS));
-    }
+    if (is_dense(c) && !c->cg_hs) SSN_TRY(vec_bytes_alloc(c, &c->cg_hs));
+    if ((is_dense(c) || csc1) && !c->cg_parts) SSN_HIP(c, hipMalloc((void **)&c->cg_parts, sizeof(double) * 4 * RED_MAX_PARTS));
+    if (csc1) SSN_TRY(ensure_doubles(c, &c->dual, &c->dual_cap, c->nS));
     CgVecs v{};
     v.p = c->d.p;
     v.K = c->K;

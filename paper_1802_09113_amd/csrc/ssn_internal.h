@@ -66,6 +66,15 @@ struct RowsArgs {
     const int32_t *rwin;
     void *zrow, *zhead;
     int64_t nnz;
+    // CSR, one weight column, ROW_APPLY inside CG (nullable): the rows' margins of the search direction, one per row.  The
+    // margins of M = r_k, plus beta times what stands there, take their place, and U is that of those: X s_k = X r_k + beta
+    // X s_{k-1}.  beta from the state before product k - 1 (nullptr: product 0) and cg_nrr partials of r_k.r_k on the sample's
+    // columns
+    double *zs;
+    const CgSlot *cg_prev;
+    const double *cg_rr;
+    int32_t cg_nrr;
+    double cg_lambda;
 };
 
 // Arguments of the transposed product: part[chunk] = X_rows(chunk)^T * U(chunk).
@@ -372,10 +381,10 @@ struct FinCgArgs {
     int n_gg;                //         0: slot *cur already holds the initial state
     double theta;
     void *pv, *r, *s, *hs, *pbest;   // CG vectors on the leading dimension FinArgs::ldm (FinArgs::M is not used)
-    const double *zu_part;   // per-wave partials of sum_i z_i . u_i left by the product's launch (operand r_k)
+    const double *zu_part;   // per-wave partials of sum_i z_i . u_i left by the product's launch (operand r_k; csc1_cg: s_k)
     int n_zu;
     const double *rr_in, *rhs_in;    // partials of r_k.r_k and r_k.(H s_{k-1}) from the previous finalize (k >= 1)
-    int n_in;
+    int n_in;                        // (csc1_cg: of r_k.s_{k-1} in place of the second)
     double *rr_out, *rhs_out;        // out: one partial per block of r_{k+1}.r_{k+1} and r_{k+1}.(H s_k)
     double *trace;           // nullable: 3 doubles per product (alpha, ||r_new||, s^T H s)
     int32_t k;
@@ -384,7 +393,7 @@ hipError_t launch_finalize_cg(int dtype, const FinArgs &a, const FinCgArgs &g, i
 // CSR, one weight column: lines 7-12 on the sample's columns from the sums of their pieces (g.gg_part, g.rhs_in at k == 0:
 // n_in partials of g.g on those columns and over all coordinates; else csc1_cg_blocks(npieces) partials of each)
 int csc1_cg_blocks(int64_t npieces);
-hipError_t launch_csc1_cg_init(int dtype, const CgVecs &v, int64_t p, int64_t ldg, const int32_t *cols, void *hs, double *gg_part,
+hipError_t launch_csc1_cg_init(int dtype, const CgVecs &v, int64_t p, int64_t ldg, const int32_t *cols, double *gg_part,
                                double *full_part, int blocks, hipStream_t st);
 hipError_t launch_csc1_cg(int dtype, const CscView &v, double scale, double lambda, const FinCgArgs &g, hipStream_t st);
 // after the last product: the final state, P = pibest G on all coordinates (launch_cg_expand_rows follows)

@@ -1578,17 +1578,19 @@ hipError_t launch_cg_r_update(int dtype, const CgVecs &v, const CgSlot *cur, dou
 }
 
 // ---- CSR with one weight column: CG in three launches per iteration ------------------------------------------
-// Margins of the sampled rows, sums of the columns' pieces, and one launch for all the rest.  The scheme is that of
-// finalize_cg_kernel -- the product is applied to the residual, H s kept as a vector, every scalar formed from partials the
-// launches before have left -- so no launch exists only to make alpha or to add r.r.  The vectors live on the sample's
-// columns; on all others r, s, p and H s are multiples of g (CgSlot::rho, sigma, pi and lambda sigma).  What bounds it is
+// Margins of the sampled rows, sums of the columns' pieces, and one launch for all the rest.  Every scalar is formed from
+// partials the launches before have left, so no launch exists only to make alpha or to add r.r.  The rows kernel forms X r and
+// adds beta X s of the product before, one number per row, so the curvature is that of s itself: formed from the residual's, as
+// in finalize_cg_kernel, it cancels where lambda is small, and fp64 directions were twice as far from extended precision.
+// s.s = r.r + 2 beta r.s + beta^2 s.s of the product before (CgSlot::sHs).  The vectors live on the sample's columns; on all
+// others r, s and p are multiples of g (CgSlot::rho, sigma, pi).  What bounds it is
 // launches: 2000 to 20000 elements per vector.  5000 rows of 57 entries, 20958 columns, fp32: an iteration of six launches
 // (products of s, alpha and r.r in kernels of their own) 24 us, this 15 us; ten products with their preparation 399 -> 305 us.
 
 // lines 1-5: the vectors on the sample's columns, partials of g.g there (gg_part) and over all coordinates (full_part)
 template <typename T>
 __global__ __launch_bounds__(VEC_BLOCK) void csc1_cg_init_kernel(CgVecs v, const T *G, int64_t p, int64_t ldg, const int32_t *cols,
-                                                                  T *hs, double *gg_part, double *full_part)
+                                                                  double *gg_part, double *full_part)
 {
     const int64_t first = (int64_t)blockIdx.x * VEC_BLOCK + threadIdx.x, stride = (int64_t)gridDim.x * VEC_BLOCK;
     T *pv = (T *)v.pv, *r = (T *)v.r, *s = (T *)v.s, *pb = (T *)v.pbest;
@@ -1598,7 +1600,6 @@ __global__ __launch_bounds__(VEC_BLOCK) void csc1_cg_init_kernel(CgVecs v, const
         pv[e] = T(0);
         r[e] = -gv;
         s[e] = T(0);
-        hs[e] = T(0);
         pb[e] = -gv;
         local += (double)gv * (double)gv;
     }
@@ -1660,20 +1661,20 @@ __global__ __launch_bounds__(VEC_BLOCK) void csc1_cg_kernel(const int32_t *piece
     const int lane = threadIdx.x & 63;
     const int64_t stride = (int64_t)gridDim.x * VEC_BLOCK;
     int64_t base = ((int64_t)blockIdx.x * VEC_BLOCK + threadIdx.x) / 64 * 64;
-    T *pv = (T *)g.pv, *r = (T *)g.r, *sv = (T *)g.s, *hsv = (T *)g.hs, *pb = (T *)g.pbest;
+    T *pv = (T *)g.pv, *r = (T *)g.r, *sv = (T *)g.s, *pb = (T *)g.pbest;
     CgSlot prev{};
     if (!g.first) prev = *g.prev;
     // pieces, partials and the vectors' elements go out together
     Piece1<T> q = piece1_load<T, true>(piece_col, npieces, pp, base, lane);
     const double *rin = g.first ? g.gg_part : g.rr_in;       // first: g.g on the sample's columns, and over all coordinates
-    const double vz = thread_parts(g.zu_part, g.n_zu), vr = thread_parts(rin, g.n_in), vh = thread_parts(g.rhs_in, g.n_in);
-    T pe = q.head ? pv[q.col] : T(0), re = q.head ? r[q.col] : T(0), se = q.head ? sv[q.col] : T(0), he = q.head ? hsv[q.col] : T(0);
-    double zu, rr_sum, h_sum;
-    block_sum3(vz, vr, vh, zu, rr_sum, h_sum);
+    const double vz = thread_parts(g.zu_part, g.n_zu), vr = thread_parts(rin, g.n_in), vs = thread_parts(g.rhs_in, g.n_in);
+    T pe = q.head ? pv[q.col] : T(0), re = q.head ? r[q.col] : T(0), se = q.head ? sv[q.col] : T(0);
+    double zu, rr_sum, rs_sum;
+    block_sum3(vz, vr, vs, zu, rr_sum, rs_sum);
     CgSlot c;
-    double beta = 0.0, sHs;
+    double beta = 0.0, ss;                                   // ss: s_k . s_k
     if (g.first) {
-        const double off = h_sum - rr_sum, gg = rr_sum + (off > 0.0 ? off : 0.0);
+        const double off = rs_sum - rr_sum, gg = rr_sum + (off > 0.0 ? off : 0.0);
         c.goff = off > 0.0 ? off : 0.0;
         c.rho = c.sigma = c.pibest = -1.0;
         c.pi = 0.0;
@@ -1681,19 +1682,19 @@ __global__ __launch_bounds__(VEC_BLOCK) void csc1_cg_kernel(const int32_t *piece
         c.rbest = c.gnorm = sqrt(gg);
         c.done = gg == 0.0 ? 1 : 0;
         c.iters = c.flags = c.best_cur = c.best_pending = 0;
-        sHs = scale * zu + lambda * c.rr;
+        ss = c.rr;
     } else {
         c = csc1_advance(prev, rr_sum, g.theta, lambda);
         beta = c.done ? 0.0 : c.rr / prev.rr;
         if (!c.done) c.sigma = c.rho + beta * prev.sigma;
-        const double rhs = h_sum + c.rho * lambda * prev.sigma * c.goff;
-        sHs = scale * zu + lambda * c.rr + 2.0 * beta * rhs + beta * beta * prev.sHs;
+        ss = c.rr + 2.0 * beta * (rs_sum + c.rho * prev.sigma * c.goff) + beta * beta * prev.sHs;
     }
+    const double sHs = scale * zu + lambda * ss;
     const bool brk = !c.done && !(sHs > 0.0);                // not positive definite in floating point: stop, keep p_best
     const double alpha = (c.done || brk) ? 0.0 : c.rr / sHs;
     c.brk = brk ? 1 : 0;
     c.alpha = alpha;
-    c.sHs = sHs;
+    c.sHs = ss;
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         slot_store(g.cur, c);
         if (!g.first && !prev.done && !prev.brk) g.trace[3 * (g.k - 1) + 1] = sqrt(c.rr);
@@ -1705,22 +1706,20 @@ __global__ __launch_bounds__(VEC_BLOCK) void csc1_cg_kernel(const int32_t *piece
     }
     const bool update = !c.done && !brk;
     if (!c.best_pending && !update) return;
-    double lrr = 0.0, lrh = 0.0;
+    double lrr = 0.0, lrs = 0.0;
     while (base < npieces) {                                 // uniform over the wave
         const T sum = piece1_column_sum(q, piece_col, npieces, pp, base, lane);
         if (q.head) {
             if (c.best_pending) pb[q.col] = pe;              // line 10 for the iterate the last product left
             if (update) {
-                const T hr = (T)(scale * (double)sum + lambda * (double)re);          // the element of H r, rounded as if stored
-                const T hs = (T)((double)hr + beta * (double)he);
                 const T sn = (T)((double)re + beta * (double)se);                     // line 12
+                const T hs = (T)(scale * (double)sum + lambda * (double)sn);          // the element of H s, rounded as if stored
                 const T rn = (T)((double)re - alpha * (double)hs);                    // line 9
-                hsv[q.col] = hs;
                 sv[q.col] = sn;
                 pv[q.col] = (T)((double)pe + alpha * (double)sn);                     // line 8
                 r[q.col] = rn;
                 lrr += (double)rn * (double)rn;
-                lrh += (double)rn * (double)hs;
+                lrs += (double)rn * (double)sn;
             }
         }
         base += stride;
@@ -1730,15 +1729,14 @@ __global__ __launch_bounds__(VEC_BLOCK) void csc1_cg_kernel(const int32_t *piece
             pe = pv[q.col];
             re = r[q.col];
             se = sv[q.col];
-            he = hsv[q.col];
         }
     }
     if (!update) return;
-    double rr_o, rh_o;
-    block_sum2(lrr, lrh, rr_o, rh_o);
+    double rr_o, rs_o;
+    block_sum2(lrr, lrs, rr_o, rs_o);
     if (threadIdx.x == 0) {
         g.rr_out[blockIdx.x] = rr_o;
-        g.rhs_out[blockIdx.x] = rh_o;
+        g.rhs_out[blockIdx.x] = rs_o;
     }
 }
 
@@ -1765,15 +1763,15 @@ int csc1_cg_blocks(int64_t npieces)
     return (int)(b > RED_MAX_PARTS ? RED_MAX_PARTS : b < 1 ? 1 : b);
 }
 
-hipError_t launch_csc1_cg_init(int dtype, const CgVecs &v, int64_t p, int64_t ldg, const int32_t *cols, void *hs, double *gg_part,
+hipError_t launch_csc1_cg_init(int dtype, const CgVecs &v, int64_t p, int64_t ldg, const int32_t *cols, double *gg_part,
                                double *full_part, int blocks, hipStream_t st)
 {
     if (dtype == SSN_F32)
         hipLaunchKernelGGL(csc1_cg_init_kernel<float>, dim3(blocks), dim3(VEC_BLOCK), 0, st, v, (const float *)v.G, p, ldg, cols,
-                           (float *)hs, gg_part, full_part);
+                           gg_part, full_part);
     else
         hipLaunchKernelGGL(csc1_cg_init_kernel<double>, dim3(blocks), dim3(VEC_BLOCK), 0, st, v, (const double *)v.G, p, ldg, cols,
-                           (double *)hs, gg_part, full_part);
+                           gg_part, full_part);
     return hipGetLastError();
 }
 
