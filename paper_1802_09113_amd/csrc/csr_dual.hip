@@ -235,8 +235,10 @@ template <typename T> static hipError_t gram_go(CscView *v, int ld, int fpad, hi
 
 hipError_t csc_gram(CscView *v, int dtype, hipStream_t st)
 {
-    // how many columns are frequent stays on the device: the buffers take what the entries allow
-    const int ld = (int)gram_ld(v->nrows), fpad = (int)(v->nnz / gram_freq_min(v->nrows) + 1 + 15) / 16 * 16;
+    // how many columns are frequent stays on the device: the buffers take what the entries allow, and the columns
+    const int ld = (int)gram_ld(v->nrows);
+    const int64_t by_nnz = v->nnz / gram_freq_min(v->nrows), most = by_nnz < v->ncols ? by_nnz : v->ncols;
+    const int fpad = most > 0 ? (int)((most + 15) / 16 * 16) : 16;
     hipError_t e = csc_frequent_columns(v, gram_freq_min(v->nrows), st);
     if (e == hipSuccess) e = dual_grow(&v->gram, &v->cap_gram, (int64_t)ld * ld);
     if (e == hipSuccess) e = dual_grow(&v->xfreq, &v->cap_xfreq, (int64_t)fpad * ld);
