@@ -191,6 +191,15 @@ int ensure_doubles(ssn_ctx *c, double **buf, int64_t *have, int64_t need)
     return SSN_OK;
 }
 
+// Whether a direction goes on in its general form because the workspace of a faster one did not fit (the failed allocation is
+// forgotten: the runtime would report it to the next launch)
+bool no_room(int status)
+{
+    if (status != SSN_E_ALLOC) return false;
+    (void)hipGetLastError();
+    return true;
+}
+
 RowsArgs rows_base(const ssn_ctx *c)
 {
     RowsArgs a{};
@@ -1076,6 +1085,11 @@ int ssn_rowmajor_to_vec(ssn_ctx *c, const void *block, void *vec)
 // validate: check the sample indices first (one pass and one synchronisation)
 // CSR, inside ssn_solve: the column-sorted view (and support) of the sample S, built on the auxiliary stream
 static bool dual_ok(const ssn_ctx *c, const CscView &v, double theta, int32_t T);
+static int gram_of(ssn_ctx *c, CscView *v, hipStream_t st)
+{
+    SSN_HIP(c, csc_gram(v, c->d.dtype, st));
+    return SSN_OK;
+}
 static int prebuild_sample_view(ssn_ctx *c, const int32_t *S, int64_t nS, double theta, int32_t T)
 {
     c->next_ready = false;
@@ -1084,7 +1098,10 @@ static int prebuild_sample_view(ssn_ctx *c, const int32_t *S, int64_t nS, double
         SSN_HIP(c, hipEventCreateWithFlags(&c->ev_aux, hipEventDisableTiming));
     }
     SSN_TRY(build_sample_view(c, &c->csc_next, S, nS, c->st_aux, true));
-    if (dual_ok(c, c->csc_next, theta, T)) SSN_HIP(c, csc_gram(&c->csc_next, c->d.dtype, c->st_aux));
+    if (dual_ok(c, c->csc_next, theta, T)) {
+        const int status = gram_of(c, &c->csc_next, c->st_aux);
+        if (status != SSN_OK && !no_room(status)) return status;
+    }
     SSN_HIP(c, hipEventRecord(c->ev_aux, c->st_aux));
     c->next_S = S;
     c->next_nS = nS;
@@ -1192,13 +1209,18 @@ static bool dual_ok(const ssn_ctx *c, const CscView &v, double theta, int32_t T)
     return (double)T * (iter - here) * 0.9 > gram;
 }
 
-static int dual_enqueue(ssn_ctx *c, const void *G, double theta, int32_t T, void *P_out, int *n_slope, bool trace)
+// the Gram matrix (if it was not made with the view) and the workspace
+static int dual_prepare(ssn_ctx *c)
 {
     CscView &v = c->csc_samp;
-    if (v.gram_rows != v.nrows) SSN_HIP(c, csc_gram(&v, c->d.dtype, c->st));
     int nks = 0, kper = 0;
-    const int64_t need = dual_doubles(v.nrows, c->K, &nks, &kper);
-    SSN_TRY(ensure_doubles(c, &c->dual, &c->dual_cap, need));
+    SSN_TRY(ensure_doubles(c, &c->dual, &c->dual_cap, dual_doubles(v.nrows, c->K, &nks, &kper)));
+    return v.gram_rows == v.nrows ? SSN_OK : gram_of(c, &v, c->st);
+}
+
+static int dual_enqueue(ssn_ctx *c, const void *G, double theta, int32_t T, void *P_out, int *n_slope, bool trace)
+{
+    const CscView &v = c->csc_samp;
     const int vb = vec_blocks(c->d.p * (int64_t)c->K);
     SSN_HIP(c, launch_dot_part(c->d.dtype, c->d.p, c->K, G, c->d.ldw, G, c->d.ldw, c->red_b, vb, nullptr, c->st));
     SSN_HIP(c, launch_cg_init_state(c->red_b, vb, c->slots + T, c->st));
@@ -1301,8 +1323,13 @@ static int cg_enqueue(ssn_ctx *c, const void *G, double theta, int32_t T, void *
     if (solve_fused) *solve_fused = false;
     SSN_TRY(ensure_slots(c, T));
     HessSmall hs{};
-    if (is_dense(c) && hess_small_plan(c->d.dtype, c->d.p, c->K, c->nS, T, c->num_cus, &hs)) {
-        SSN_TRY(ensure_doubles(c, &c->hess, &c->hess_cap, hs.work));
+    bool formed = is_dense(c) && hess_small_plan(c->d.dtype, c->d.p, c->K, c->nS, T, c->num_cus, &hs);
+    if (formed) {
+        const int status = ensure_doubles(c, &c->hess, &c->hess_cap, hs.work);
+        if (status != SSN_OK && !no_room(status)) return status;
+        formed = status == SSN_OK;
+    }
+    if (formed) {
         RowsArgs r = rows_base(c);
         r.S = c->S;
         r.nrows = c->nS;
@@ -1327,7 +1354,11 @@ static int cg_enqueue(ssn_ctx *c, const void *G, double theta, int32_t T, void *
         SSN_HIP(c, launch_hess_small(c->d.dtype, hs, r, c->Pbuf, c->hess, h, c->st));
         return SSN_OK;
     }
-    if (!is_dense(c) && dual_ok(c, c->csc_samp, theta, T)) return dual_enqueue(c, G, theta, T, P_out, n_slope, !solve_W);
+    if (!is_dense(c) && dual_ok(c, c->csc_samp, theta, T)) {
+        const int status = dual_prepare(c);
+        if (status == SSN_OK) return dual_enqueue(c, G, theta, T, P_out, n_slope, !solve_W);
+        if (!no_room(status)) return status;
+    }
     if (!c->cg_p) {
         SSN_TRY(vec_bytes_alloc(c, &c->cg_p));
         SSN_TRY(vec_bytes_alloc(c, &c->cg_r));
