@@ -1065,13 +1065,21 @@ void dense_rows_plan(int dtype, int64_t nrows, int64_t p, int K, int num_cus, in
     const int nb = (K + 15) / 16;
     // A wave per row block puts as many waves on the chip as there are row blocks, each with a chain of loads as long as a
     // row; a workgroup per row block shares the row out.  Its waves per block, by row blocks per compute unit (nblk /
-    // num_cus) and features, as measured on 1000 to 120000 rows of 64 to 2000 features with 2, 9 and 23 weight columns
-    // (objective call, us: wave per row block / this):
+    // num_cus) and features, as measured on 1000 to 120000 rows of 64 to 2000 features and, from 4.25 to 8 row blocks per
+    // compute unit, 784 to 8000 features, with 2, 9 and 23 weight columns (objective call, us: wave per row block / this; four
+    // waves in brackets):
     //   up to 2:     4 from 128 features, 8 from 256, 16 from 2048   fp64, K 23, 1000 x 331 22/13; fp32 13/10
     //   up to 2.5:   4 from 128                                      fp64, K 9, 8300 x 1300 71/29; fp32, K 23, x 331 14/13
     //   up to 4.25:  2 from 128, 4 from 256                          fp64, K 23, 16300 x 400 31/24; fp32, K 9, x 1900 56/32
-    //   up to 6:     2 from 128                                      fp64, K 9, 24000 x 784 54/36; fp32, K 23, x 256 16.1/15.2
-    //   up to 8:     2 from 512, one class tile                      fp64, K 9, 30000 x 512 38/32; K 23, x 1900 159/166 (not)
+    //   up to 6:     2 from 128; fp32: 4 beyond 2048, or from 1280 with two class tiles
+    //                                                                fp64, K 9, 24000 x 784 54/36, 22000 x 2500 168/114 (110), x 3072
+    //                                                                214/129 (131); K 23, 20000 x 3072 214/180 (204); fp32, K 23,
+    //                                                                x 256 16.1/15.2, 22000 x 1900 72/53, 2 waves 60; K 9, x 2500
+    //                                                                72/52, 2 waves 54
+    //   up to 8:     one class tile: 2 from 512, 4 beyond 2048; two: fp64, K 9, 30000 x 512 38/32, 26500 x 2500 171/129, 2 waves 139;
+    //                2 from 768 up to 7 (fp64), fp32: 4 from 1280    K 23, 28500 x 1300 105/94 (109), x 3072 235/219 (246), 30500 x
+    //                                                                2500 206, 2 and 4 waves 219 and 215 (not); fp32, K 23, 26500 x
+    //                                                                1900 72/60
     //   up to 10:    2 from 512, 4 from 768, one class tile; 4 from 512 (fp64) or 768 (fp32), two
     //                                                                fp64, K 9, 33000 x 1300 133/87; fp32, K 23, 40000 x 784 46/44
     //   beyond:      4 from 1280                                     fp64, K 9, 60000 x 1300 162/142, 50000 x 3072 303/280;
@@ -1083,8 +1091,8 @@ void dense_rows_plan(int dtype, int64_t nrows, int64_t p, int K, int num_cus, in
     else if (p >= 1280 && per_cu > 8.0) w = 4;
     else if (per_cu <= 2.5) w = p >= 128 ? 4 : 0;
     else if (per_cu <= 4.25) w = p >= 256 ? 4 : p >= 128 ? 2 : 0;
-    else if (per_cu <= 6.0) w = p >= 128 ? 2 : 0;
-    else if (per_cu <= 8.0) w = nb == 1 && p >= 512 ? 2 : 0;
+    else if (per_cu <= 6.0) w = f32 && p >= (nb == 1 ? 2049 : 1280) ? 4 : p >= 128 ? 2 : 0;
+    else if (per_cu <= 8.0) w = nb == 1 ? (p > 2048 ? 4 : p >= 512 ? 2 : 0) : f32 ? (p >= 1280 ? 4 : 0) : (p >= 768 && per_cu <= 7.0 ? 2 : 0);
     else if (per_cu <= 10.0) w = nb == 1 ? (p >= 768 ? 4 : p >= 512 ? 2 : 0) : (p >= (f32 ? 768 : 512) ? 4 : 0);
     if ((size_t)w * nb * 256 * es > 32768) w = 8;
     *split_waves = w;

@@ -22,6 +22,10 @@ CASES = [
     (17409, 140, 25, None, None),         # two
     (24577, 128, 18, None, None),         # two class tiles: a wave per row block
     (24577, 1100, 3, None, 3),            # one class tile: two
+    (17410, 1281, 19, None, None),        # two class tiles: fp64 two, fp32 four
+    (24600, 2050, 18, 2051, None),        # fp64 two, fp32 four
+    (25000, 2305, 9, None, 9),            # one class tile: four
+    (20000, 2307, 3, None, None),         # fp64 two, fp32 four
     (32784, 513, 18, 520, None),          # fp64 four, fp32 a wave per row block
     (32784, 1280, 2, None, None),         # binary kernels next to it: one weight column
     (32784, 1281, 3, None, None),         # four
