@@ -33,65 +33,55 @@ __device__ __forceinline__ int wave_min_int(int x)
     return x;
 }
 
-// z_c = sum over the row's stored entries of x * M[col, c]; result valid in lanes c < K.
+// One weight column: z = sum over the row's stored entries of x * M[col], an entry per lane; the result is in lane 0, zero in
+// the others.
 // (b, e: the row's range of stored entries, loaded by the caller one row ahead)
-template <typename T>
-__device__ __forceinline__ T csr_row_margin(const RowsArgs &a, int64_t b, int64_t e, int lane, int K, int NS)
+template <typename T> __device__ __forceinline__ T csr_row_margin1(const RowsArgs &a, int64_t b, int64_t e, int lane)
 {
-    const int s = lane / K, c = lane - s * K;
-    const bool act = s < NS;
     const T *vals = (const T *)a.vals;
     const T *M = (const T *)a.M;
     // eight stored entries per lane in flight: a row's gathers depend on its column indices, and a single chain
-    // of index -> gather round trips is what bounds a wave that owns a whole row (four in flight: the sampled
-    // product's rows kernel took 26 us instead of 21 on the sparse workload, the fp32 objective 150 instead of 136)
-    T acc = 0;
-    if (act) {
-        constexpr int U = 8;
-        T av[U];
+    // of index -> gather round trips is what bounds a wave that owns a whole row
+    constexpr int U = 8;
+    T av[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) av[u] = 0;
-        int64_t t = b + s;
-        for (; t + (U - 1) * NS < e; t += U * NS) {
-            int64_t cc[U];
-            T vv[U], mm[U];
+    for (int u = 0; u < U; ++u) av[u] = 0;
+    int64_t t = b + lane;
+    for (; t + (U - 1) * 64 < e; t += U * 64) {
+        int64_t cc[U];
+        T vv[U], mm[U];
 #pragma unroll
-            for (int u = 0; u < U; ++u) cc[u] = a.colidx[t + u * NS];
+        for (int u = 0; u < U; ++u) cc[u] = a.colidx[t + u * 64];
 #pragma unroll
-            for (int u = 0; u < U; ++u) vv[u] = vals[t + u * NS];
+        for (int u = 0; u < U; ++u) vv[u] = vals[t + u * 64];
 #pragma unroll
-            for (int u = 0; u < U; ++u) mm[u] = M[cc[u] * a.ldm + c];
+        for (int u = 0; u < U; ++u) mm[u] = M[cc[u] * a.ldm];
 #pragma unroll
-            for (int u = 0; u < U; ++u) av[u] += vv[u] * mm[u];
-        }
-        if (t + NS < e) {          // two or more entries left for this lane: the same round with lanes switched off
-            int64_t cc[U];
-            T vv[U], mm[U];
-#pragma unroll
-            for (int u = 0; u < U; ++u) cc[u] = (t + u * NS < e) ? (int64_t)a.colidx[t + u * NS] : (int64_t)-1;
-#pragma unroll
-            for (int u = 0; u < U; ++u) vv[u] = (t + u * NS < e) ? vals[t + u * NS] : T(0);
-#pragma unroll
-            for (int u = 0; u < U; ++u) mm[u] = (cc[u] >= 0) ? M[cc[u] * a.ldm + c] : T(0);
-#pragma unroll
-            for (int u = 0; u < U; ++u) av[u] += vv[u] * mm[u];
-        } else if (t < e) {
-            av[0] += vals[t] * M[(int64_t)a.colidx[t] * a.ldm + c];
-        }
-#pragma unroll
-        for (int u = 1; u < U; ++u) av[0] += av[u];
-        acc = av[0];
+        for (int u = 0; u < U; ++u) av[u] += vv[u] * mm[u];
     }
-    // fold the NS slots onto slot 0: a tree over the slots (log2 NS steps in a fixed order; with one weight column a
-    // wave holds 64 slots, and adding them one after the other was most of a short row's time)
-    int top = 1;
-    while (top < NS) top <<= 1;
-    T tot = acc;
-    for (int h = top >> 1; h >= 1; h >>= 1) {
-        const T o = __shfl(tot, (lane + h * K) & 63);
-        if (s + h < NS) tot += o;
+    if (t + 64 < e) {              // two or more entries left for this lane: the same round with lanes switched off
+        int64_t cc[U];
+        T vv[U], mm[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) cc[u] = (t + u * 64 < e) ? (int64_t)a.colidx[t + u * 64] : (int64_t)-1;
+#pragma unroll
+        for (int u = 0; u < U; ++u) vv[u] = (t + u * 64 < e) ? vals[t + u * 64] : T(0);
+#pragma unroll
+        for (int u = 0; u < U; ++u) mm[u] = (cc[u] >= 0) ? M[cc[u] * a.ldm] : T(0);
+#pragma unroll
+        for (int u = 0; u < U; ++u) av[u] += vv[u] * mm[u];
+    } else if (t < e) {
+        av[0] += vals[t] * M[(int64_t)a.colidx[t] * a.ldm];
     }
-    return (lane < K) ? tot : T(0);
+#pragma unroll
+    for (int u = 1; u < U; ++u) av[0] += av[u];
+    // a tree over the lanes, in a fixed order (adding 64 lanes one after the other was most of a short row's time)
+    T tot = av[0];
+    for (int h = 32; h >= 1; h >>= 1) {
+        const T o = __shfl(tot, (lane + h) & 63);
+        if (lane + h < 64) tot += o;
+    }
+    return lane == 0 ? tot : T(0);
 }
 
 // SPLIT: a pass over few, long rows (the sampled rows of a matrix with hundreds of entries per row) leaves most of
@@ -111,7 +101,7 @@ __global__ __launch_bounds__(64 * ROWS_WAVES_PER_BLOCK) void csr_rows_kernel(Row
     const int NS = 64 / ((K + VEC - 1) / VEC);
     const bool cv = lane < K && (!SPLIT || wib == 0);            // lanes that hold (and store) a row's K values
     auto margin = [&](const RowsArgs &r, int64_t rb, int64_t re) {
-        if constexpr (VEC == 1) return csr_row_margin<T>(r, rb, re, lane, K, NS);
+        if constexpr (VEC == 1) return csr_row_margin1<T>(r, rb, re, lane);          // K == 1
         else return csr_row_margin_vec<T, T, VEC>(r.colidx, (const T *)r.vals, (const T *)r.M, r.ldm, rb, re, lane, K);
     };
     __shared__ T zs[SPLIT ? 2 * ROWS_WAVES_PER_BLOCK * 64 : 1];
@@ -225,8 +215,8 @@ template <typename T, int MODE> __global__ __launch_bounds__(64 * ROWS_WAVES_PER
     T zl = T(0);
     int64_t svl = 0;
     int labl = 0, cnt = 0;
-    // inside CG: the partials of r.r are on their way while the first margins are formed (RowsArgs::zs)
-    constexpr int RR = MODE == ROW_APPLY ? RED_MAX_PARTS / 64 : 1;
+    // inside CG: the (first) partials of r.r are on their way while the first margins are formed (RowsArgs::zs)
+    constexpr int RR = MODE == ROW_APPLY ? 4 : 1;
     double rr_part[RR], beta = 0.0;
     bool have_beta = true;
     if constexpr (MODE == ROW_APPLY) {
@@ -245,6 +235,7 @@ template <typename T, int MODE> __global__ __launch_bounds__(64 * ROWS_WAVES_PER
                 double v = 0.0;
 #pragma unroll
                 for (int u = 0; u < RR; ++u) v += rr_part[u];
+                for (int i = 64 * RR + lane; i < a.cg_nrr; i += 64) v += a.cg_rr[i];
                 v = __shfl(wave_inclusive_scan(v), 63);
                 const CgSlot *q = a.cg_prev;
                 const double rho = q->rho - q->alpha * a.cg_lambda * q->sigma;
@@ -299,7 +290,7 @@ template <typename T, int MODE> __global__ __launch_bounds__(64 * ROWS_WAVES_PER
         bn = a.rowptr[rown];
         en = a.rowptr[rown + 1];
         if constexpr (NEED_LAB) labn = a.labels[rown];
-        const T z = __shfl(csr_row_margin<T>(a, b, e, lane, 1, 64), 0);
+        const T z = __shfl(csr_row_margin1<T>(a, b, e, lane), 0);
         if (lane == cnt) {
             zl = z;
             svl = sv;
