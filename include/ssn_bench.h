@@ -37,6 +37,12 @@ int ssn_dense_path(const ssn_ctx *ctx);
  * dense_xtu_kernel forming U from the slices' partial margins); 0: the plain kernels served it. */
 int ssn_sampled_slices(const ssn_ctx *ctx);
 
+/* Which form the last direction of this context (ssn_cg, or an iteration of ssn_solve) was formed in: 0 = none yet; dense
+ * layouts: 1 = matrix-free, two launches per product, 2 = on the formed sub-sampled Hessian, in one workgroup; CSR layout:
+ * 3 = on the sample's columns, six launches per product, 4 = in the sample's row space, 5 = one weight column, three launches
+ * per product. */
+int ssn_direction_form(const ssn_ctx *ctx);
+
 #ifdef __cplusplus
 }
 #endif

@@ -55,6 +55,7 @@ struct ssn_ctx {
     bool next_ready = false;
     bool csc_full_built = false;
     int32_t csr_max_len = 0;      // longest row of the CSR matrix (read when the whole matrix's view is built)
+    int direction_form = 0;       // of the last direction (ssn_direction_form)
     bool csr_distinct = false;    // no row stores a column twice (every row's columns ascend strictly)
     // CSR with one weight column: what the lane-per-entry kernels of the full passes need (csr1_flat_kernel) -- the row
     // of every 64th stored entry, the rows' margins, the windows' leading partial sums
@@ -1329,6 +1330,7 @@ static int cg_enqueue(ssn_ctx *c, const void *G, double theta, int32_t T, void *
         if (status != SSN_OK && !no_room(status)) return status;
         formed = status == SSN_OK;
     }
+    c->direction_form = formed ? 2 : is_dense(c) ? 1 : 3;
     if (formed) {
         RowsArgs r = rows_base(c);
         r.S = c->S;
@@ -1356,6 +1358,7 @@ static int cg_enqueue(ssn_ctx *c, const void *G, double theta, int32_t T, void *
     }
     if (!is_dense(c) && dual_ok(c, c->csc_samp, theta, T)) {
         const int status = dual_prepare(c);
+        if (status == SSN_OK) c->direction_form = 4;
         if (status == SSN_OK) return dual_enqueue(c, G, theta, T, P_out, n_slope, !solve_W);
         if (!no_room(status)) return status;
     }
@@ -1410,6 +1413,7 @@ static int cg_enqueue(ssn_ctx *c, const void *G, double theta, int32_t T, void *
             c->cg_pb_cap = need + need / 8 + 64;
         }
         if (csc1) {
+            c->direction_form = 5;
             v.p = sv.ncols;
             v.ld = 1;
             v.pbest = c->cg_pb;
@@ -2069,6 +2073,8 @@ int ssn_sampled_slices(const ssn_ctx *c)
     if (!c) return SSN_E_INVALID_ARG;
     return c->z_active ? c->z_slices : 0;
 }
+
+int ssn_direction_form(const ssn_ctx *c) { return c ? c->direction_form : SSN_E_INVALID_ARG; }
 
 int ssn_dense_path(const ssn_ctx *c)
 {

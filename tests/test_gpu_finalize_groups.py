@@ -39,8 +39,8 @@ def test_groups_of_elements(n, p, C, nS, ldw, dtype):
     Gh, Gd = pair.block(G_ref)
     pair.gpu.ssn_hess_prepare(Wd, pair.idx(S))
     # Rows of norm one and lambda = 0.01: H_S has eigenvalues between lambda and about 0.1, so a product's rounding (1e-16, or
-    # the 1e-7 of fp32 operands) is amplified at most some tenfold per iteration at first and hardly behind the fourth
-    tol = 1e-10 if dtype == F64 else 1e-3
+    # the 6e-8 of fp32 operands) is amplified at most some tenfold; observed 1.3e-7 in fp32
+    tol = 1e-10 if dtype == F64 else 2e-6
     ref, out = pair.oracle.cg(Wh, S, Gh, 1e-4, 6), pair.gpu.ssn_cg(Gd, 1e-4, 6)
     torch.cuda.synchronize()
     assert (out["iters"], out["flags"]) == (ref["iters"], ref["flags"])

@@ -54,9 +54,8 @@ def test_columns_stored_more_than_once(n, p, mean, C, nS, repeats, dtype):
     HV = pair.gpu.ssn_hess_apply(Vd)
     torch.cuda.synchronize()
     assert rel_err(pair.host(HV), pair.oracle.hessvec(Wh, S, Vh)) <= TOL[dtype] / 10
-    # rows of norm one, lambda 0.01: a product's rounding (1e-16 / 1e-7) grows at most thirtyfold in each of the first iterations
-    # and hardly behind the fourth
-    tol = 1e-10 if dtype == F64 else 1e-4
+    # rows of norm one, lambda 0.01: a product's rounding (1e-16 / 6e-8) is amplified at most some thirtyfold; observed 3e-7 in fp32
+    tol = 1e-10 if dtype == F64 else 5e-6
     for theta, T in [(1e-4, 5), (0.2, 20)]:
         ref, out = pair.oracle.cg(Wh, S, Gh, theta, T), pair.gpu.ssn_cg(Gd, theta, T)
         torch.cuda.synchronize()
