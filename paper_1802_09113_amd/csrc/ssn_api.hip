@@ -1197,17 +1197,20 @@ static bool dual_ok(const ssn_ctx *c, const CscView &v, double theta, int32_t T)
     if (!c->csr_distinct) return false;
     if (!(theta >= 1e-5) || v.nnz < 1 || !v.has_support || v.nrows > GRAM_ROWS_MAX) return false;
     if (dual_blocks(v.nrows, c->K) > RED_MAX_PARTS) return false;
-    // Where the line lies: the Gram matrix against what T iterations save, in us as measured on text-like and evenly spread
-    // columns (direction with its preparation, nS rows; iteration on the sample's columns / in the row space, then the
-    // direction of ten products):
-    //   1355191 columns, 450 entries a row, K 19, fp64:  nS 100 40/10, 698/444; 1000 85/12, 1231/594; 2000 125/20, 1724/868
-    //   the same, K 1, fp32:                             nS 400 16/9,  336/321; 1000 16/11, 357/360 (refused)
-    //   20958 columns, 57 entries a row, K 4, fp64:      nS 1000 32/10, 469/293; 2000 35/14, 500/371
-    //   12500 columns, 400 entries a row, K 1, fp64:     nS 400 17/9,  343/317; 1000 16/11, 345/367 (refused)
+    // Where the line lies: the Gram matrix against what T iterations save, in us as fitted to 128 samples of 100 to 2000 rows of
+    // text-like and evenly spread columns (on them it takes the faster form, within 3 percent, but for one at 7).  For example,
+    // direction with its preparation, nS rows; iteration on the sample's columns / in the row space, then the direction of ten
+    // products, of four:
+    //   1355191 columns, 450 entries a row, K 19, fp64:  nS 100 35/10, 628/430, 421/372; 1000 74/13, 1110/577, 665/497; 2000 111/22,
+    //                                                    1552/845, 886/711
+    //   9000 columns, 450 entries a row, K 32, fp64:     nS 1000 50/14, 690/433, 388/349; 2000 70/25, 921/723, 500/575 (refused)
+    //   1355191 columns, 450 entries a row, K 1, fp64:   nS 400 17/9,  326/310, 226/254 (refused); 1000 20/10, 372/361 (refused)
+    //   20958 columns, 57 entries a row, K 4, fp64:      nS 1000 26/10, 393/278, 236/217; 2000 29/14, 430/368, 255/284 (refused)
+    //   20958 columns, 57 entries a row, K 1, fp32:      nS 400 14/9,  252/249; 1000 14/10, 261/271 (refused)
     const double n = (double)v.nrows / 1000.0, nnz = (double)v.nnz, es = (double)c->es, K = (double)c->K;
-    const double iter = c->K == 1 ? 15.1 + nnz / 400e3 : 27.0 + (9.0 * (double)v.ncols + 2.0 * nnz) * K * es / 7e6;
-    const double here = 9.5 + n * n * (1.0 + K / 16.0), gram = 45.0 + 100.0 * n * nnz / 1e6;
-    return (double)T * (iter - here) * 0.9 > gram;
+    const double iter = c->K == 1 ? 14.5 + nnz / 100e3 : 24.0 + nnz / 60e3 + (2.2 * (double)v.ncols + 0.1 * nnz) * K * es / 1e6;
+    const double here = 10.1 + n * n * (0.6 + K / 8.7), gram = 32.0 + 6.5 * n * n + (51.0 + 50.0 * n) * nnz / 1e6;
+    return (double)T * (iter - here) * 0.95 > gram;
 }
 
 // the Gram matrix (if it was not made with the view) and the workspace

@@ -227,7 +227,11 @@ hipError_t launch_check_range_post(const int32_t *v, int count, int64_t lo, int6
 hipError_t launch_check_rowptr(const int32_t *rowptr, int64_t n, int64_t nnz, int32_t *bad, hipStream_t st);
 hipError_t launch_check_ascending(const int32_t *rowptr, const int32_t *colidx, int64_t n, int32_t *bad, hipStream_t st);
 
-constexpr int GRAM_ROWS_MAX = 2048;      // the most rows of a sample whose Gram matrix is formed
+// The most rows of a sample whose Gram matrix is formed.  gram_rare_kernel keeps four copies of a row of it in LDS, 64 KB here:
+// beyond, one workgroup fits a compute unit and the rows' cost grows twice.  Directions of ten products, sample's columns / row
+// space, us: 3000 rows of 450 entries, K 19, fp64 2064/1367 and fp32 1358/1245, but 9000 columns, K 32, fp64 1164/1355, and 57
+// entries a row, K 4, 470/558; 4000 rows 2414/1911, 1561/1712, 1383/2010 and 499/730.
+constexpr int GRAM_ROWS_MAX = 2048;
 
 // ---- column-sorted view of a set of CSR rows (csc.hip) --------------------------------------------
 struct CscView {
