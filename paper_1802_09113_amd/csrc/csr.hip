@@ -203,7 +203,8 @@ __global__ __launch_bounds__(64 * ROWS_WAVES_PER_BLOCK) void csr_rows_kernel(Row
 // Here a wave parks the margins of its rows in its lanes, one row per lane, and does the per-row work for up to 64
 // rows at once.  Margins, prefetch and partial sums as in csr_rows_kernel; the loss of a wave is the sum of its lanes'
 // sums (fixed order).
-template <typename T, int MODE> __global__ __launch_bounds__(64 * ROWS_WAVES_PER_BLOCK) void csr_rows1_kernel(RowsArgs a)
+// CG: a product inside Alg. 2 (ROW_APPLY, RowsArgs::zs).
+template <typename T, int MODE, bool CG = false> __global__ __launch_bounds__(64 * ROWS_WAVES_PER_BLOCK) void csr_rows1_kernel(RowsArgs a)
 {
     if (a.skip && *a.skip) return;
     const int lane = threadIdx.x & 63, wib = threadIdx.x >> 6;
@@ -215,13 +216,22 @@ template <typename T, int MODE> __global__ __launch_bounds__(64 * ROWS_WAVES_PER
     T zl = T(0);
     int64_t svl = 0;
     int labl = 0, cnt = 0;
-    // inside CG: the (first) partials of r.r are on their way while the first margins are formed (RowsArgs::zs)
-    constexpr int RR = MODE == ROW_APPLY ? 4 : 1;
-    double rr_part[RR], beta = 0.0;
+    // CG: the state and the (first) partials of r.r are on their way while the first margins are formed, a row's probability and
+    // its margin of the product before while its own is; a wave looks at them when it has margins to work on
+    constexpr int RR = CG ? 4 : 1;
+    double rr_part[RR], beta = 0.0, rr_prev = 1.0, rho = 0.0, alpha_prev = 0.0, sigma = 0.0, goff = 0.0, zo = 0.0;
+    T pin = T(0);
     bool have_beta = true;
-    if constexpr (MODE == ROW_APPLY) {
-        have_beta = !(a.zs && a.cg_prev);
+    int ended = 0;
+    if constexpr (CG) {
+        have_beta = !a.cg_prev;
         if (!have_beta) {
+            rr_prev = a.cg_prev->rr;
+            rho = a.cg_prev->rho;
+            alpha_prev = a.cg_prev->alpha;
+            sigma = a.cg_prev->sigma;
+            goff = a.cg_prev->goff;
+            ended = a.cg_prev->done | a.cg_prev->brk;
 #pragma unroll
             for (int u = 0; u < RR; ++u) {
                 rr_part[u] = 0.0;
@@ -230,27 +240,25 @@ template <typename T, int MODE> __global__ __launch_bounds__(64 * ROWS_WAVES_PER
         }
     }
     auto flush = [&]() {
-        if constexpr (MODE == ROW_APPLY) {
+        if constexpr (CG) {
             if (!have_beta) {
                 double v = 0.0;
 #pragma unroll
                 for (int u = 0; u < RR; ++u) v += rr_part[u];
                 for (int i = 64 * RR + lane; i < a.cg_nrr; i += 64) v += a.cg_rr[i];
                 v = __shfl(wave_inclusive_scan(v), 63);
-                const CgSlot *q = a.cg_prev;
-                const double rho = q->rho - q->alpha * a.cg_lambda * q->sigma;
-                beta = (q->done || q->brk) ? 0.0 : (v + rho * rho * q->goff) / q->rr;
+                rho -= alpha_prev * a.cg_lambda * sigma;
+                beta = ended ? 0.0 : (v + rho * rho * goff) / rr_prev;
                 have_beta = true;
             }
         }
         if (lane < cnt) {
             if constexpr (MODE == ROW_APPLY) {
-                if (a.zs) {
-                    const double z = (double)zl + (a.cg_prev ? beta * a.zs[svl] : 0.0);
+                if constexpr (CG) {
+                    const double z = (double)zl + beta * zo;
                     a.zs[svl] = z;
                     zl = (T)z;
                 }
-                const T pin = ((const T *)a.Pin)[svl * a.KP];
                 const T t = pin * zl;
                 const T u = pin * zl - pin * t;              // eq. (12) with one class
                 ((T *)a.UP)[svl * a.KP] = u;
@@ -290,8 +298,18 @@ template <typename T, int MODE> __global__ __launch_bounds__(64 * ROWS_WAVES_PER
         bn = a.rowptr[rown];
         en = a.rowptr[rown + 1];
         if constexpr (NEED_LAB) labn = a.labels[rown];
+        T pn = T(0);
+        double zn = 0.0;
+        if constexpr (MODE == ROW_APPLY) {
+            pn = ((const T *)a.Pin)[sv * a.KP];
+            if (CG && a.cg_prev) zn = a.zs[sv];
+        }
         const T z = __shfl(csr_row_margin1<T>(a, b, e, lane), 0);
         if (lane == cnt) {
+            if constexpr (MODE == ROW_APPLY) {
+                pin = pn;
+                zo = zn;
+            }
             zl = z;
             svl = sv;
             labl = lab;
@@ -489,7 +507,10 @@ template <typename T> static hipError_t csr_rows_dispatch(const RowsArgs &a, int
         case ROW_OBJ: hipLaunchKernelGGL((csr_rows1_kernel<T, ROW_OBJ>), grid, block, 0, st, a); return hipGetLastError();
         case ROW_GRAD: hipLaunchKernelGGL((csr_rows1_kernel<T, ROW_GRAD>), grid, block, 0, st, a); return hipGetLastError();
         case ROW_PREP: hipLaunchKernelGGL((csr_rows1_kernel<T, ROW_PREP>), grid, block, 0, st, a); return hipGetLastError();
-        case ROW_APPLY: hipLaunchKernelGGL((csr_rows1_kernel<T, ROW_APPLY>), grid, block, 0, st, a); return hipGetLastError();
+        case ROW_APPLY:
+            if (a.zs) hipLaunchKernelGGL((csr_rows1_kernel<T, ROW_APPLY, true>), grid, block, 0, st, a);
+            else hipLaunchKernelGGL((csr_rows1_kernel<T, ROW_APPLY>), grid, block, 0, st, a);
+            return hipGetLastError();
         case ROW_PRED: hipLaunchKernelGGL((csr_rows1_kernel<T, ROW_PRED>), grid, block, 0, st, a); return hipGetLastError();
         default: break;                  // ROW_MARGIN
         }
