@@ -29,7 +29,10 @@
  *     the index check of every call that validates a sample (ssn_hess_prepare,
  *     ssn_hessvec, ssn_gradient_sampled, ssn_solve).
  *   - Element type T is float (SSN_F32) or double (SSN_F64) for X/vals, W, V,
- *     G, HV, P.  Sums over rows are carried in fp64 in both cases.
+ *     G, HV, P.  Sums over rows are carried in fp64 in both cases: a lane or a
+ *     matrix-core accumulator adds the rows of its share in T, the shares are
+ *     added in fp64.  (The formed Hessian of small problems, see ssn_cg, is
+ *     summed in fp64 throughout.)
  *   - W, V, G, HV, P (direction) are p-by-K, row-major, class index fastest,
  *     leading dimension ldw >= K elements: entry (j,c) at [j*ldw + c].  This
  *     is the paper's vec(.) ordering up to a fixed permutation, so norms and
@@ -218,7 +221,8 @@ int ssn_hessvec(ssn_ctx *ctx, const void *W, const int32_t *S, int64_t nS, const
  * G [dev] right-hand side gradient; P_out [dev] receives p_best; at most T products.
  * trace [host, nullable, 3*T doubles]: per product k the step alpha_k, ||r_{k+1}||, s_k^T H s_k.
  * The whole loop runs on the device without host round trips; the call synchronises once at
- * the end to fill info / trace.  The iterates are those of Alg. 2 up to rounding; how they are formed:
+ * the end to fill info / trace.  The iterates are those of Alg. 2 up to rounding, whichever of these forms takes the call
+ * (rules on sizes, nS, T and theta; ssn_direction_form of ssn_bench.h tells which did):
  *   - No inner product waits for a vector: with Z = X_S v and U the rows of eq. (12), v^T (X_S^T U) is the
  *     sum over the sample of z_i . u_i, which the product's own launch leaves as partial sums.
  *   - Dense layouts: the product is applied to the residual r_k (H is linear, so with line 12
@@ -226,9 +230,18 @@ int ssn_hessvec(ssn_ctx *ctx, const void *W, const int32_t *S, int64_t nS, const
  *     s_k^T H s_k = r_k^T H r_k + 2 beta r_k^T H s_{k-1} + beta^2 s_{k-1}^T H s_{k-1}: two launches per product.
  *     The theta test for r_k is made after product k has been enqueued, so a run that stops early has made
  *     one product more than info.iters reports (its result is discarded).
+ *   - Dense layouts, p K of a few hundred (at most 1024, and the K (K + 1) / 2 distinct p x p blocks at most some 32 000
+ *     elements in fp64, 70 000 in fp32), where T products cost more than forming it: H_S is formed once and all of Alg. 2
+ *     runs in one workgroup.
  *   - CSR layout: H_S acts as lambda I on every coordinate whose column no sampled row touches, so r, s, p
  *     stay multiples of g there; the vectors of Alg. 2 are kept on the sampled columns only, three scalars
- *     carry the rest, and P_out is assembled at the end. */
+ *     carry the rest, and P_out is assembled at the end: six launches per product, three with one weight column.
+ *   - CSR layout, nS <= 2048, theta >= 1e-5 and no row that stores a column twice, where T products cost more than the Gram
+ *     matrix X_S X_S^T: the vectors are a g + X_S^T Y, with nS x K coefficients Y in fp64.  ||r||^2 is then a difference of
+ *     terms of the size of ||g||^2: ||r_k|| (rel_res, trace, the theta test) carries an error of some
+ *     1e-16 ||g||^2 / ||r_k||, 1e-11 ||g|| at theta 1e-5.
+ * The formed H_S takes up to 28 MB of workspace, the Gram matrix up to 38 MB and 18 KB for each column of many entries in the
+ * sample (kept, and grown when a sample needs more); where it cannot be allocated the form before it in this list serves. */
 int ssn_cg(ssn_ctx *ctx, const void *G, double theta, int32_t T, void *P_out,
            ssn_cg_info *info, double *trace);
 
