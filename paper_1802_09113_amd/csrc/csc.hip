@@ -929,7 +929,9 @@ struct CscApply {
 // With a lane per weight column, entries handed round the group by lane shuffles and 8-byte gathers this kernel was bound
 // by instruction issue: 12 instructions per entry and three entries at a time at K = 19 (9 M entries of 817 000 columns,
 // K 19: 234 us in fp32 against 306 in fp64).
-template <typename T, int VEC> __global__ __launch_bounds__(256) void csc_piece_kernel(CscApply a)
+// Six waves per SIMD asked for: left to itself the compiler takes 82 registers for fp64, which makes five (148 against 138 us
+// for the average of both uses in a solver iteration).
+template <typename T, int VEC> __global__ __launch_bounds__(256, 6) void csc_piece_kernel(CscApply a)
 {
     if (a.skip && *a.skip) return;
     double coef = a.coef;
